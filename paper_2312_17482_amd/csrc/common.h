@@ -104,9 +104,8 @@ mb_status launch_add_layernorm_bwd(mb_dtype dt, const void* dy, const void* s, c
                                    const float* rstd, int T_cap, const int32_t* meta, int W, void* ds, float* dgamma,
                                    float* dbeta, float* part, const int32_t* dy_rows, hipStream_t stream);
 
-// Generic ALU kernels: any D <= 128, fp32 or bf16 storage, fp32 arithmetic.
-// Their backward keeps two score rows of max_seqlen floats plus two head vectors in LDS and must stay
-// within the 64 KB a kernel may use without opting in to more.
+// Generic kernels: any D <= 128, fp32 or bf16 storage, fp32 arithmetic.  Longer promises are refused (part of the
+// calls' contract; the kernels themselves stream their keys and have no such limit).
 static constexpr int kGenericMaxSeqlen = 8000;
 mb_status launch_attn_fwd_generic(const AttnShape& s, mb_dtype dt, const void* q, const void* k, const void* v,
                                   int64_t qs, int64_t ks, int64_t vs, void* o, int64_t os, float* lse,

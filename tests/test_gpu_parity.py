@@ -152,6 +152,64 @@ def test_generic_fp32_shapes(mb, D, H, lengths, L):
     compare_attention(got, ref, c["mask"], F32_TOL, 1e-4, "generic fp32 D=%d" % D)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("D", [8, 16, 24, 48, 64, 96, 104, 128])
+def test_generic_tile_edges(mb, bf16, D):
+    """The fp32-arithmetic kernels at the edges of their blocks (16 queries per wave, 64 per workgroup, 32 keys per
+    tile) for every padded head size, sequences that start anywhere inside a block of packed tokens, empty ones in
+    between; bf16 storage with head size 64 reaches them through a negative scale.  Tolerances as for the other
+    fp32 / bf16 cases: the products are fp32 sums of at most 128 + 160 terms."""
+    lengths = [1, 0, 15, 16, 17, 0, 31, 32, 33, 63, 64, 65, 0, 96, 127, 129, 160, 0]
+    print("generic edges D=%d bf16=%s" % (D, bf16), flush=True)
+    c = wl.random_attention_case(23, lengths, 160, 2, D, std=0.5, bf16=bf16)
+    slopes = mb.mb_alibi_slopes(2)
+    scale = -0.2 if bf16 and D == 64 else c["scale"]
+    got = run_hip_path(mb, c, slopes, bf16=bf16, scale=scale)
+    ref = run_oracle(c, orc.alibi_slopes(2), scale=scale)
+    compare_attention(got, ref, c["mask"], BF16_TOL if bf16 else F32_TOL, 1e-3 if bf16 else 1e-4,
+                      "generic edges D=%d bf16=%s" % (D, bf16))
+
+
+def test_generic_token_rows_with_holes_and_more_sequences_than_blocks(mb):
+    """Rows looked up per token, a capacity T, and a batch of mostly empty sequences (more work slots than tokens)."""
+    B, L, H, D = 400, 24, 3, 20
+    mask = wl.random_mask(24, B, L, 0.5)
+    mask[np.random.default_rng(5).random(B) < 0.7] = 0
+    rng = np.random.default_rng(25)
+    qkv = torch.from_numpy(rng.standard_normal((B * L, 3, H, D), dtype=np.float32)).cuda()
+    do = torch.from_numpy(rng.standard_normal((B * L, H, D), dtype=np.float32)).cuda()
+    seqlens, cu, indices, meta = mb.mb_unpad_index(torch.from_numpy(mask).cuda())
+    T, _ = mb.mb_read_meta(meta)
+    slopes, scale, cap = mb.mb_alibi_slopes(H).cuda(), D ** -0.5, B * L
+    idx = indices[:T].long()
+    packed, dop = qkv[idx].contiguous(), do[idx].contiguous()
+    o, lse = mb.mb_alibi_attn_fwd(packed[:, 0], packed[:, 1], packed[:, 2], cu, L, slopes, scale)
+    g = torch.empty_like(packed)
+    mb.mb_alibi_attn_bwd(dop, packed[:, 0], packed[:, 1], packed[:, 2], o, lse, cu, L, slopes, scale, dq=g[:, 0],
+                         dk=g[:, 1], dv=g[:, 2])
+    o2, g2 = torch.full_like(do, 7.0), torch.full_like(qkv, 7.0)
+    lse2 = torch.full((H, cap), 7.0, device="cuda")
+    mb.mb_alibi_attn_fwd(qkv[:, 0], qkv[:, 1], qkv[:, 2], cu, L, slopes, scale, out=o2, lse=lse2, token_rows=indices,
+                         T=cap)
+    mb.mb_alibi_attn_bwd(do, qkv[:, 0], qkv[:, 1], qkv[:, 2], o2, lse2, cu, L, slopes, scale, dq=g2[:, 0], dk=g2[:, 1],
+                         dv=g2[:, 2], token_rows=indices, T=cap)
+    keep = torch.zeros(cap, dtype=torch.bool, device="cuda")
+    keep[idx] = True
+    assert torch.equal(o2[idx], o) and torch.equal(g2[idx], g) and torch.equal(lse2[:, :T], lse)
+    assert torch.all(o2[~keep] == 7.0) and torch.all(g2[~keep] == 7.0) and torch.all(lse2[:, T:] == 7.0)
+    lens = mask.sum(1)
+    at = np.concatenate([[0], np.cumsum(lens)])
+    for b in np.flatnonzero(lens)[:6]:   # against the oracle: the kept tokens at the front of their own row
+        n = int(lens[b])
+        x, d = (t[at[b]:at[b] + n].double().cpu().numpy()[None] for t in (packed, dop))
+        one = np.ones((1, n), dtype=np.int32)
+        O, _ = orc.attention_fwd(x[:, :, 0], x[:, :, 1], x[:, :, 2], one, orc.alibi_slopes(H), scale)
+        grads = orc.attention_bwd(d, x[:, :, 0], x[:, :, 1], x[:, :, 2], one, orc.alibi_slopes(H), scale)
+        assert np.max(np.abs(o[at[b]:at[b] + n].double().cpu().numpy() - O[0])) <= 1e-4
+        for i, ref in enumerate(grads):
+            assert np.max(np.abs(g[at[b]:at[b] + n, i].double().cpu().numpy() - ref[0])) <= 1e-4
+
+
 def test_fp32_scale_one_matches_eq1_literally(mb):
     """Eq. 1 as printed has no 1/sqrt(d): scale = 1."""
     c = wl.random_attention_case(22, [9, 31], 31, 2, 16, std=0.5)
