@@ -9,26 +9,30 @@
 //      the accumulators: neither projection is ever written to memory.
 //   2. plain:  y = a W2 with the [hidden, inter] matrix W2^T.
 //
-// Tiling: 256 tokens x 256 (or 192) weight rows per workgroup of 4 waves (2 x 2, each 128 x 128 or
-// 128 x 96 = 16 or 12 accumulator tiles of v_mfma_f32_32x32x16_bf16), k in steps of 64 through two LDS
-// stages (next stage is written while the current one is consumed: one barrier per step), the two steps
-// after that in flight in registers.  The narrower tile exists for the second projection, whose few
-// column tiles otherwise leave the last round of workgroups mostly empty.
+// Tiling: 64 to 320 tokens x 256 weight rows per workgroup of 8 waves (2 x 4, each up to 160 x 64 = 10 accumulator tiles
+// of v_mfma_f32_32x32x16_bf16), k in steps of 64 through two LDS stages that are filled by loads straight from
+// global memory.  One workgroup per compute unit walks its tiles without a break in the stream of loads.
 // The products are formed transposed (weight rows along accumulator rows, tokens along lanes), so a
-// lane owns runs of 4 consecutive output columns of one token; the tile is turned into full 128-byte
-// row segments through a wave-private LDS slab before it is stored.
+// lane owns runs of 4 consecutive output columns of one token; the tile is turned into row segments through a
+// wave-private LDS slab before it is stored.
+//
+// What bounds it, measured: the loads into LDS (without them the k loop runs 1.2 to 1.5 times as fast; they take about
+// 32 cycles per KB and compute unit in 128-byte pieces and half as long again in 64-byte ones), and the power limit: at
+// 1380 TFLOP/s (8192^3) the clock is down to 1.7 GHz and the matrix cores are busy 72 % of the time.  Hence the largest
+// tile that fits the registers (fewest bytes per product), no pass of the operands through registers, and whole cache
+// lines.  Tried: 256 x 128 tiles, two workgroups per compute unit (1035 TFLOP/s at 8192^3), four waves of 128 x 128 (1210),
+// rows of 64 bytes in four stages (1284); the former kernel, four waves of 128 x 128 staged through registers, one tile per
+// workgroup: 1262, and at K = 768 or 768 columns, where a tile's start and end or an empty last round weigh most:
+//   26963 x 768, K = 3072: 135 -> 101 us;  26963 x 6144, K = 768: 283 -> 224 us;  26963 x 768, K = 6144: 292 -> 220 us;
+//   8089 x 30528, K = 768: 496 -> 371 us (494 MB of output).
 #include "common.h"
 #include "mfma_util.h"
-
-
-
 
 namespace mb {
 namespace {
 
-constexpr int kBM = 256;                              // tokens per workgroup
 constexpr int kBK = 64;                               // k per stage
-constexpr int kPitch = 72;                            // LDS row pitch, elements (144 B: conflict-free 16-byte reads)
+constexpr int kStages = 2;
 constexpr int kGroupM = 4;                            // token panels walked together (L2 reuse of the weight tiles)
 
 // GeLU(h) = h * Phi(h), the exact (error-function) form, with Phi evaluated by the classic five-term
@@ -67,257 +71,296 @@ __device__ __forceinline__ void gelu_and_grad(float h, float& val, float& grad) 
 // Epilogues of the GEMM kernel.
 constexpr int kPlain = 0;      // out = product
 constexpr int kGatedFwd = 1;   // out = GeLU(x W1) (*) x V on the accumulators (weight = W1^T over V^T)
+constexpr int kPartial = 3;    // out = fp32 sums of one of several splits of the contraction
 constexpr int kGateBwd = 2;    // the product is dA; with h | g read from `aux`: out = dA g GeLU'(h) | dA GeLU(h)
 
-template <int kMode, int kNB>   // kNB: 32-row weight blocks per wave (4 or 3); workgroup = 64 * kNB weight rows
-__global__ __launch_bounds__(256, 1) void ffn_gemm_kernel(const uint16_t* __restrict__ X, int ldx,
-                                                          const uint16_t* __restrict__ W, int ldw, int K,
-                                                          int n_tiles, int gate_row, int w_rows, int T_cap,
+// One wave moves 64 x 16 bytes from global memory straight into LDS: lane l's piece lands at byte `lds` + 16 l.  Lanes
+// whose offset lies outside the descriptor deposit zeros.  (Inline assembly on purpose: it writes no register, and the
+// compiler, which cannot tell one part of LDS from another, would wait for every such load before any LDS read if it
+// knew of it.  The waits are the kernel's own, see stage_ready.)
+__device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t lane_off, u32x4 rsrc, uint32_t scalar_off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(lds), "v"(lane_off), "s"(rsrc), "s"(scalar_off)
+               : "memory");
+}
+// Descriptor of `bytes` bytes from `base` (both wave-uniform).
+__device__ __forceinline__ u32x4 raw_rsrc(const uint16_t* base, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  u32x4 r;
+  r[0] = __builtin_amdgcn_readfirstlane((uint32_t)a);
+  r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu);
+  r[2] = __builtin_amdgcn_readfirstlane(bytes);
+  r[3] = 0x00020000u;   // raw buffer, 32-bit data format (gfx9 family)
+  return r;
+}
+// All but the newest `kNewer` loads of this wave have arrived and its LDS reads are done; then the workgroup's barrier.
+template <int kNewer>
+__device__ __forceinline__ void stage_ready() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(kNewer) : "memory");
+}
+
+// One workgroup of 8 waves (2 along the tokens by 4 along the weight rows) per compute unit walks the tiles blockIdx.x,
+// + gridDim.x, ...  A tile is 64 kMB tokens x 256 weight rows; a wave computes 32 kMB x 64 of it.
+// X rows and W rows are both K elements long.  kPartial: the contraction is split, tile id = split * tiles + tile, and
+// the split's fp32 sums go to out (as float) + split * T_cap * ldo.
+template <int kMode, int kMB>
+__global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __restrict__ X,
+                                                          const uint16_t* __restrict__ W, int K, int n_tiles,
+                                                          int splits, int gate_row, int w_rows, int T_cap,
                                                           const int32_t* __restrict__ meta,
                                                           uint16_t* __restrict__ out, int ldo,
                                                           const uint16_t* __restrict__ aux, int gate_col) {
   constexpr bool kGated = kMode == kGatedFwd;
-  static_assert(!kGated || kNB == 4, "the gated epilogue pairs weight blocks 0,1 with 2,3");
-  static_assert(kMode != kGateBwd || kNB == 4, "the gate-backward epilogue is written for 64-column passes");
-  constexpr int kBN = 64 * kNB;                     // weight rows per workgroup
-  constexpr int kStage = (kBM + kBN) * kPitch;      // elements per LDS stage
-  constexpr int kLoads = 8 + 2 * kNB;               // 16-byte loads per thread and k step (32 rows per load)
-  constexpr int kSlots = 4 * kNB;                   // matrix instructions per sub-step
-  constexpr int kFrags = 4 + kNB;                   // fragments per sub-step
-  __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kStage];
+  constexpr int kBM = 64 * kMB, kBN = 256, kNB = 2;
+  constexpr int kRows = kBM + kBN;                  // rows of a stage: tokens, then weight rows
+  constexpr int kStageElems = kRows * kBK;
+  constexpr int kLoads = kRows / 64;                // 8-row loads per wave and k step
+  constexpr int kSlabElems = 32 * 32;               // per wave: 32 tokens x 32 columns on their way out
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kStages * kStageElems + 8 * kSlabElems];
 
   // (readfirstlane: tells the compiler the value is wave-uniform, so descriptors built from it stay scalar)
   const int T = __builtin_amdgcn_readfirstlane(meta ? min(meta[0], T_cap) : T_cap);
   // (the grid is sized for T_cap rows; the tile map uses the token panels that hold tokens, so that the
   // idle workgroups are the last ones and not the share of one XCD)
   const int m_tiles = (T + kBM - 1) / kBM;
-  if ((int)blockIdx.x >= m_tiles * n_tiles) return;
+  const int tiles = m_tiles * n_tiles;
+  const int total = kMode == kPartial ? tiles * splits : tiles;
+  if ((int)blockIdx.x >= total) return;
+  constexpr int kOutCols = kGated ? kBN / 2 : kBN;    // output columns per tile
+  const int nk = kMode == kPartial ? K / (kBK * splits) : K / kBK;   // k steps per tile
 
-  // Workgroup -> tile.  Consecutive workgroup ids go round-robin to the 8 XCDs; give every XCD a
-  // contiguous run of tiles, walked kGroupM token panels at a time, so that the tiles resident on one
+  // Tile id -> token panel, weight tile and first k step.  Consecutive workgroup ids go round-robin to the 8 XCDs; give
+  // every XCD a contiguous run of tiles, walked kGroupM token panels at a time, so that the tiles resident on one
   // XCD share their token panels and weight tiles in that XCD's L2.
-  const int total = m_tiles * n_tiles, per = total >> 3;
-  int lin = blockIdx.x;
-  if (lin < (per << 3)) lin = (lin & 7) * per + (lin >> 3);
-  const int group = lin / (kGroupM * n_tiles);
-  const int first_m = group * kGroupM;
-  const int gsize = min(m_tiles - first_m, kGroupM);
-  const int rem = lin - group * (kGroupM * n_tiles);
-  // (the divisions run on the vector unit; readfirstlane moves the wave-uniform results back to scalars)
-  const int tile_m = __builtin_amdgcn_readfirstlane(first_m + rem % gsize);
-  const int tile_n = __builtin_amdgcn_readfirstlane(rem / gsize);
-  const int m0 = tile_m * kBM;
-  if (m0 >= T) return;
-  constexpr int kOutCols = kGated ? kBN / 2 : kBN;    // output columns per workgroup
-  const int n0 = tile_n * kOutCols;
+  auto locate = [&](int id, int& m0, int& n0, int& k0) {
+    const int per = total >> 3;
+    int lin = id;
+    if (lin < (per << 3)) lin = (lin & 7) * per + (lin >> 3);
+    k0 = 0;
+    if (kMode == kPartial) {
+      k0 = __builtin_amdgcn_readfirstlane(lin / tiles) * nk;
+      lin = lin % tiles;
+    }
+    const int group = lin / (kGroupM * n_tiles);
+    const int first_m = group * kGroupM;
+    const int gsize = min(m_tiles - first_m, kGroupM);
+    const int rem = lin - group * (kGroupM * n_tiles);
+    // (the divisions run on the vector unit; readfirstlane moves the wave-uniform results back to scalars)
+    m0 = __builtin_amdgcn_readfirstlane(first_m + rem % gsize) * kBM;
+    n0 = __builtin_amdgcn_readfirstlane(rem / gsize) * kOutCols;
+  };
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 31, g = lane >> 5;
-  const int wm = wave >> 1, wn = wave & 1;
+  const int wm = wave >> 2, wn = wave & 3;
 
-  // Global -> LDS staging: a row of a stage is 128 bytes = 8 lanes x 16 bytes; 32 rows per load.
-  const int lrow = tid >> 3, lchunk = (tid & 7) * 8;
-  // Buffer loads: address = descriptor base + scalar offset + one per-lane offset, so the loads of a
-  // step need no vector address arithmetic.  Token rows get one descriptor per load whose extent ends at
-  // row T: rows at or beyond T read as zero instead of touching memory that may not exist.  (Byte
-  // offsets fit 32 bits: the host checks rows * row length < 2^31 elements.)
-  constexpr int kRsrcFlags = 0x00020000;        // raw buffer, 32-bit data format (gfx9 family)
-  const uint32_t xlane = ((uint32_t)lrow * (uint32_t)ldx + lchunk) * 2u;
-  const uint32_t wlane = ((uint32_t)lrow * (uint32_t)ldw + lchunk) * 2u;
-  const __amdgpu_buffer_rsrc_t wrs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W), 0, w_rows * ldw * 2, kRsrcFlags);
-  // Load i of a step: i < 8 token rows 32 i .., else weight rows 32 (i - 8) .. of the tile (stage row 32 i).
-  // (descriptor and offsets are scalar arithmetic on wave-uniform values)
-  auto fetch_one = [&](u32x4 (&st)[kLoads], int i, int k0) {
-    if (i < 8) {
-      const int first = m0 + 32 * i;
-      const int rows = __builtin_amdgcn_readfirstlane(max(min(T - first, 32), 0));   // (the clamp is a vector op)
-      const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<uint16_t*>(X) + (int64_t)first * ldx, 0, rows * ldx * 2, kRsrcFlags);
-      st[i] = __builtin_amdgcn_raw_buffer_load_b128(xrs, xlane, k0 * 2, 0);
-    } else {
-      const int p = i - 8;
-      const int wr = kGated ? (p < 4 ? n0 + 32 * p : gate_row + n0 + 32 * (p - 4)) : n0 + 32 * p;
-      st[i] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wlane, (wr * ldw + k0) * 2, 0);
+  // Global -> LDS: a row of a stage is 128 bytes = 8 pieces, a load carries 8 rows (whole cache lines: rows of 64 bytes,
+  // with twice the stages, measured a fifth slower).  Piece x of row r sits at position x ^ (r / 2) % 8, so that a
+  // fragment read (one piece of 16 consecutive rows per quarter wave) touches every bank once.  Row bounds are the
+  // descriptors': token rows at or beyond T and weight rows past the matrix deposit zeros.
+  // (The k offset is the scalar operand, which takes no part in the range check.)
+  // Load i of wave w carries rows 8 (w + 8 i) .. of the stage.
+  const uint32_t lane_off =
+      ((uint32_t)(lane >> 3) * (uint32_t)K + (((lane & 7) ^ (4 * (wave & 1) + (lane >> 4))) * 8)) * 2u;
+  const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(
+      (__attribute__((address_space(3))) uint16_t*)smem);
+  u32x4 rsrc[kLoads];
+  uint32_t k_bytes = 0;              // scalar offset of the tile's first k step
+  auto aim = [&](int id) {           // descriptors of this wave's share of a tile's rows
+    int m0, n0, k0;
+    locate(id, m0, n0, k0);
+    k_bytes = (uint32_t)k0 * (kBK * 2);
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int row = 8 * (wave + 8 * i), r = row - kBM;   // r: row of the weight tile
+      const bool token = row < kBM;
+      const int first = token ? m0 + row : kGated ? (r < kBN / 2 ? n0 + r : gate_row + n0 + r - kBN / 2) : n0 + r;
+      const int rows = max(min((token ? T : w_rows) - first, 8), 0);
+      rsrc[i] = raw_rsrc((token ? X : W) + (int64_t)first * K, (uint32_t)rows * (uint32_t)K * 2u);
     }
   };
-  auto deposit_one = [&](const u32x4 (&st)[kLoads], int i, uint16_t* buf) {
-    *reinterpret_cast<u32x4*>(&buf[(32 * i + lrow) * kPitch + lchunk]) = st[i];
+  auto fetch_one = [&](int i, int stage, int kt) {
+    load_to_lds(lds0 + (stage * kStageElems + 8 * (wave + 8 * i) * kBK) * 2, lane_off, rsrc[i], k_bytes + kt * (kBK * 2));
   };
-  // Two register sets: while one k step is computed, the next one goes from registers to LDS and the two
-  // after it are in flight from memory (a load has two whole steps to arrive).
-  u32x4 st0[kLoads], st1[kLoads];
 
-  // Fragment rows of this wave inside a stage: tokens at rows 0..255, weight rows from 256 on.
-  // Gated: accumulator rows nb = 0,1 are columns of x W1, nb = 2,3 the same columns of x V.
-  int xoff[4], woff[kNB];
+  // Fragments of this wave inside a stage: tokens at rows 0 .., weight rows from kBM on.  Gated: the first weight block
+  // holds columns of x W1, the second the same columns of x V.
+  // (row r = multiple of 32 + c: its swizzle is (c / 2) % 8; piece 2 kk + g of the row)
+  uint32_t frag[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) xoff[i] = (wm * 128 + i * 32 + c) * kPitch + g * 8;
+  for (int kk = 0; kk < 4; ++kk) frag[kk] = c * kBK + (((2 * kk + g) ^ ((c >> 1) & 7)) * 8);
+  const uint32_t xrow = wm * (32 * kMB) * kBK;
+  const uint32_t wrow = (kBM + wn * (kGated ? 32 : 64)) * kBK;
+  constexpr uint32_t kWBlock = (kGated ? kBN / 2 : 32) * kBK;   // from the first weight block of the wave to the second
+  bf16x8 xf[2][kMB], wf[2][kNB];
+  auto read_frag = [&](int stage, int kk, int i) {   // weight fragments first
+    const uint16_t* cur = smem + stage * kStageElems;
+    if (i < kNB) wf[kk & 1][i] = lds_read8(cur + wrow + i * kWBlock + frag[kk]);
+    else xf[kk & 1][i - kNB] = lds_read8(cur + xrow + (i - kNB) * 32 * kBK + frag[kk]);
+  };
+  constexpr int kFrags = kMB + kNB, kMfma = kMB * kNB;
+  f32x16 acc[kNB][kMB];
+
+  // The k steps of all the workgroup's tiles form one sequence; the loads run two steps ahead of the products, across the
+  // end of a tile, so that the next tile's first steps arrive during this one's last products and its epilogue.
+  // (Past the last tile the loads repeat it: their number stays the same and nobody reads them.)
+  int f_tile = blockIdx.x, f_kt = 0;
+  aim(f_tile);
+  auto advance = [&]() {
+    if (++f_kt < nk) return;
+    f_kt = 0;
+    if (f_tile + (int)gridDim.x < total) {
+      f_tile += gridDim.x;
+      aim(f_tile);
+    }
+  };
 #pragma unroll
-  for (int i = 0; i < kNB; ++i) {
-    const int wr = kGated ? (i >> 1) * 128 + wn * 64 + (i & 1) * 32 : wn * (32 * kNB) + i * 32;
-    woff[i] = (kBM + wr + c) * kPitch + g * 8;
+  for (int st = 0; st < kStages; ++st) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) fetch_one(i, st, f_kt);
+    advance();
   }
+  stage_ready<kLoads>();
+#pragma unroll
+  for (int i = 0; i < kFrags; ++i) read_frag(0, 0, i);
 
-  f32x16 acc[kNB][4];
+  // store instructions of an epilogue, per wave (they are issued also where every lane is out of range)
+  constexpr int kStores = kMode == kPartial ? 0 : kMode == kGatedFwd ? 2 * kMB : kMode == kGateBwd ? 8 * kMB : 4 * kMB;
+  bool first = true;
+  int stage = 0;
+  for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
 #pragma unroll
-  for (int nb = 0; nb < kNB; ++nb)
+    for (int nb = 0; nb < kNB; ++nb)
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+      for (int mb = 0; mb < kMB; ++mb)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[nb][mb][v] = 0.f;
-
-  const int nk = K / kBK;                       // even (the host checks K % 128 == 0)
-  // (the first two k steps are requested together, so that only one memory latency is exposed)
+        for (int v = 0; v < 16; ++v) acc[nb][mb][v] = 0.f;
+    // One step = four quarters of kMfma matrix instructions (k = 16 each); during a quarter the next one's fragments are
+    // read.  In front of the last quarter stands the barrier, behind which nobody reads this stage any more and the
+    // next one has arrived: the last quarter reads the next stage's first fragments, and this stage is refilled.  The
+    // memory instructions are spread over the matrix instructions: the waves share one address unit and one LDS, and a
+    // wave that issues its loads in one go waits for everybody's.
+    // Loads and stores complete in the order they were issued, and the loads of a tile's second step are issued before
+    // the stores of the tile before it: the first barrier of a tile lets those stores (at least kStores) travel on.
+#pragma unroll 1
+    for (int kt = 0; kt < nk; ++kt) {
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) fetch_one(st0, i, 0);
+      for (int kk = 0; kk < 4; ++kk) {
+        if (kk == 3) {
+          if (kt == 0 && !first) stage_ready<kStores>();
+          else stage_ready<0>();
+        }
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) fetch_one(st1, i, kBK);
+        for (int x = 0; x < kMfma; ++x) {
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) deposit_one(st0, i, smem);
+          for (int i = x; i < kFrags; i += kMfma) read_frag(kk == 3 ? stage ^ 1 : stage, (kk + 1) & 3, i);
+          if (kk == 3) {
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) fetch_one(st0, i, min(2, nk - 1) * kBK);
-  __syncthreads();
-
-  // One k step = 4 sub-steps of 4 kNB matrix instructions (k = 16 each) on stage `cur`.  Issue order is
-  // written out by hand and fenced (with one wave per SIMD nothing but the order hides latencies): in
-  // front of every matrix instruction go at most three memory instructions, so that their issue hides
-  // under the previous matrix instruction: one LDS read of the NEXT sub-step's fragments
-  // (double-buffered) in each of the first slots; in sub-step 0 the LDS writes that move register set
-  // `st` (tile kt + 1) to stage `nxt`; in sub-step 1 the global loads that refill `st` with tile
-  // kt + 3.  The workgroup barrier sits before sub-step 3: by then this wave has read all of `cur` and
-  // written its share of `nxt`, so sub-step 3 already reads the first fragments of `nxt`, and the next
-  // step may overwrite `cur`.  No branches: the last steps fetch a clamped, redundant tile and deposit
-  // it where nobody reads.
-  bf16x8 wf[2][kNB], xf[2][4];
-  // Fragment i of sub-step kk: i = 0..3 token fragments, then the weight fragments.
-  auto read_frag = [&](const uint16_t* stage_ptr, int kk, int buf, int i) {
-    if (i < 4) xf[buf][i] = lds_read8(stage_ptr + xoff[i] + kk * 16);
-    else wf[buf][i - 4] = lds_read8(stage_ptr + woff[i - 4] + kk * 16);
-  };
-#pragma unroll
-  for (int i = 0; i < kFrags; ++i) read_frag(smem, 0, 0, i);
-  auto step = [&](const uint16_t* cur, uint16_t* nxt, u32x4 (&st)[kLoads], int k_fetch) {
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      if (kk == 3) __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kNB; ++q) {
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-          const int slot = 4 * q + mb;
-          if (slot < kFrags) {
-            if (kk < 3) read_frag(cur, kk + 1, (kk + 1) & 1, slot);
-            else read_frag(nxt, 0, 0, slot);
-          }
-#pragma unroll
-          for (int i = slot; i < kLoads; i += kSlots) {
-            if (kk == 0) deposit_one(st, i, nxt);
-            if (kk == 1) fetch_one(st, i, k_fetch);
+            for (int i = x; i < kLoads; i += kMfma) fetch_one(i, stage, f_kt);
           }
           __builtin_amdgcn_sched_barrier(0);
-          acc[q][mb] = mfma32(wf[kk & 1][q], xf[kk & 1][mb], acc[q][mb]);
+          acc[x % kNB][x / kNB] = mfma32(wf[kk & 1][x % kNB], xf[kk & 1][x / kNB], acc[x % kNB][x / kNB]);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
+      advance();
+      stage ^= 1;
     }
-  };
-  for (int kt = 0; kt < nk; kt += 2) {
-    step(smem, smem + kStage, st1, min(kt + 3, nk - 1) * kBK);
-    step(smem + kStage, smem, st0, min(kt + 4, nk - 1) * kBK);
-  }
-  __syncthreads();
+    first = false;
 
-  // Epilogue: through a wave-private slab of 128 tokens x 64 columns (both stages are free now), two
-  // 32-column accumulator blocks at a time (the last pass of an odd kNB has one).
-  uint16_t* slab = smem + wave * (128 * kPitch);
-  const int row_base = m0 + wm * 128;
-  constexpr int kOutBlocks = kGated ? 2 : kNB;      // 32-column output blocks per wave
+    int m0, n0, k0;
+    locate(tile, m0, n0, k0);
+    if (kMode == kPartial) {   // fp32 sums: a lane owns runs of 4 consecutive columns of one token
+      float* dst = reinterpret_cast<float*>(out) + (int64_t)(k0 / nk) * T_cap * ldo;
 #pragma unroll
-  for (int b0 = 0; b0 < kOutBlocks; b0 += 2) {
-    constexpr int kTwo = 2;
-    const int nblk = (kOutBlocks - b0) < kTwo ? (kOutBlocks - b0) : kTwo;
-    // Gate backward: the h and g values this lane will combine with dA are requested before the
-    // accumulators go through the slab, so that they arrive meanwhile (the staging registers of the k
-    // loop are free now).
-    u32x4 hpre[kMode == kGateBwd ? 16 : 1], gpre[kMode == kGateBwd ? 16 : 1];
-    if (kMode == kGateBwd) {
-      const int orow = lane >> 3, ocol = (lane & 7) * 8;
-      const int colp = n0 + wn * (32 * kOutBlocks) + b0 * 32 + ocol;
+      for (int mb = 0; mb < kMB; ++mb) {
+        const int row = m0 + wm * (32 * kMB) + mb * 32 + c;
 #pragma unroll
-      for (int it = 0; it < 16; ++it) {
-        const int row = row_base + 8 * it + orow;
-        hpre[it] = gpre[it] = u32x4{0u, 0u, 0u, 0u};
-        if (row < T) {
-          const int64_t at = (int64_t)row * ldo + colp;
-          hpre[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aux + at));
-          gpre[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aux + at + gate_col));
+        for (int nb = 0; nb < kNB; ++nb) {
+          const int col = n0 + wn * 64 + nb * 32 + 4 * g;
+          if (row < T && col < w_rows) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              *reinterpret_cast<float4*>(dst + (int64_t)row * ldo + col + 8 * j) =
+                  make_float4(acc[nb][mb][4 * j], acc[nb][mb][4 * j + 1], acc[nb][mb][4 * j + 2], acc[nb][mb][4 * j + 3]);
+          }
         }
       }
+      continue;
     }
+    // Epilogue: 32 tokens x 32 columns at a time through the wave's own slab, out of which rows leave as 64-byte
+    // segments.  (Piece x of a row at position x ^ (row / 4) % 4; the LDS operations of one wave complete in order.)
+    uint16_t* slab = smem + kStages * kStageElems + wave * kSlabElems;
+    const int orow = lane >> 2, opiece = lane & 3;
+    const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc(
+        out + (int64_t)m0 * ldo, 0, (uint32_t)min(T - m0, kBM) * (uint32_t)ldo * 2u, 0x00020000);
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      if (nb < nblk) {
+    for (int mb = 0; mb < kMB; ++mb) {
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
+      for (int nb = 0; nb < (kGated ? 1 : kNB); ++nb) {
+        const int col = n0 + wn * (kGated ? 32 : 64) + nb * 32 + opiece * 8;
+        const int row0 = m0 + wm * (32 * kMB) + mb * 32 + orow;
+        const bool cols_ok = kGated || col < w_rows;
+        const uint32_t off0 = ((uint32_t)(row0 - m0) * (uint32_t)ldo + (uint32_t)col) * 2u;
+        u32x4 hv[2], gv[2];   // gate backward: requested before the accumulators go through the slab
+        if (kMode == kGateBwd) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            float r[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              if (kGated) r[i] = gelu_exact(acc[nb][mb][4 * j + i]) * acc[nb + 2][mb][4 * j + i];
-              else r[i] = acc[b0 + nb][mb][4 * j + i];
+          for (int u = 0; u < 2; ++u) {
+            hv[u] = gv[u] = u32x4{0u, 0u, 0u, 0u};
+            if (row0 + 16 * u < T) {
+              const int64_t at = (int64_t)(row0 + 16 * u) * ldo + col;
+              hv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aux + at));
+              gv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aux + at + gate_col));
             }
-            u32x2 w;
-            w[0] = pack_bf16(r[0], r[1]);
-            w[1] = pack_bf16(r[2], r[3]);
-            *reinterpret_cast<u32x2*>(&slab[(mb * 32 + c) * kPitch + nb * 32 + 8 * j + 4 * g]) = w;
           }
         }
-      }
-    }
-    // (same wave wrote and reads the slab: LDS operations of one wave complete in order)
-    const int col0 = n0 + wn * (32 * kOutBlocks) + b0 * 32;
-    if (nblk == 2) {                // rows of 64 columns = 128 bytes = 8 lanes
-      const int orow = lane >> 3, ocol = (lane & 7) * 8;
 #pragma unroll
-      for (int it = 0; it < 16; ++it) {
-        const int row = 8 * it + orow;
-        const u32x4 w = *reinterpret_cast<const u32x4*>(&slab[row * kPitch + ocol]);
-        if (row_base + row < T) {
-          const int64_t at = (int64_t)(row_base + row) * ldo + col0 + ocol;
+        for (int j = 0; j < 4; ++j) {
+          float r[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (kGated) r[i] = gelu_exact(acc[0][mb][4 * j + i]) * acc[1][mb][4 * j + i];
+            else r[i] = acc[nb][mb][4 * j + i];
+          }
+          u32x2 w;
+          w[0] = pack_bf16(r[0], r[1]);
+          w[1] = pack_bf16(r[2], r[3]);
+          *reinterpret_cast<u32x2*>(&slab[c * 32 + ((j ^ ((c >> 2) & 3)) * 8) + 4 * g]) = w;
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int r = 16 * u + orow;
+          const u32x4 w = *reinterpret_cast<const u32x4*>(&slab[r * 32 + ((opiece ^ ((r >> 2) & 3)) * 8)]);
+          // (rows at or beyond T and columns past the matrix: an offset past the descriptor, the store is dropped)
+          // (as the vector operand, where all of it is checked)
+          const bool ok = row0 + 16 * u < T && cols_ok;
+          const uint32_t off = ok ? off0 + (uint32_t)(32 * u) * (uint32_t)ldo : 0xffffffe0u;
           if (kMode == kGateBwd) {
-            // w holds 8 values of dA; h and g of the same positions came from aux (columns col and
+            // w holds 8 values of dA; h and g of the same positions come from aux (columns col and
             // gate_col + col of a row); dh and dg go to the same two places of out
-            const u32x4 hv = hpre[kMode == kGateBwd ? it : 0], gv = gpre[kMode == kGateBwd ? it : 0];
             u32x4 dh, dg;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               float v0, d0, v1, d1;
-              gelu_and_grad(__uint_as_float(hv[i] << 16), v0, d0);
-              gelu_and_grad(__uint_as_float(hv[i] & 0xffff0000u), v1, d1);
+              gelu_and_grad(__uint_as_float(hv[u][i] << 16), v0, d0);
+              gelu_and_grad(__uint_as_float(hv[u][i] & 0xffff0000u), v1, d1);
               const float a0 = __uint_as_float(w[i] << 16), a1 = __uint_as_float(w[i] & 0xffff0000u);
-              const float g0 = __uint_as_float(gv[i] << 16), g1 = __uint_as_float(gv[i] & 0xffff0000u);
+              const float g0 = __uint_as_float(gv[u][i] << 16), g1 = __uint_as_float(gv[u][i] & 0xffff0000u);
               dh[i] = pack_bf16(a0 * g0 * d0, a1 * g1 * d1);
               dg[i] = pack_bf16(a0 * v0, a1 * v1);
             }
-            *reinterpret_cast<u32x4*>(out + at) = dh;
-            *reinterpret_cast<u32x4*>(out + at + gate_col) = dg;
+            __builtin_amdgcn_raw_buffer_store_b128(dh, ors, off, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(dg, ors, ok ? off + (uint32_t)gate_col * 2u : off, 0, 0);
           } else {
-            *reinterpret_cast<u32x4*>(out + at) = w;
+            __builtin_amdgcn_raw_buffer_store_b128(w, ors, off, 0, 0);
           }
         }
       }
-    } else {                        // rows of 32 columns = 64 bytes = 4 lanes
-      const int orow = lane >> 2, ocol = (lane & 3) * 8;
-#pragma unroll
-      for (int it = 0; it < 8; ++it) {
-        const int row = 16 * it + orow;
-        const u32x4 w = *reinterpret_cast<const u32x4*>(&slab[row * kPitch + ocol]);
-        if (row_base + row < T) *reinterpret_cast<u32x4*>(out + (int64_t)(row_base + row) * ldo + col0 + ocol) = w;
-      }
     }
   }
+  stage_ready<0>();   // no load may still be on its way to LDS that the next workgroup owns
 }
 
 // a = GeLU(h) (*) g, elementwise over [T, inter]: the separate activation pass of the unfused arrangements
@@ -499,6 +542,26 @@ __global__ __launch_bounds__(256) void ffn_wgrad_reduce_kernel(const float* __re
   }
 }
 
+// out[t, :] = sum over splits of partial[s][t, :], in order, for t < T (rows of N floats, N a multiple of 4).
+__global__ __launch_bounds__(256) void add_splits_kernel(const float* __restrict__ partial, int splits, int T_cap,
+                                                         const int32_t* __restrict__ meta, int N,
+                                                         uint16_t* __restrict__ out) {
+  const int T = meta ? min(meta[0], T_cap) : T_cap;
+  const int64_t pitch = (int64_t)T_cap * N / 4, count = (int64_t)T * N / 4;
+  const float4* src = reinterpret_cast<const float4*>(partial);
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x) {
+    float4 a = src[i];
+    for (int s = 1; s < splits; ++s) {
+      const float4 b = src[s * pitch + i];
+      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+    }
+    u32x2 w;
+    w[0] = pack_bf16(a.x, a.y);
+    w[1] = pack_bf16(a.z, a.w);
+    reinterpret_cast<u32x2*>(out)[i] = w;
+  }
+}
+
 // out[c][r] = in[r][c] for a [R, C] bf16 matrix (R, C multiples of 64): 64 x 64 tiles through LDS.
 __global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* __restrict__ in, int R, int C,
                                                         uint16_t* __restrict__ out) {
@@ -514,37 +577,63 @@ __global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* __restri
 
 }  // namespace
 
-// out[t, n] = sum_k x[t, k] * wt[n, k] with the plain epilogue; the tile width (256 or 192 weight rows) is the
-// one that wastes less of the last round of workgroups on the 256 compute units.
+constexpr int kComputeUnits = 256;
+
+template <int kMode, int kMB>
+static void launch_gemm_tile(const void* x, const void* wt, int K, int n_cols, int splits, int gate_row, int w_rows,
+                             int T_cap, const int32_t* meta, void* out, int ldo, const uint16_t* aux, int gate_col,
+                             hipStream_t stream) {
+  const int m_tiles = (T_cap + 64 * kMB - 1) / (64 * kMB), n_tiles = (n_cols + 255) / 256;
+  const int64_t total = (int64_t)m_tiles * n_tiles * splits;
+  ffn_gemm_kernel<kMode, kMB><<<dim3((unsigned)(total < kComputeUnits ? total : kComputeUnits)), dim3(512), 0, stream>>>(
+      static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_tiles, splits, gate_row, w_rows, T_cap,
+      meta, static_cast<uint16_t*>(out), ldo, aux, gate_col);
+}
+
+// Estimated microseconds of a product with tiles of 64 mb tokens and `splits` shares of the contraction.  A k step of a
+// tile took 0.31 (mb + 1) us with all compute units busy (26963 x 768, K = 6144: mb = 1 .. 4 68, 89, 120, 152 us a
+// round) and no less than 0.7 us alone, where the loads' latency shows.
+static double gemm_cost(int T_cap, int n_cols, int K, int mb, int splits) {
+  const int64_t tiles = (int64_t)((T_cap + 64 * mb - 1) / (64 * mb)) * ((n_cols + 255) / 256) * splits;
+  const double step = 0.31 * (mb + 1);
+  return (double)((tiles + kComputeUnits - 1) / kComputeUnits) * (K / (kBK * splits)) * (step < 0.7 ? 0.7 : step);
+}
+
+// The tile height (64 to 320 tokens) with the least cost: a tile count just above a multiple of 256 leaves the last
+// round nearly empty (26963 x 768, K = 3072: tiles of 256 tokens 132 us, of 320 tokens 101 us; 945 x 6144, K = 768:
+// 256 tokens 20 us, 128 tokens 14 us).
+static int tile_height(int T_cap, int n_cols, int K, int splits) {
+  int best = 5;
+  for (int mb = 4; mb > 0; --mb)
+    if (gemm_cost(T_cap, n_cols, K, mb, splits) < gemm_cost(T_cap, n_cols, K, best, splits)) best = mb;
+  return best;
+}
+
+template <int kMode>
+static void launch_gemm(const void* x, const void* wt, int K, int n_cols, int splits, int gate_row, int w_rows, int T_cap,
+                        const int32_t* meta, void* out, int ldo, const uint16_t* aux, int gate_col, hipStream_t stream) {
+#define MB_TILE(n) \
+  launch_gemm_tile<kMode, n>(x, wt, K, n_cols, splits, gate_row, w_rows, T_cap, meta, out, ldo, aux, gate_col, stream)
+  switch (tile_height(T_cap, n_cols, K, splits)) {
+    case 1: MB_TILE(1); break;
+    case 2: MB_TILE(2); break;
+    case 3: MB_TILE(3); break;
+    case 4: MB_TILE(4); break;
+    default: MB_TILE(5);
+  }
+#undef MB_TILE
+}
+
+// out[t, n] = sum_k x[t, k] * wt[n, k] with the plain epilogue.
 static void launch_plain(const void* x, const void* wt, int T_cap, const int32_t* meta, int n_in, int n_out, void* y,
                          hipStream_t stream) {
-  const int m_tiles = (T_cap + kBM - 1) / kBM;
-  const auto cost = [&](int bn) {
-    const int tiles = m_tiles * (n_out / bn);
-    return (double)((tiles + 255) / 256) * bn;
-  };
-  const bool narrow = n_out % 192 == 0 && (n_out % 256 != 0 || cost(192) < cost(256));
-  if (narrow) {
-    const int n_tiles = n_out / 192;
-    ffn_gemm_kernel<kPlain, 3><<<dim3(m_tiles * n_tiles), dim3(256), 0, stream>>>(
-        static_cast<const uint16_t*>(x), n_in, static_cast<const uint16_t*>(wt), n_in, n_in, n_tiles, 0, n_out, T_cap,
-        meta, static_cast<uint16_t*>(y), n_out, nullptr, 0);
-  } else {
-    const int n_tiles = n_out / 256;
-    ffn_gemm_kernel<kPlain, 4><<<dim3(m_tiles * n_tiles), dim3(256), 0, stream>>>(
-        static_cast<const uint16_t*>(x), n_in, static_cast<const uint16_t*>(wt), n_in, n_in, n_tiles, 0, n_out, T_cap,
-        meta, static_cast<uint16_t*>(y), n_out, nullptr, 0);
-  }
+  launch_gemm<kPlain>(x, wt, n_in, n_out, 1, 0, n_out, T_cap, meta, y, n_out, nullptr, 0, stream);
 }
 
 mb_status launch_geglu_fwd(const void* x, const void* w1v, const void* w2, int T_cap, const int32_t* meta,
                            int hidden, int inter, void* act, void* y, hipStream_t stream) {
   if (T_cap == 0) return MB_OK;
-  const int m_tiles = (T_cap + kBM - 1) / kBM;
-  const int n_tiles = inter / 128;
-  ffn_gemm_kernel<kGatedFwd, 4><<<dim3(m_tiles * n_tiles), dim3(256), 0, stream>>>(
-      static_cast<const uint16_t*>(x), hidden, static_cast<const uint16_t*>(w1v), hidden, hidden, n_tiles, inter,
-      2 * inter, T_cap, meta, static_cast<uint16_t*>(act), inter, nullptr, 0);
+  launch_gemm<kGatedFwd>(x, w1v, hidden, 2 * inter, 1, inter, 2 * inter, T_cap, meta, act, inter, nullptr, 0, stream);
   launch_plain(act, w2, T_cap, meta, inter, hidden, y, stream);
   return check_launch("ffn_gemm_kernel");
 }
@@ -613,15 +702,34 @@ mb_status launch_geglu_bwd(const void* dy, const void* x, const void* w1v, const
   transpose_kernel<<<dim3(hidden / 64, 2 * inter / 64), dim3(256), 0, stream>>>(static_cast<const uint16_t*>(w1v),
                                                                                2 * inter, hidden, w1vt);
   if (T_cap > 0) {
-    const int m_tiles = (T_cap + kBM - 1) / kBM;
     // h | g = x (W1 | V): handed over by a caller that stored it, else computed again
     if (!hg_saved) launch_plain(x, w1v, T_cap, meta, hidden, 2 * inter, ws + off[0], stream);
     // dA = dy W2^T, and on its way out  dh = dA g GeLU'(h),  dg = dA GeLU(h)
-    ffn_gemm_kernel<kGateBwd, 4><<<dim3(m_tiles * (inter / 256)), dim3(256), 0, stream>>>(
-        static_cast<const uint16_t*>(dy), hidden, w2t, hidden, hidden, inter / 256, 0, inter, T_cap, meta, dhg,
-        2 * inter, hg, inter);
-    // dx = dh W1^T + dg V^T = (dh | dg) (W1 | V)^T
-    launch_plain(dhg, w1vt, T_cap, meta, 2 * inter, hidden, dx, stream);
+    launch_gemm<kGateBwd>(dy, w2t, hidden, inter, 1, 0, inter, T_cap, meta, dhg, 2 * inter, hg, inter, stream);
+    // dx = dh W1^T + dg V^T = (dh | dg) (W1 | V)^T: the longest contraction onto the fewest columns.  With few tokens its
+    // tiles leave most compute units idle, so the contraction is split where that pays for adding up the shares
+    // (945 tokens, 768 x 3072: 74 us in one piece, 25 us in 8 shares); the partial sums lie where the weight
+    // gradients' partial tiles come later.
+    int splits = 1;
+    double least = 1e300;
+    for (int s = 1; s <= 8; s *= 2) {   // (2 inter / 64 is a multiple of 8)
+      if ((size_t)s * T_cap > (size_t)kWgradSplits * 2 * inter) break;
+      const double cost = gemm_cost(T_cap, hidden, 2 * inter, tile_height(T_cap, hidden, 2 * inter, s), s) +
+                          (s > 1 ? 6.0 + 8.0 * s * T_cap * hidden / 4.5e6 : 0.0);   // launch, write and read at 4.5 TB/s
+      if (cost < least) {
+        least = cost;
+        splits = s;
+      }
+    }
+    if (splits == 1) {
+      launch_plain(dhg, w1vt, T_cap, meta, 2 * inter, hidden, dx, stream);
+    } else {
+      launch_gemm<kPartial>(dhg, w1vt, 2 * inter, hidden, splits, 0, hidden, T_cap, meta, partial, hidden, nullptr, 0,
+                            stream);
+      const int64_t pieces = (int64_t)T_cap * hidden / 4;
+      add_splits_kernel<<<dim3((unsigned)(pieces < 256 * 1024 ? (pieces + 255) / 256 : 1024)), dim3(256), 0, stream>>>(
+          partial, splits, T_cap, meta, hidden, static_cast<uint16_t*>(dx));
+    }
   }
   // dW2^T[c, j] = sum_t dy[t, c] act[t, j];   d(W1|V)^T[j, c] = sum_t (dh|dg)[t, j] x[t, c]
   launch_wgrad(dy, hidden, act, inter, hidden, inter, T_cap, meta, partial, dw2, stream);
