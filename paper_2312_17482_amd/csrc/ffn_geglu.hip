@@ -296,6 +296,19 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
     const int orow = lane >> 2, opiece = lane & 3;
     const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc(
         out + (int64_t)m0 * ldo, 0, (uint32_t)min(T - m0, kBM) * (uint32_t)ldo * 2u, 0x00020000);
+    // Gate backward: h and g of a pass are requested kAhead passes before it (rows past the last token read the last one;
+    // their results are dropped).
+    constexpr int kAhead = 2;
+    u32x4 hv[kMB * kNB][2], gv[kMB * kNB][2];
+    auto request = [&](int p) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int row = m0 + wm * (32 * kMB) + (p / kNB) * 32 + 16 * u + orow;
+        const int64_t at = (int64_t)min(row, T - 1) * ldo + n0 + wn * 64 + (p % kNB) * 32 + opiece * 8;
+        hv[p][u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aux + at));
+        gv[p][u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aux + at + gate_col));
+      }
+    };
 #pragma unroll
     for (int mb = 0; mb < kMB; ++mb) {
 #pragma unroll
@@ -304,17 +317,13 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
         const int row0 = m0 + wm * (32 * kMB) + mb * 32 + orow;
         const bool cols_ok = kGated || col < w_rows;
         const uint32_t off0 = ((uint32_t)(row0 - m0) * (uint32_t)ldo + (uint32_t)col) * 2u;
-        u32x4 hv[2], gv[2];   // gate backward: requested before the accumulators go through the slab
+        const int pass = mb * kNB + nb;
         if (kMode == kGateBwd) {
+          if (pass == 0) {
 #pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            hv[u] = gv[u] = u32x4{0u, 0u, 0u, 0u};
-            if (row0 + 16 * u < T) {
-              const int64_t at = (int64_t)(row0 + 16 * u) * ldo + col;
-              hv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aux + at));
-              gv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aux + at + gate_col));
-            }
+            for (int p = 0; p < kAhead; ++p) request(p);
           }
+          if (pass + kAhead < kMB * kNB) request(pass + kAhead);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -344,10 +353,10 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               float v0, d0, v1, d1;
-              gelu_and_grad(__uint_as_float(hv[u][i] << 16), v0, d0);
-              gelu_and_grad(__uint_as_float(hv[u][i] & 0xffff0000u), v1, d1);
+              gelu_and_grad(__uint_as_float(hv[pass][u][i] << 16), v0, d0);
+              gelu_and_grad(__uint_as_float(hv[pass][u][i] & 0xffff0000u), v1, d1);
               const float a0 = __uint_as_float(w[i] << 16), a1 = __uint_as_float(w[i] & 0xffff0000u);
-              const float g0 = __uint_as_float(gv[u][i] << 16), g1 = __uint_as_float(gv[u][i] & 0xffff0000u);
+              const float g0 = __uint_as_float(gv[pass][u][i] << 16), g1 = __uint_as_float(gv[pass][u][i] & 0xffff0000u);
               dh[i] = pack_bf16(a0 * g0 * d0, a1 * g1 * d1);
               dg[i] = pack_bf16(a0 * v0, a1 * v1);
             }
