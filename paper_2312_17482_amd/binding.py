@@ -110,26 +110,33 @@ def _check(status: int) -> None:
         raise MosaicAttnError(status, _lib.mb_last_error().decode())
 
 
+# The marshalling itself: small batches are bound by it (a whole layer step of 8 x 128 positions is nine launches and
+# took 84 us of host time for 49 us of kernels), so what is called on every argument touches each tensor once.
+_DTYPE_CODES = {torch.float32: MB_F32, torch.bfloat16: MB_BF16}
+_current_device = torch.cuda.current_device
+_raw_stream = torch._C._cuda_getCurrentRawStream   # (torch.cuda.current_stream() makes a Stream object on every call)
+
+
 def _ptr(t) -> int | None:
     return None if t is None else t.data_ptr()
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return MB_F32
-    if t.dtype == torch.bfloat16:
-        return MB_BF16
-    raise TypeError("unsupported dtype %s" % t.dtype)
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError("unsupported dtype %s" % t.dtype)
+    return code
 
 
 def _row_stride(t: torch.Tensor) -> int:
     """[T, H, D] view with contiguous (H, D): returns the token stride in elements."""
-    assert t.dim() == 3 and t.stride(2) == 1 and t.stride(1) == t.shape[2], "need [T, H, D] with dense (H, D)"
-    return t.stride(0) if t.shape[0] > 1 else max(t.stride(0), t.shape[1] * t.shape[2])
+    shape, strides = t.shape, t.stride()
+    assert len(strides) == 3 and strides[2] == 1 and strides[1] == shape[2], "need [T, H, D] with dense (H, D)"
+    return strides[0] if shape[0] > 1 else max(strides[0], shape[1] * shape[2])
 
 
 def mb_version() -> int:
@@ -209,12 +216,14 @@ def mb_alibi_attn_fwd(q, k, v, cu_seqlens, max_seqlen: int, slopes, softmax_scal
         out = torch.empty((q.shape[0], H, D), dtype=q.dtype, device=q.device)
     if lse is None:
         lse = torch.empty((H, T), dtype=torch.float32, device=q.device)
-    need = 0 if plan is not None else mb_alibi_attn_fwd_workspace_bytes(B, T, max_seqlen, H, D, _dtype_code(q))
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+    dt = _dtype_code(q)
+    if workspace is None and plan is None:
+        need = _lib.mb_alibi_attn_fwd_workspace_bytes(B, T, max_seqlen, H, D, dt)
+        if need > 0:
+            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
     _check(_lib.mb_alibi_attn_fwd(_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v),
                                   _ptr(cu_seqlens), B, T, max_seqlen, H, D, _ptr(slopes), float(softmax_scale),
-                                  _dtype_code(q), _ptr(out), _row_stride(out), _ptr(lse), _ptr(workspace),
+                                  dt, _ptr(out), _row_stride(out), _ptr(lse), _ptr(workspace),
                                   0 if workspace is None else workspace.numel(), _ptr(key_lens), _ptr(token_rows),
                                   _ptr(plan), _stream()))
     return out, lse
@@ -251,12 +260,13 @@ def mb_alibi_attn_bwd(dout, q, k, v, o, lse, cu_seqlens, max_seqlen: int, slopes
     dq = torch.empty((R, H, D), dtype=q.dtype, device=q.device) if dq is None else dq
     dk = torch.empty((R, H, D), dtype=q.dtype, device=q.device) if dk is None else dk
     dv = torch.empty((R, H, D), dtype=q.dtype, device=q.device) if dv is None else dv
-    need = mb_alibi_attn_bwd_workspace_bytes(B, T, max_seqlen, H, D, _dtype_code(q))
+    dt = _dtype_code(q)
     if workspace is None:
+        need = _lib.mb_alibi_attn_bwd_workspace_bytes(B, T, max_seqlen, H, D, dt)
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
     _check(_lib.mb_alibi_attn_bwd(_ptr(dout), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _row_stride(dout),
                                   _row_stride(q), _row_stride(k), _row_stride(v), _row_stride(o), _ptr(cu_seqlens),
-                                  B, T, max_seqlen, H, D, _ptr(slopes), float(softmax_scale), _dtype_code(q),
+                                  B, T, max_seqlen, H, D, _ptr(slopes), float(softmax_scale), dt,
                                   _ptr(dq), _ptr(dk), _ptr(dv), _row_stride(dq), _row_stride(dk), _row_stride(dv),
                                   _ptr(workspace), workspace.numel(), _ptr(key_lens), _ptr(token_rows), _ptr(plan),
                                   _stream()))
