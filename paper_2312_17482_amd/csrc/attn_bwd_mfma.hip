@@ -57,7 +57,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
     const int32_t* __restrict__ token_rows, const int32_t* __restrict__ plan, int64_t plan_cap) {
   const int32_t* rows = kMode == kRowsIdentity ? nullptr : token_rows;
   __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kBuf];   // per buffer: Q tile, dO tile
-  __shared__ __attribute__((aligned(16))) float sL[2][kTileS];       // -lse in base-2 units (-inf past the end)
+  __shared__ __attribute__((aligned(16))) float sL[2][3][kTileS];    // -lse / scale (-inf past the end): alone, with the
+                                                                     // row's bias left and right of the diagonal
   __shared__ __attribute__((aligned(16))) float sD[2][kTileS];       // -Delta
 
   int start, n, nk, ktile, h;   // nk <= n: the sequence's first nk tokens are its keys
@@ -88,7 +89,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
   const int ntiles = (n + kTileS - 1) / kTileS;
   const int st_row = tid >> 3, st_col = (tid & 7) * 8;
   const float cs = scale * kLog2e;
-  const float k1 = slopes[h] / scale;
+  const float k1 = slopes[h] / scale, inv_scale = 1.f / scale;
 
   // ---- K, V rows of this workgroup's 128 keys (coalesced) -> LDS -> K^T, V^T fragments
   bf16x8 bk[4], bv[4];
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
     }
     if (tid < kTileS) {
       const bool ok = i0 + tid < n;
-      tl = ok ? -lse[(int64_t)h * T + start + i0 + tid] * kLog2e : -INFINITY;
+      tl = ok ? -lse[(int64_t)h * T + start + i0 + tid] * inv_scale : -INFINITY;
       td = ok ? -delta[(int64_t)h * T + start + i0 + tid] : 0.f;
     }
   };
@@ -162,7 +163,12 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
       *reinterpret_cast<u32x4*>(&bq_[(32 * it + st_row) * kPitch + st_col]) = tq[it];
       *reinterpret_cast<u32x4*>(&bq_[kHalf + (32 * it + st_row) * kPitch + st_col]) = tg[it];
     }
-    if (tid < kTileS) { sL[buf][tid] = tl; sD[buf][tid] = td; }
+    if (tid < kTileS) {
+      sL[buf][0][tid] = tl;
+      sL[buf][1][tid] = fmaf((float)tid, k1, tl);
+      sL[buf][2][tid] = fmaf((float)tid, -k1, tl);
+      sD[buf][tid] = td;
+    }
   };
 
   f32x16 dkacc[2], dvacc[2];   // dK^T, dV^T: d along accumulator rows (two blocks of 32), keys along lanes
@@ -175,26 +181,31 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
   asm volatile("" : "+v"(fj));
 
   // The two blocks of 32 queries of a staged tile (rows 32ib..) against this wave's keys.  The S accumulator
-  // is pre-loaded with bias/scale and the dP accumulator with -Delta_i, so that after the products
-  // P = exp2(acc_S * c - lse2_i) and dS = P * acc_dP.  Rows past the sequence end are staged as zeros
+  // starts from -lse_i / scale plus the bias and the dP accumulator from -Delta_i, so that after the products
+  // P = exp2(acc_S * c) and dS = P * acc_dP.  Off the diagonal block |i-j| is linear in i and j: the query's part of the
+  // bias comes out of LDS together with lse_i (one of two tables, for either side), the key's part is the exponent's
+  // constant; no instruction per score is spent on either.  Rows past the sequence end are staged as zeros
   // with lse = +inf, which makes their P and dS exact zeros: no branch around the accumulating code.
-  // Only the bias pre-load has variants (diagonal block or not); everything after it is one straight
+  // Only the start values have variants (diagonal block or not); everything after it is one straight
   // run of instructions for both blocks, so that the exponentials of one block can be issued between
   // the matrix instructions of the other.
-  auto qtile = [&](const uint16_t* sQ, const uint16_t* sG, const float* pl, const float* pd, int i0) {
+  auto qtile = [&](const uint16_t* sQ, const uint16_t* sG, const float (*pl)[kTileS], const float* pd, int i0) {
     f32x16 sacc[2], pacc[2];
+    float off[2];
 #pragma unroll
     for (int ib = 0; ib < 2; ++ib) {
-      const float d0 = (float)(i0 + 32 * ib) - fj;
       const int qb = (i0 >> 5) + ib;
+      const float* table = pl[qb == kblk ? 0 : qb < kblk ? 1 : 2];
+      off[ib] = qb == kblk ? 0.f : (qb < kblk ? k1 : -k1) * (float)(i0 - kj) * cs;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float4 l4 = *reinterpret_cast<const float4*>(&table[32 * ib + 8 * r + 4 * g]);
+        sacc[ib][4 * r + 0] = l4.x; sacc[ib][4 * r + 1] = l4.y; sacc[ib][4 * r + 2] = l4.z; sacc[ib][4 * r + 3] = l4.w;
+      }
       if (qb == kblk) {   // block with the diagonal
+        const float d0 = (float)(i0 + 32 * ib) - fj;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sacc[ib][i] = -k1 * fabsf(d0 + (float)(8 * (i >> 2) + (i & 3)));
-      } else {            // |i-j| = +-(ci - fj) on the whole block
-        const float sk = qb < kblk ? k1 : -k1;
-        const float a = sk * d0;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sacc[ib][i] = fmaf((float)(8 * (i >> 2) + (i & 3)), sk, a);
+        for (int i = 0; i < 16; ++i) sacc[ib][i] = fmaf(-k1, fabsf(d0 + (float)(8 * (i >> 2) + (i & 3))), sacc[ib][i]);
       }
     }
 #pragma unroll
@@ -215,15 +226,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
 #pragma unroll
     for (int ib = 0; ib < 2; ++ib) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float4 l4 = *reinterpret_cast<const float4*>(&pl[32 * ib + 8 * r + 4 * g]);
-        const float nl[4] = {l4.x, l4.y, l4.z, l4.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float p = fast_exp2(fmaf(sacc[ib][4 * r + e], cs, nl[e]));
-          sacc[ib][4 * r + e] = p;
-          pacc[ib][4 * r + e] = p * pacc[ib][4 * r + e];
-        }
+      for (int i = 0; i < 16; ++i) {
+        const float p = fast_exp2(fmaf(sacc[ib][i], cs, off[ib]));
+        sacc[ib][i] = p;
+        pacc[ib][i] = p * pacc[ib][i];
       }
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
@@ -253,7 +259,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
     if (wave_active) {
       const uint16_t* sQ = smem + (it & 1) * kBuf;
       const uint16_t* sG = sQ + kHalf;
-      const float* pl = sL[it & 1];
+      const float (*pl)[kTileS] = sL[it & 1];
       const float* pd = sD[it & 1];
       qtile(sQ, sG, pl, pd, i0);
     }
@@ -428,8 +434,14 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
   const int tr_row = (tr_i >> 2) + 4 * (tr_q >> 1);
   const int tr_col = 16 * (tr_q & 1) + 4 * (tr_i & 3);
 
+  f32x16 row_bias;      // (m_h / scale) * (accumulator row) left of the diagonal, its negative right of it
+#pragma unroll
+  for (int i = 0; i < 16; ++i) row_bias[i] = k1 * (float)(8 * (i >> 2) + (i & 3));
+  // in vector registers, where there is room: the compiler would keep it in scalar ones and copy it each time
+  if (kMode == kRowsIdentity) asm volatile("" : "+v"(row_bias));
+
   // One block of 32 keys (rows 32jb.. of the staged tile) against this wave's queries, transposed
-  // orientation: S^T = K Q^T (+ bias/scale pre-loaded), dP^T = V dO^T (- Delta pre-loaded).  The code
+  // orientation: S^T = K Q^T (bias/scale in the C operand), dP^T = V dO^T (- Delta pre-loaded).  The code
   // that accumulates dQ exists once with no branch around it; a ragged last tile only zeroes the dS of
   // the keys that do not exist.
   auto kblock = [&](const uint16_t* sK, const uint16_t* sV, int j0, int jb, int rem) {
@@ -437,26 +449,31 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
     asm volatile("" : "+v"(fi));
     f32x16 sacc, pacc;
     const int kb = (j0 >> 5) + jb;
+    const uint16_t* krow = &sK[(32 * jb + c) * kPitch + 8 * g];
+    const uint16_t* vrow = &sV[(32 * jb + c) * kPitch + 8 * g];
+    const bf16x8 ak0 = lds_read8(krow);
+    float e0 = nlse2;   // the exponent's constant
     if (kb == qblk) {
+      f32x16 diag;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sacc[i] = -k1 * fabsf(fi - (float)(jb * 32 + 8 * (i >> 2) + (i & 3)));
-    } else {
-      const float sk = kb < qblk ? k1 : -k1;
-      const float a = -sk * fi;
+      for (int i = 0; i < 16; ++i) diag[i] = -k1 * fabsf(fi - (float)(jb * 32 + 8 * (i >> 2) + (i & 3)));
+      sacc = mfma32(ak0, bq[0], diag);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sacc[i] = fmaf((float)(jb * 32 + 8 * (i >> 2) + (i & 3)), sk, a);
+      for (int i = 0; i < 16; ++i) row_bias[i] = -row_bias[i];
+    } else {   // (see the forward: the bias per accumulator row is the C operand, the bias per lane goes to the exponent)
+      sacc = mfma32(ak0, bq[0], row_bias);
+      e0 = fmaf((kb < qblk ? -k1 : k1) * (fi - (float)(32 * jb)), cs, e0);
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) pacc[i] = ndlt;
-    const uint16_t* krow = &sK[(32 * jb + c) * kPitch + 8 * g];
-    const uint16_t* vrow = &sV[(32 * jb + c) * kPitch + 8 * g];
+    pacc = mfma32(lds_read8(vrow), bg[0], pacc);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int s = 1; s < 4; ++s) {
       sacc = mfma32(lds_read8(krow + 16 * s), bq[s], sacc);
       pacc = mfma32(lds_read8(vrow + 16 * s), bg[s], pacc);
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) pacc[i] = fast_exp2(fmaf(sacc[i], cs, nlse2)) * pacc[i];
+    for (int i = 0; i < 16; ++i) pacc[i] = fast_exp2(fmaf(sacc[i], cs, e0)) * pacc[i];
     if (rem < kTileS) {
       // a key past the sequence end has a zero K row, but its p may overflow (its score was never part
       // of lse): force the product with that zero row to be 0, not inf * 0

@@ -164,28 +164,47 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_tiled_kernel(
   float m_run = -INFINITY;   // running maximum of the raw accumulator (dot product + bias/scale)
   float l_run = 0.f;         // running row sum, this half-wave's share
 
+  f32x16 row_bias;           // (m_h / scale) * (accumulator row) left of the diagonal, its negative right of it
+#pragma unroll
+  for (int i = 0; i < 16; ++i) row_bias[i] = k1 * (float)(8 * (i >> 2) + (i & 3));
+  asm volatile("" : "+v"(row_bias));   // in vector registers: the compiler would keep it in scalar ones and copy it each time
+
   // One tile of 64 keys.  The code that touches the running output exists once, with no branch
-  // around it: a ragged last tile is handled by pre-loading -inf for the keys that do not exist (their
-  // K rows are staged as zeros), so that only the accumulator pre-load has variants.
+  // around it: a ragged last tile is handled by setting the scores of the keys that do not exist to -inf (their
+  // K rows are staged as zeros), and only the first product has variants.
   auto tile = [&](int j0, int jt) {
     const uint16_t* bufK = smem + (jt & 1) * kBufElems;
     const uint16_t* bufV = bufK + kTileK * kKStride;
     const int rem = nk - j0;
     float fi = (float)(qi - j0 - 4 * g);   // i - j = fi - cj with cj = 32jb + 8*(v/4) + v%4
     asm volatile("" : "+v"(fi));
+    // Off the diagonal block |i-j| = +-(fi - cj) is linear: its part per accumulator row is the same in every block (up
+    // to the sign) and enters as the first product's C operand, straight from the registers that hold it; its part per
+    // lane, off[jb], is added to the block's maximum and to the exponent's constant.  No instruction per score.
     f32x16 sacc[2];
+    float off[2];
+    const uint16_t* krow = &bufK[c * kKStride + 8 * g];
 #pragma unroll
     for (int jb = 0; jb < 2; ++jb) {
       const int kblk = 2 * jt + jb;
-      if (kblk == qblk) {   // the block that holds the diagonal
+      const bf16x8 ak = lds_read8(krow + 32 * jb * kKStride);
+      if (kblk == qblk) {   // the block that holds the diagonal; the ones behind it lie on its other side
+        f32x16 diag;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sacc[jb][i] = -k1 * fabsf(fi - (float)(jb * 32 + 8 * (i >> 2) + (i & 3)));
-      } else {              // |i-j| = +-(fi - cj) on the whole block
-        const float sk = kblk < qblk ? k1 : -k1;
-        const float a = -sk * fi;
+        for (int i = 0; i < 16; ++i) diag[i] = -k1 * fabsf(fi - (float)(jb * 32 + 8 * (i >> 2) + (i & 3)));
+        sacc[jb] = mfma32(ak, bq[0], diag);
+        off[jb] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sacc[jb][i] = fmaf((float)(jb * 32 + 8 * (i >> 2) + (i & 3)), sk, a);
+        for (int i = 0; i < 16; ++i) row_bias[i] = -row_bias[i];
+      } else {
+        sacc[jb] = mfma32(ak, bq[0], row_bias);
+        off[jb] = (kblk < qblk ? -k1 : k1) * (fi - (float)(32 * jb));
       }
+    }
+#pragma unroll
+    for (int s = 1; s < 4; ++s) {
+      sacc[0] = mfma32(lds_read8(krow + 16 * s), bq[s], sacc[0]);
+      sacc[1] = mfma32(lds_read8(krow + 32 * kKStride + 16 * s), bq[s], sacc[1]);
     }
     if (rem < kTileK) {   // ragged end: keys that do not exist (or are masked out) get -inf
       const int lim = rem - 4 * g;
@@ -195,17 +214,14 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_tiled_kernel(
         for (int i = 0; i < 16; ++i)
           sacc[jb][i] = (jb * 32 + 8 * (i >> 2) + (i & 3)) >= lim ? -INFINITY : sacc[jb][i];
     }
-    const uint16_t* krow = &bufK[c * kKStride + 8 * g];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      sacc[0] = mfma32(lds_read8(krow + 16 * s), bq[s], sacc[0]);
-      sacc[1] = mfma32(lds_read8(krow + 32 * kKStride + 16 * s), bq[s], sacc[1]);
-    }
     float mt = -INFINITY;
 #pragma unroll
-    for (int jb = 0; jb < 2; ++jb)
+    for (int jb = 0; jb < 2; ++jb) {
+      float mb = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) mt = fmaxf(mt, sacc[jb][i]);
+      for (int i = 0; i < 16; ++i) mb = fmaxf(mb, sacc[jb][i]);
+      mt = fmaxf(mt, mb + off[jb]);
+    }
     mt = max_both_halves(mt);
     const float m_new = fmaxf(m_run, mt);
     if (jt > 0 && __any(m_new > m_run)) {   // some query's maximum moved: rescale the running sums
@@ -215,13 +231,13 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_tiled_kernel(
       for (int i = 0; i < 16; ++i) { oacc[0][i] *= alpha; oacc[1][i] *= alpha; }
     }
     m_run = m_new;
-    const float mc = m_new * cs;
     float lsum[4] = {0.f, 0.f, 0.f, 0.f};   // four short chains of additions instead of one long one
 #pragma unroll
     for (int jb = 0; jb < 2; ++jb) {
+      const float e0 = (off[jb] - m_new) * cs;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const float p = fast_exp2(fmaf(sacc[jb][i], cs, -mc));
+        const float p = fast_exp2(fmaf(sacc[jb][i], cs, e0));
         sacc[jb][i] = p;
         lsum[i & 3] += p;
       }
