@@ -32,7 +32,6 @@ namespace mb {
 namespace {
 
 constexpr int kBK = 64;                               // k per stage
-constexpr int kStages = 2;
 constexpr int kGroupM = 4;                            // token panels walked together (L2 reuse of the weight tiles)
 
 // GeLU(h) = h * Phi(h), the exact (error-function) form, with Phi evaluated by the classic five-term
@@ -100,24 +99,27 @@ __device__ __forceinline__ void stage_ready() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(kNewer) : "memory");
 }
 
-// One workgroup of 8 waves (2 along the tokens by 4 along the weight rows) per compute unit walks the tiles blockIdx.x,
-// + gridDim.x, ...  A tile is 64 kMB tokens x 256 weight rows; a wave computes 32 kMB x 64 of it.
+// One workgroup of 2 kWN waves (2 along the tokens by kWN along the weight rows) per compute unit walks the tiles
+// blockIdx.x, + gridDim.x, ...  A tile is 64 kMB tokens x 32 kWN kNB weight rows; a wave computes 32 kMB x 32 kNB of it.
+// Wide (4 x 2 blocks, two stages): 64 to 320 tokens x 256.  Narrow (2 x 1 blocks, eight stages): 64 x 64 for products of
+// few rows and columns, whose time is the latency of a step: a sixteenth of the bytes per step, seven steps in flight.
 // X rows and W rows are both K elements long.  kPartial: the contraction is split, tile id = split * tiles + tile, and
 // the split's fp32 sums go to out (as float) + split * T_cap * ldo.
-template <int kMode, int kMB>
-__global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __restrict__ X,
+template <int kMode, int kMB, int kWN, int kNB, int kStages>
+__global__ __launch_bounds__(128 * kWN, kWN / 2) void ffn_gemm_kernel(const uint16_t* __restrict__ X,
                                                           const uint16_t* __restrict__ W, int K, int n_tiles,
                                                           int splits, int gate_row, int w_rows, int T_cap,
                                                           const int32_t* __restrict__ meta,
                                                           uint16_t* __restrict__ out, int ldo,
                                                           const uint16_t* __restrict__ aux, int gate_col) {
   constexpr bool kGated = kMode == kGatedFwd;
-  constexpr int kBM = 64 * kMB, kBN = 256, kNB = 2;
+  constexpr int kBM = 64 * kMB, kBN = 32 * kWN * kNB, kWaves = 2 * kWN;
+  static_assert(!kGated || kNB == 2, "the gated epilogue pairs the wave's two weight blocks");
   constexpr int kRows = kBM + kBN;                  // rows of a stage: tokens, then weight rows
   constexpr int kStageElems = kRows * kBK;
-  constexpr int kLoads = kRows / 64;                // 8-row loads per wave and k step
+  constexpr int kLoads = kRows / (8 * kWaves);      // 8-row loads per wave and k step
   constexpr int kSlabElems = 32 * 32;               // per wave: 32 tokens x 32 columns on their way out
-  __shared__ __attribute__((aligned(1024))) uint16_t smem[kStages * kStageElems + 8 * kSlabElems];
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kStages * kStageElems + kWaves * kSlabElems];
 
   // (readfirstlane: tells the compiler the value is wave-uniform, so descriptors built from it stay scalar)
   const int T = __builtin_amdgcn_readfirstlane(meta ? min(meta[0], T_cap) : T_cap);
@@ -154,14 +156,14 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 31, g = lane >> 5;
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = wave / kWN, wn = wave % kWN;
 
   // Global -> LDS: a row of a stage is 128 bytes = 8 pieces, a load carries 8 rows (whole cache lines: rows of 64 bytes,
   // with twice the stages, measured a fifth slower).  Piece x of row r sits at position x ^ (r / 2) % 8, so that a
   // fragment read (one piece of 16 consecutive rows per quarter wave) touches every bank once.  Row bounds are the
   // descriptors': token rows at or beyond T and weight rows past the matrix deposit zeros.
   // (The k offset is the scalar operand, which takes no part in the range check.)
-  // Load i of wave w carries rows 8 (w + 8 i) .. of the stage.
+  // Load i of wave w carries rows 8 (w + kWaves i) .. of the stage.
   const uint32_t lane_off =
       ((uint32_t)(lane >> 3) * (uint32_t)K + (((lane & 7) ^ (4 * (wave & 1) + (lane >> 4))) * 8)) * 2u;
   const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(
@@ -174,7 +176,7 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
     k_bytes = (uint32_t)k0 * (kBK * 2);
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
-      const int row = 8 * (wave + 8 * i), r = row - kBM;   // r: row of the weight tile
+      const int row = 8 * (wave + kWaves * i), r = row - kBM;   // r: row of the weight tile
       const bool token = row < kBM;
       const int first = token ? m0 + row : kGated ? (r < kBN / 2 ? n0 + r : gate_row + n0 + r - kBN / 2) : n0 + r;
       const int rows = max(min((token ? T : w_rows) - first, 8), 0);
@@ -182,7 +184,7 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
     }
   };
   auto fetch_one = [&](int i, int stage, int kt) {
-    load_to_lds(lds0 + (stage * kStageElems + 8 * (wave + 8 * i) * kBK) * 2, lane_off, rsrc[i], k_bytes + kt * (kBK * 2));
+    load_to_lds(lds0 + (stage * kStageElems + 8 * (wave + kWaves * i) * kBK) * 2, lane_off, rsrc[i], k_bytes + kt * (kBK * 2));
   };
 
   // Fragments of this wave inside a stage: tokens at rows 0 .., weight rows from kBM on.  Gated: the first weight block
@@ -192,7 +194,8 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) frag[kk] = c * kBK + (((2 * kk + g) ^ ((c >> 1) & 7)) * 8);
   const uint32_t xrow = wm * (32 * kMB) * kBK;
-  const uint32_t wrow = (kBM + wn * (kGated ? 32 : 64)) * kBK;
+  constexpr int kWaveCols = kGated ? 32 : 32 * kNB;   // output columns per wave
+  const uint32_t wrow = (kBM + wn * kWaveCols) * kBK;
   constexpr uint32_t kWBlock = (kGated ? kBN / 2 : 32) * kBK;   // from the first weight block of the wave to the second
   bf16x8 xf[2][kMB], wf[2][kNB];
   auto read_frag = [&](int stage, int kk, int i) {   // weight fragments first
@@ -203,8 +206,8 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
   constexpr int kFrags = kMB + kNB, kMfma = kMB * kNB;
   f32x16 acc[kNB][kMB];
 
-  // The k steps of all the workgroup's tiles form one sequence; the loads run two steps ahead of the products, across the
-  // end of a tile, so that the next tile's first steps arrive during this one's last products and its epilogue.
+  // The k steps of all the workgroup's tiles form one sequence; the loads run kStages steps ahead of the products, across
+  // the end of a tile, so that the next tile's first steps arrive during this one's last products and its epilogue.
   // (Past the last tile the loads repeat it: their number stays the same and nobody reads them.)
   int f_tile = blockIdx.x, f_kt = 0;
   aim(f_tile);
@@ -222,12 +225,14 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
     for (int i = 0; i < kLoads; ++i) fetch_one(i, st, f_kt);
     advance();
   }
-  stage_ready<kLoads>();
+  stage_ready<(kStages - 1) * kLoads>();
 #pragma unroll
   for (int i = 0; i < kFrags; ++i) read_frag(0, 0, i);
 
   // store instructions of an epilogue, per wave (they are issued also where every lane is out of range)
-  constexpr int kStores = kMode == kPartial ? 0 : kMode == kGatedFwd ? 2 * kMB : kMode == kGateBwd ? 8 * kMB : 4 * kMB;
+  constexpr int kStores = kMode == kPartial ? 0 : kGated ? 2 * kMB : (kMode == kGateBwd ? 4 : 2) * kMB * kNB;
+  constexpr int kNewer = (kStages - 2) * kLoads;   // loads of the steps after the next one
+  static_assert(kNewer + kStores < 64, "fits the counter");
   bool first = true;
   int stage = 0;
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
@@ -246,16 +251,17 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
     // the stores of the tile before it: the first barrier of a tile lets those stores (at least kStores) travel on.
 #pragma unroll 1
     for (int kt = 0; kt < nk; ++kt) {
+      const int next = stage + 1 == kStages ? 0 : stage + 1;
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         if (kk == 3) {
-          if (kt == 0 && !first) stage_ready<kStores>();
-          else stage_ready<0>();
+          if (kt == 0 && !first) stage_ready<kNewer + kStores>();
+          else stage_ready<kNewer>();
         }
 #pragma unroll
         for (int x = 0; x < kMfma; ++x) {
 #pragma unroll
-          for (int i = x; i < kFrags; i += kMfma) read_frag(kk == 3 ? stage ^ 1 : stage, (kk + 1) & 3, i);
+          for (int i = x; i < kFrags; i += kMfma) read_frag(kk == 3 ? next : stage, (kk + 1) & 3, i);
           if (kk == 3) {
 #pragma unroll
             for (int i = x; i < kLoads; i += kMfma) fetch_one(i, stage, f_kt);
@@ -266,7 +272,7 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
         }
       }
       advance();
-      stage ^= 1;
+      stage = next;
     }
     first = false;
 
@@ -279,7 +285,7 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
         const int row = m0 + wm * (32 * kMB) + mb * 32 + c;
 #pragma unroll
         for (int nb = 0; nb < kNB; ++nb) {
-          const int col = n0 + wn * 64 + nb * 32 + 4 * g;
+          const int col = n0 + wn * kWaveCols + nb * 32 + 4 * g;
           if (row < T && col < w_rows) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -304,7 +310,7 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int row = m0 + wm * (32 * kMB) + (p / kNB) * 32 + 16 * u + orow;
-        const int64_t at = (int64_t)min(row, T - 1) * ldo + n0 + wn * 64 + (p % kNB) * 32 + opiece * 8;
+        const int64_t at = (int64_t)min(row, T - 1) * ldo + n0 + wn * kWaveCols + (p % kNB) * 32 + opiece * 8;
         hv[p][u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aux + at));
         gv[p][u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aux + at + gate_col));
       }
@@ -313,7 +319,7 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_kernel(const uint16_t* __rest
     for (int mb = 0; mb < kMB; ++mb) {
 #pragma unroll
       for (int nb = 0; nb < (kGated ? 1 : kNB); ++nb) {
-        const int col = n0 + wn * (kGated ? 32 : 64) + nb * 32 + opiece * 8;
+        const int col = n0 + wn * kWaveCols + nb * 32 + opiece * 8;
         const int row0 = m0 + wm * (32 * kMB) + mb * 32 + orow;
         const bool cols_ok = kGated || col < w_rows;
         const uint32_t off0 = ((uint32_t)(row0 - m0) * (uint32_t)ldo + (uint32_t)col) * 2u;
@@ -581,15 +587,17 @@ __global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* __restri
 
 constexpr int kComputeUnits = 256;
 
-template <int kMode, int kMB>
+template <int kMode, int kMB, int kWN, int kNB, int kStages>
 static void launch_gemm_tile(const void* x, const void* wt, int K, int n_cols, int splits, int gate_row, int w_rows,
                              int T_cap, const int32_t* meta, void* out, int ldo, const uint16_t* aux, int gate_col,
                              hipStream_t stream) {
-  const int m_tiles = (T_cap + 64 * kMB - 1) / (64 * kMB), n_tiles = (n_cols + 255) / 256;
+  constexpr int kBN = 32 * kWN * kNB;
+  const int m_tiles = (T_cap + 64 * kMB - 1) / (64 * kMB), n_tiles = (n_cols + kBN - 1) / kBN;
   const int64_t total = (int64_t)m_tiles * n_tiles * splits;
-  ffn_gemm_kernel<kMode, kMB><<<dim3((unsigned)(total < kComputeUnits ? total : kComputeUnits)), dim3(512), 0, stream>>>(
-      static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_tiles, splits, gate_row, w_rows, T_cap,
-      meta, static_cast<uint16_t*>(out), ldo, aux, gate_col);
+  ffn_gemm_kernel<kMode, kMB, kWN, kNB, kStages>
+      <<<dim3((unsigned)(total < kComputeUnits ? total : kComputeUnits)), dim3(128 * kWN), 0, stream>>>(
+          static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_tiles, splits, gate_row, w_rows, T_cap,
+          meta, static_cast<uint16_t*>(out), ldo, aux, gate_col);
 }
 
 // Estimated microseconds of a product with tiles of 64 mb tokens and `splits` shares of the contraction.  A k step of a
@@ -615,7 +623,7 @@ template <int kMode>
 static void launch_gemm(const void* x, const void* wt, int K, int n_cols, int splits, int gate_row, int w_rows, int T_cap,
                         const int32_t* meta, void* out, int ldo, const uint16_t* aux, int gate_col, hipStream_t stream) {
 #define MB_TILE(n) \
-  launch_gemm_tile<kMode, n>(x, wt, K, n_cols, splits, gate_row, w_rows, T_cap, meta, out, ldo, aux, gate_col, stream)
+  launch_gemm_tile<kMode, n, 4, 2, 2>(x, wt, K, n_cols, splits, gate_row, w_rows, T_cap, meta, out, ldo, aux, gate_col, stream)
   switch (tile_height(T_cap, n_cols, K, splits)) {
     case 1: MB_TILE(1); break;
     case 2: MB_TILE(2); break;
@@ -626,9 +634,17 @@ static void launch_gemm(const void* x, const void* wt, int K, int n_cols, int sp
 #undef MB_TILE
 }
 
-// out[t, n] = sum_k x[t, k] * wt[n, k] with the plain epilogue.
+// out[t, n] = sum_k x[t, k] * wt[n, k] with the plain epilogue; in narrow tiles where their estimate (0.23 us a step, 1.5 us
+// a tile) is less: 945 x 768, K = 3072: 37 us in tiles of 64 x 256, 14 us in 64 x 64; 300 x 768, K = 768: 8.0 and 6.0 us;
+// 2000 x 768, K = 768 (two rounds of narrow tiles): 8.7 and 9.9 us.
 static void launch_plain(const void* x, const void* wt, int T_cap, const int32_t* meta, int n_in, int n_out, void* y,
                          hipStream_t stream) {
+  const int64_t narrow = (int64_t)((T_cap + 63) / 64) * (n_out / 64);
+  const double cost = (double)((narrow + kComputeUnits - 1) / kComputeUnits) * (0.23 * (n_in / kBK) + 1.5);
+  if (cost < gemm_cost(T_cap, n_out, n_in, tile_height(T_cap, n_out, n_in, 1), 1)) {
+    launch_gemm_tile<kPlain, 1, 2, 1, 8>(x, wt, n_in, n_out, 1, 0, n_out, T_cap, meta, y, n_out, nullptr, 0, stream);
+    return;
+  }
   launch_gemm<kPlain>(x, wt, n_in, n_out, 1, 0, n_out, T_cap, meta, y, n_out, nullptr, 0, stream);
 }
 

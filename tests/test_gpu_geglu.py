@@ -115,13 +115,13 @@ def test_linear_forward_parity(mb, T, n_in, n_out):
 
 @pytest.mark.parametrize("T,T_cap,n_in,n_out", [(40, 40, 128, 192), (200, 200, 256, 6144), (950, 1000, 128, 4608),
                                                 (8089, 8089, 128, 3072), (12345, 13000, 192 * 2, 1344), (26963, 26963, 128, 768),
-                                                (33000, 33000, 128, 512), (5000, 5000, 128, 30528), (3991, 3991, 128, 2304),
+                                                (33000, 33000, 128, 512), (5000, 5000, 128, 30528), (3991, 3991, 128, 2304), (2000, 2050, 3072, 768),
                                                 (6900, 6982, 128, 2304)])
 def test_linear_every_tile_height_and_several_tiles_per_workgroup(mb, T, T_cap, n_in, n_out):
     """Sizes that take each tile height of the projection kernel (64 to 320 tokens), fewer and more tiles than compute
     units, a last token panel and a last weight tile that are partly empty, a device-side row count.  Reference:
     float32 product of the same values; the result is that product rounded to bf16 (2^-9 of a value), the sums'
-    order moves it by far less than the 1e-4 allowed on top (128 to 384 terms of about 0.02)."""
+    order moves it by far less than the 1e-4 allowed on top (128 to 3072 terms of about 0.02: 2^-24 of at most 60 a term)."""
     print("linear tiles T=%d n_in=%d n_out=%d" % (T, n_in, n_out), flush=True)
     gen = torch.Generator(device="cuda").manual_seed(T)
     x = torch.randn((T_cap, n_in), generator=gen, device="cuda").bfloat16()
