@@ -50,6 +50,10 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(const int32_t* 
   __shared__ __attribute__((aligned(16))) PlanLds lds;
   build_plan_list(cu, key_lens, B, H, max_seqlen, cap, plan, blockIdx.x, misuse, lds);
   if (blockIdx.x != 0 || lse == nullptr) return;
+  // is there one at all?  (a thread per sequence: looked at one after the other, 64 sequences took as long as the plan)
+  bool skipped = false;
+  for (int b = threadIdx.x; b < B; b += kPlanThreads) skipped = skipped || cu[b + 1] - cu[b] > max_seqlen;
+  if (!__syncthreads_or(skipped)) return;
   for (int b = 0; b < B; ++b) {
     const int s0 = cu[b], len = cu[b + 1] - s0;
     if (len > max_seqlen)
