@@ -22,27 +22,17 @@ __device__ __forceinline__ float wsum(float x) {
   return x;
 }
 
-// Cache policy: rows that are read here for the last time (x and r in the forward, dy and s in the backward) are loaded
-// non-temporally (load_once), so that these one-pass streams leave the memory-side cache to what is read again: s and y.
-// Forward + backward of 26963 x 768 on new inputs each time: 74.1 -> 71.5 us.
-typedef unsigned int nt_u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int nt_u32x2 __attribute__((ext_vector_type(2)));
-
 template <typename E> struct Piece;      // one 16-byte piece of a row <-> floats
 template <> struct Piece<uint16_t> {
   static constexpr int kN = 8;
-  static __device__ __forceinline__ void floats(nt_u32x4 w, float* f) {
+  static __device__ __forceinline__ void load(const uint16_t* p, float* f) {
+    const uint4 u = *reinterpret_cast<const uint4*>(p);
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       f[2 * i] = __uint_as_float(w[i] << 16);
       f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
-  }
-  static __device__ __forceinline__ void load(const uint16_t* p, float* f) {
-    floats(*reinterpret_cast<const nt_u32x4*>(p), f);
-  }
-  static __device__ __forceinline__ void load_once(const uint16_t* p, float* f) {
-    floats(__builtin_nontemporal_load(reinterpret_cast<const nt_u32x4*>(p)), f);
   }
   static __device__ __forceinline__ uint32_t rne(float x) {   // float -> bf16 bits, nearest even; NaN stays NaN
     const uint32_t u = __float_as_uint(x);
@@ -65,15 +55,10 @@ template <> struct Piece<uint16_t> {
 // more load instructions per row than the extra wave per SIMD buys) and keeps 16-byte pieces.
 struct HalfPiece {
   static constexpr int kN = 4;
-  static __device__ __forceinline__ void floats(nt_u32x2 u, float* f) {
-    f[0] = __uint_as_float(u[0] << 16); f[1] = __uint_as_float(u[0] & 0xffff0000u);
-    f[2] = __uint_as_float(u[1] << 16); f[3] = __uint_as_float(u[1] & 0xffff0000u);
-  }
   static __device__ __forceinline__ void load(const uint16_t* p, float* f) {
-    floats(*reinterpret_cast<const nt_u32x2*>(p), f);
-  }
-  static __device__ __forceinline__ void load_once(const uint16_t* p, float* f) {
-    floats(__builtin_nontemporal_load(reinterpret_cast<const nt_u32x2*>(p)), f);
+    const uint2 u = *reinterpret_cast<const uint2*>(p);
+    f[0] = __uint_as_float(u.x << 16); f[1] = __uint_as_float(u.x & 0xffff0000u);
+    f[2] = __uint_as_float(u.y << 16); f[3] = __uint_as_float(u.y & 0xffff0000u);
   }
   static __device__ __forceinline__ void store(uint16_t* p, const float* f) {
     uint2 u;
@@ -88,11 +73,6 @@ template <> struct Piece<float> {
   static __device__ __forceinline__ void load(const float* p, float* f) {
     const float4 u = *reinterpret_cast<const float4*>(p);
     f[0] = u.x; f[1] = u.y; f[2] = u.z; f[3] = u.w;
-  }
-  static __device__ __forceinline__ void load_once(const float* p, float* f) {
-    const nt_u32x4 u = __builtin_nontemporal_load(reinterpret_cast<const nt_u32x4*>(p));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) f[i] = __uint_as_float(u[i]);
   }
   static __device__ __forceinline__ void store(float* p, const float* f) {
     *reinterpret_cast<float4*>(p) = make_float4(f[0], f[1], f[2], f[3]);
@@ -119,10 +99,10 @@ __global__ __launch_bounds__(kLnThreads) void add_layernorm_fwd_kernel(
   for (int c = 0; c < kMaxPieces; ++c) {
     const int pc = lane + 64 * c;
     if (pc < pieces) {
-      PT::load_once(xr + pc * N, v[c]);
+      PT::load(xr + pc * N, v[c]);
       if (r) {
         float t[N];
-        PT::load_once(r + (size_t)row * W + pc * N, t);
+        PT::load(r + (size_t)row * W + pc * N, t);
 #pragma unroll
         for (int i = 0; i < N; ++i) v[c][i] = PT::round(v[c][i] + t[i]);   // the stored sum is what is normalised
         PT::store(s + (size_t)row * W + pc * N, v[c]);
@@ -185,8 +165,8 @@ __global__ __launch_bounds__(kLnThreads) void add_layernorm_bwd_kernel(
       const int pc = lane + 64 * c;
       if (pc < pieces) {
         float d[N];
-        PT::load_once(s + (size_t)row * W + pc * N, xh[c]);
-        PT::load_once(dyr + pc * N, d);
+        PT::load(s + (size_t)row * W + pc * N, xh[c]);
+        PT::load(dyr + pc * N, d);
 #pragma unroll
         for (int i = 0; i < N; ++i) {
           xh[c][i] = (xh[c][i] - mu) * rs;
