@@ -76,7 +76,7 @@ constexpr int kGateBwd = 2;    // the product is dA; with h | g read from `aux`:
 // One wave moves 64 x 16 bytes from global memory straight into LDS: lane l's piece lands at byte `lds` + 16 l.  Lanes
 // whose offset lies outside the descriptor deposit zeros.  (Inline assembly on purpose: it writes no register, and the
 // compiler, which cannot tell one part of LDS from another, would wait for every such load before any LDS read if it
-// knew of it.  The waits are the kernel's own, see stage_ready.)
+// knew of it.  The waits are the kernel's own, see stage_ready; m0 is no register the compiler keeps values in.)
 __device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t lane_off, u32x4 rsrc, uint32_t scalar_off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :
