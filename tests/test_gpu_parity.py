@@ -664,6 +664,48 @@ def test_bf16_many_sequences_through_the_any_length_kernels(mb, B):
     compare_attention(got, ref, c["mask"], BF16_TOL, 1e-3, "bf16 %d sequences" % B)
 
 
+@pytest.mark.parametrize("rows_mode", [False, True])
+def test_single_tile_backward_one_and_two_units_per_workgroup(mb, rows_mode):
+    """513 (sequence, head) pairs take two per workgroup, the last workgroup one; the same sequences in calls of 255, 255
+    and 3 pairs take one each.  Same arithmetic: bit for bit the same gradients; the first and last sequences against
+    the oracle."""
+    B, L, H, D = 171, 128, 3, 64
+    lengths = np.random.default_rng(7).integers(0, L + 1, size=B)
+    lengths[:3], lengths[-1] = (128, 1, 97), 65
+    c = wl.random_attention_case(71, lengths, L, H, D, std=0.5, bf16=True)
+    qkv = to_dev(np.stack([c["q"], c["k"], c["v"]], axis=2).reshape(B * L, 3, H, D), True)
+    do = to_dev(c["do"].reshape(B * L, H, D), True)
+    slopes = mb.mb_alibi_slopes(H).cuda()
+
+    def grads(b0, b1):
+        mask = torch.from_numpy(c["mask"][b0:b1].copy()).cuda()
+        seqlens, cu, indices, meta = mb.mb_unpad_index(mask)
+        n = (b1 - b0) * L
+        x, g = qkv[b0 * L:b1 * L], do[b0 * L:b1 * L]
+        if not rows_mode:
+            T, _ = mb.mb_read_meta(meta)
+            x = mb.mb_unpad(x.reshape(n, 3 * H * D), indices, n, meta)[:T].view(T, 3, H, D)
+            g = mb.mb_unpad(g.reshape(n, H * D), indices, n, meta)[:T].view(T, H, D)
+        opt = dict(token_rows=indices, T=n) if rows_mode else {}
+        o, lse = torch.zeros_like(g), torch.zeros((H, n if rows_mode else T), device="cuda")
+        mb.mb_alibi_attn_fwd(x[:, 0], x[:, 1], x[:, 2], cu, L, slopes, c["scale"], out=o, lse=lse, **opt)
+        out = torch.zeros_like(x)
+        mb.mb_alibi_attn_bwd(g, x[:, 0], x[:, 1], x[:, 2], o, lse, cu, L, slopes, c["scale"], dq=out[:, 0],
+                             dk=out[:, 1], dv=out[:, 2], **opt)
+        return out
+
+    whole = grads(0, B)
+    assert torch.equal(whole, torch.cat([grads(0, 85), grads(85, 170), grads(170, 171)]))
+    ref = run_oracle(c, orc.alibi_slopes(H), seq_ids=[0, 2, B - 1])
+    at = np.concatenate([[0], np.cumsum(lengths)])
+    for b in (0, 2, B - 1):
+        r0, n = (b * L if rows_mode else at[b]), lengths[b]
+        got = whole[r0:r0 + n].double().cpu().numpy()
+        for i, key in enumerate(("dq", "dk", "dv")):
+            ma, rf = err_stats(got[:, i], ref[b][key])
+            assert ma <= BF16_TOL[0] and rf <= BF16_TOL[1], (b, key, ma, rf)
+
+
 @pytest.mark.parametrize("seed", [0, 1, 2, 3])
 def test_bf16_random_shapes(mb, seed):
     """Random batch sizes, head counts and lengths (both kernel families, chosen by the longest sequence)."""
