@@ -103,11 +103,16 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(const int32_t* __rest
   compact_row(mask + (size_t)b * L, L, b * L, prefix, indices, wave_count);
 }
 
-// Index maps of a small batch in one launch (at most kSmallRows rows and kSmallMask mask entries): every row's block counts
-// the mask in front of its row itself instead of waiting for a launch that counts each row, and block 0 finds the
-// longest row, a wave per row.  8 x 128 positions: two launches of 2.4 and 3.0 us, one of 3.3 us; beyond a few
-// thousand entries the repeated counting costs what the second launch does (256 x 128: 9.2 us either way).
-constexpr int kSmallRows = 64, kSmallMask = 8192;
+// Index maps of a small batch in one launch: every row's block counts the mask in front of its row itself instead of
+// waiting for a launch that counts each row, and block 0 finds the longest row, a wave per row.  That wave is the
+// longest chain: a load per 64 entries of each of its rows, and the sum over its lanes, which takes as long as two loads.
+// Up to 20 such steps one launch is the faster (replayed, two launches and one: 8 x 128 4.9 and 3.6 us, 16 x 128 4.9 and
+// 4.4, 1 x 1024 5.6 and 5.3, 4 x 1024 5.9 and 5.3, 8 x 512 5.4 and 5.1); from 24 on it is the slower (16 x 256 4.9 and
+// 5.3, 32 x 64 5.0 and 5.3, 64 x 16 5.0 and 8.1, 64 x 128 5.0 and 9.9, 1 x 8192 16 and 26).
+constexpr int kSmallSteps = 20;
+static bool index_in_one_launch(int B, int L) {
+  return (int64_t)((B + kWaves - 1) / kWaves) * (((int64_t)L + 63) / 64 + 2) <= kSmallSteps;
+}
 __global__ __launch_bounds__(kThreads) void index_small_kernel(const int32_t* __restrict__ mask, int B, int L,
                                                                int32_t* __restrict__ seqlens,
                                                                int32_t* __restrict__ cu_seqlens,
@@ -278,7 +283,7 @@ __global__ __launch_bounds__(kThreads) void zero_padding_kernel(const int32_t* _
 
 mb_status launch_unpad_index(const int32_t* mask, int B, int L, int32_t* seqlens, int32_t* cu_seqlens,
                              int32_t* indices, int32_t* meta, hipStream_t stream) {
-  if (B > 0 && B <= kSmallRows && (int64_t)B * L <= kSmallMask) {
+  if (B > 0 && index_in_one_launch(B, L)) {
     hipLaunchKernelGGL(index_small_kernel, dim3(B), dim3(kThreads), 0, stream, mask, B, L, seqlens, cu_seqlens, indices,
                        meta);
     return check_launch("index_small_kernel");

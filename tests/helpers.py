@@ -73,3 +73,28 @@ def err_stats(got: np.ndarray, ref: np.ndarray):
     denom = float(np.linalg.norm(ref.ravel()))
     rel_f = float(np.linalg.norm(diff.ravel()) / denom) if denom > 0 else float(np.linalg.norm(diff.ravel()))
     return max_abs, rel_f
+
+
+def replay_us(call, calls=20, replays=5):
+    """Microseconds per call of `call` (kernels only, buffers given), from a graph of `calls` of them: no host time in
+    it.  The least of several replays, which no other load on the GPU can make look faster than it is."""
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(calls):
+            call()
+    graph.replay()
+    times = []
+    for _ in range(replays):
+        start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        start.record()
+        graph.replay()
+        end.record()
+        end.synchronize()
+        times.append(start.elapsed_time(end) * 1e3 / calls)
+    return min(times)

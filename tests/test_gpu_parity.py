@@ -10,7 +10,7 @@ import torch
 
 from oracle import mosaic_oracle as orc
 from paper_2312_17482_amd import workloads as wl
-from tests.helpers import err_stats, run_hip_path, run_oracle, to_dev
+from tests.helpers import err_stats, replay_us, run_hip_path, run_oracle, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -59,9 +59,12 @@ def compare_attention(got, ref, mask, tol, lse_tol, label, abs_floor_ulps=False)
                                         (4, 3, 1000, 1.0), (5, 300, 17, 0.3), (6, 2, 5000, 0.01), (7, 256, 128, 0.8),
                                         (8, 600, 128, 0.7), (9, 3, 40000, 0.5), (10, 512, 128, 1.0), (11, 1, 65536, 0.9),
                                         (12, 65536, 1, 0.5), (13, 1000, 65, 0.2), (14, 1, 63, 1.0),
-                                        # the one-launch path at its limits (64 rows, 8192 entries) and just past them
                                         (15, 64, 128, 0.7), (16, 65, 126, 0.7), (17, 64, 129, 0.7), (18, 1, 8192, 0.4),
-                                        (19, 8, 1024, 0.9), (20, 64, 1, 0.5), (21, 33, 0, 1.0)])
+                                        (19, 8, 1024, 0.9), (20, 64, 1, 0.5), (21, 33, 0, 1.0),
+                                        # the one-launch path at its limits and just past them
+                                        (22, 4, 1152, 0.7), (23, 4, 1153, 0.7), (24, 8, 512, 0.4), (25, 8, 513, 0.4),
+                                        (26, 16, 192, 0.9), (27, 17, 128, 0.5), (28, 24, 64, 0.6), (29, 25, 64, 0.6),
+                                        (30, 40, 0, 1.0), (31, 41, 0, 1.0)])
 def test_unpad_index_arbitrary_masks_bit_exact(mb, seed, B, L, p):
     print("unpad_index seed=%d B=%d L=%d p=%.2f" % (seed, B, L, p), flush=True)
     mask = wl.random_mask(seed, B, L, p)
@@ -71,6 +74,20 @@ def test_unpad_index_arbitrary_masks_bit_exact(mb, seed, B, L, p):
     got = {"T": T, "max_seqlen": mx, "seqlens": seqlens.cpu().numpy(), "cu": cu.cpu().numpy(),
            "indices": indices[:T].cpu().numpy()}
     check_index_maps(got, mask)
+
+
+def test_index_maps_of_up_to_64_rows_take_no_longer_than_those_of_more(mb):
+    """Up to 64 rows the maps can come from one launch or from two; neither may be chosen where it is the slower one.
+    65 x 126 always takes two: batches with fewer rows and entries take no longer (a quarter more for the spread)."""
+    def us(B, L):
+        mask = torch.from_numpy(wl.random_mask(1, B, L, 0.7)).cuda()
+        out = [torch.empty(max(n, 4), dtype=torch.int32, device="cuda") for n in (B, B + 1, B * L, 2)]
+        return replay_us(lambda: mb.raw().mb_unpad_index(mask.data_ptr(), B, L, *[t.data_ptr() for t in out],
+                                                         torch.cuda.current_stream().cuda_stream))
+    bound = 1.25 * us(65, 126)
+    times = {(B, L): us(B, L) for B, L in ((64, 128), (64, 16), (32, 256), (32, 64), (16, 512), (16, 128), (8, 128))}
+    print("index maps", times, "bound", bound, flush=True)
+    assert max(times.values()) <= bound
 
 
 def test_unpad_index_leaves_tail_untouched_and_handles_empty_batch(mb):
