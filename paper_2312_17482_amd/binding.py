@@ -114,7 +114,9 @@ def _check(status: int) -> None:
 # took 84 us of host time for 49 us of kernels), so what is called on every argument touches each tensor once.
 _DTYPE_CODES = {torch.float32: MB_F32, torch.bfloat16: MB_BF16}
 _current_device = torch.cuda.current_device
-_raw_stream = torch._C._cuda_getCurrentRawStream   # (torch.cuda.current_stream() makes a Stream object on every call)
+# (torch.cuda.current_stream() makes a Stream object on every call.  A torch without a GPU backend has no such function:
+# this module can be imported there all the same, for the host-side calls.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _ptr(t) -> int | None:
@@ -122,6 +124,8 @@ def _ptr(t) -> int | None:
 
 
 def _stream() -> int:
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
     return _raw_stream(_current_device())
 
 

@@ -1,11 +1,14 @@
 """Host-side checks of the C ABI that need no GPU: the library loads, exports every symbol the
 header declares, computes the slopes, and rejects bad arguments before launching anything."""
 import ctypes
+import importlib.util
 import os
 import re
+import types
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2312_17482_amd import binding as mb
 
@@ -42,6 +45,19 @@ def test_slopes_against_fixture():
         mb.mb_alibi_slopes(0)
     assert e.value.status == mb.MB_ERR_INVALID_ARG and "H=0" in str(e.value)
     assert lib.mb_alibi_slopes(4, None) == mb.MB_ERR_INVALID_ARG
+
+
+def test_imports_with_a_torch_that_has_no_gpu_backend(monkeypatch):
+    """Such a torch lacks the raw-stream lookup; the module loads and the host-side calls work, and a call that needs a
+    stream asks torch the public way."""
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    spec = importlib.util.spec_from_file_location("binding_without_gpu_backend", mb.__file__)
+    plain = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(plain)
+    assert np.array_equal(plain.mb_alibi_slopes(12).numpy(), mb.mb_alibi_slopes(12).numpy())
+    assert plain.raw().mb_alibi_slopes(4, None) == mb.MB_ERR_INVALID_ARG
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=7))
+    assert plain._stream() == 7
 
 
 def fwd_args(**over):
