@@ -8,7 +8,8 @@
 // other operand is streamed in tiles of 32 rows through two LDS buffers.  The 16x16x4 instruction has the rate of
 // the 32x32x2 one with half the rows per wave, so a batch makes twice as many waves.
 // Forward + backward, fp32, 16 sequences of up to 256 tokens, 12 heads of 64 (9.6 GFLOP): 206 us (50 + 62 + 88), of
-// which the matrix cores are busy a third; one wave per (token, head) on the vector unit, as it was, took 3239 us.
+// which the matrix cores are busy a third; one wave per (token, head) on the vector unit takes 3239 us (and is kept for
+// sequences of a few tokens, below).
 //
 // Instruction layout (lane l, c = l % 16, g = l / 16):  A: row c, k = g.  B: column c, k = g.  D: column c, rows
 // 4 g + v for register v = 0..3.  k is summed away, so it may be numbered freely as long as A and B agree:
@@ -128,14 +129,18 @@ struct Tile {
   }
 };
 
-// A wave's own 16 rows (lane column c) as B operand fragments: register 4 s + e holds element 16 s + 4 g + e.
+// A wave's own 16 rows (lane column c) as B operand fragments: register 4 s + e holds element 16 s + 4 g + e.  (All loads
+// first, as stored: converted where it is loaded, each bf16 piece would wait for the one before it, as in Tile.)
 template <typename E, int NB>
 __device__ __forceinline__ void own_rows(f32x4 (&f)[NB], const E* __restrict__ row, bool ok, int g, int D) {
+  decltype(raw4(row)) r[NB];
 #pragma unroll
   for (int s = 0; s < NB; ++s) {
-    f[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (ok && 16 * s + 4 * g < D) f[s] = floats(raw4(row + 16 * s + 4 * g));
+    r[s] = decltype(raw4(row)){};
+    if (ok && 16 * s + 4 * g < D) r[s] = raw4(row + 16 * s + 4 * g);
   }
+#pragma unroll
+  for (int s = 0; s < NB; ++s) f[s] = floats(r[s]);
 }
 
 // 16 rows of an LDS tile (from `rowp` = its first row, this lane's row c and column 4 g) times the wave's own rows, in
@@ -501,6 +506,212 @@ mb_status bwd_t(const AttnShape& s, const void* dout, const void* q, const void*
   return check_launch("bwd_f32_dkv_kernel");
 }
 
+// ------------------------------------------------------------------------------------------------ very short sequences
+// One wave per (token, head) on the vector unit.  The kernels above give a sequence at least one workgroup and a whole
+// tile of products however short it is: with a handful of tokens per sequence most of that is padding, and a workgroup's
+// chain of loads, products and barriers is longer than the work.  Here every token is its own wave with nothing in front
+// of it but its rows.  `limit` <= kTokenMax bounds the sequences' lengths.
+constexpr int kTokenMax = 16;
+
+__device__ __forceinline__ float to_f32(float x) { return x; }
+__device__ __forceinline__ float to_f32(uint16_t x) { return __uint_as_float((uint32_t)x << 16); }
+__device__ __forceinline__ void from_f32(float* p, float x) { *p = x; }
+__device__ __forceinline__ void from_f32(uint16_t* p, float x) { *p = (uint16_t)bf16_rne(x); }
+__device__ __forceinline__ float wave_sum(float x) {
+  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+  return x;
+}
+__device__ __forceinline__ float wave_max(float x) {
+  for (int off = 32; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, 64));
+  return x;
+}
+// Sequence that owns packed token t: the b with cu[b] <= t < cu[b+1] (empty sequences are skipped).
+__device__ __forceinline__ int seq_of_token(const int32_t* __restrict__ cu, int B, int t) {
+  int lo = 0, hi = B;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (cu[mid] <= t) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+template <typename E>
+__global__ __launch_bounds__(64) void fwd_token_kernel(
+    const E* __restrict__ q, const E* __restrict__ k, const E* __restrict__ v, int64_t qs, int64_t ks, int64_t vs,
+    const int32_t* __restrict__ cu, int B, int T, int D, const float* __restrict__ slopes, float scale,
+    E* __restrict__ o, int64_t os, float* __restrict__ lse, const int32_t* __restrict__ rows, int limit,
+    int32_t* __restrict__ misuse) {
+  __shared__ float sq[128], ss[kTokenMax];
+  const int t = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
+  if (t >= cu[B]) return;   // T may be a capacity: rows past the last real token are not touched
+  const int b = seq_of_token(cu, B, t);
+  const int start = cu[b], n = cu[b + 1] - start, i = t - start;
+  if (n > limit) {   // longer than the caller promised: skipped
+    raise_misuse(misuse);
+    if (lane == 0) lse[(int64_t)h * T + t] = __builtin_nanf("");
+    return;
+  }
+  const float slope = slopes[h];
+  for (int d = lane; d < D; d += 64) sq[d] = to_f32(q[tok_row(rows, t) * qs + h * D + d]);
+  __syncthreads();
+  float s = -INFINITY;
+  if (lane < n) {
+    const E* kr = k + tok_row(rows, start + lane) * ks + h * D;
+    float dot = 0.f;
+    for (int d = 0; d < D; ++d) dot = fmaf(sq[d], to_f32(kr[d]), dot);
+    s = scale * dot - slope * fabsf((float)(i - lane));
+  }
+  const float m = wave_max(s);
+  const float e = lane < n ? expf(s - m) : 0.f;
+  if (lane < n) ss[lane] = e;
+  const float z = wave_sum(e);
+  __syncthreads();
+  const float inv = 1.f / z;
+  for (int d = lane; d < D; d += 64) {
+    float acc = 0.f;
+    for (int j = 0; j < n; ++j) acc = fmaf(ss[j], to_f32(v[tok_row(rows, start + j) * vs + h * D + d]), acc);
+    from_f32(&o[tok_row(rows, t) * os + h * D + d], acc * inv);
+  }
+  if (lane == 0) lse[(int64_t)h * T + t] = m + logf(z);
+}
+
+// Query side: Delta_i, dS_ij for all j, dQ_i.
+template <typename E>
+__global__ __launch_bounds__(64) void bwd_token_dq_kernel(
+    const E* __restrict__ dout, const E* __restrict__ q, const E* __restrict__ k, const E* __restrict__ v,
+    const E* __restrict__ o, const float* __restrict__ lse, int64_t dos, int64_t qs, int64_t ks, int64_t vs,
+    int64_t os, const int32_t* __restrict__ cu, int B, int T, int D, const float* __restrict__ slopes, float scale,
+    E* __restrict__ dq, int64_t dqs, float* __restrict__ delta, const int32_t* __restrict__ rows, int limit,
+    int32_t* __restrict__ misuse) {
+  __shared__ float sq[128], sg[128], sds[kTokenMax];
+  const int t = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
+  if (t >= cu[B]) return;
+  const int b = seq_of_token(cu, B, t);
+  const int start = cu[b], n = cu[b + 1] - start, i = t - start;
+  if (n > limit) {
+    raise_misuse(misuse);
+    return;
+  }
+  const float slope = slopes[h];
+  float part = 0.f;
+  for (int d = lane; d < D; d += 64) {
+    const float g = to_f32(dout[tok_row(rows, t) * dos + h * D + d]);
+    sq[d] = to_f32(q[tok_row(rows, t) * qs + h * D + d]);
+    sg[d] = g;
+    part = fmaf(g, to_f32(o[tok_row(rows, t) * os + h * D + d]), part);
+  }
+  const float dlt = wave_sum(part);
+  if (lane == 0) delta[(int64_t)h * T + t] = dlt;
+  __syncthreads();
+  const float l = lse[(int64_t)h * T + t];
+  if (lane < n) {
+    const E* kr = k + tok_row(rows, start + lane) * ks + h * D;
+    const E* vr = v + tok_row(rows, start + lane) * vs + h * D;
+    float dot = 0.f, dp = 0.f;
+    for (int d = 0; d < D; ++d) {
+      dot = fmaf(sq[d], to_f32(kr[d]), dot);
+      dp = fmaf(sg[d], to_f32(vr[d]), dp);
+    }
+    sds[lane] = expf(scale * dot - slope * fabsf((float)(i - lane)) - l) * (dp - dlt);
+  }
+  __syncthreads();
+  for (int d = lane; d < D; d += 64) {
+    float acc = 0.f;
+    for (int j = 0; j < n; ++j) acc = fmaf(sds[j], to_f32(k[tok_row(rows, start + j) * ks + h * D + d]), acc);
+    from_f32(&dq[tok_row(rows, t) * dqs + h * D + d], scale * acc);
+  }
+}
+
+// Key side: P_ij and dS_ij for all i, dV_j and dK_j.
+template <typename E>
+__global__ __launch_bounds__(64) void bwd_token_dkv_kernel(
+    const E* __restrict__ dout, const E* __restrict__ q, const E* __restrict__ k, const E* __restrict__ v,
+    const float* __restrict__ lse, const float* __restrict__ delta, int64_t dos, int64_t qs, int64_t ks, int64_t vs,
+    const int32_t* __restrict__ cu, int B, int T, int D, int limit, const float* __restrict__ slopes, float scale,
+    E* __restrict__ dk, E* __restrict__ dv, int64_t dks, int64_t dvs, const int32_t* __restrict__ rows,
+    int32_t* __restrict__ misuse) {
+  __shared__ float sk[128], sv[128], sp[kTokenMax], sds[kTokenMax];
+  const int t = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
+  if (t >= cu[B]) return;
+  const int b = seq_of_token(cu, B, t);
+  const int start = cu[b], n = cu[b + 1] - start, j = t - start;
+  if (n > limit) {
+    raise_misuse(misuse);
+    return;
+  }
+  const float slope = slopes[h];
+  for (int d = lane; d < D; d += 64) {
+    sk[d] = to_f32(k[tok_row(rows, t) * ks + h * D + d]);
+    sv[d] = to_f32(v[tok_row(rows, t) * vs + h * D + d]);
+  }
+  __syncthreads();
+  if (lane < n) {
+    const E* qr = q + tok_row(rows, start + lane) * qs + h * D;
+    const E* gr = dout + tok_row(rows, start + lane) * dos + h * D;
+    float dot = 0.f, dp = 0.f;
+    for (int d = 0; d < D; ++d) {
+      dot = fmaf(to_f32(qr[d]), sk[d], dot);
+      dp = fmaf(to_f32(gr[d]), sv[d], dp);
+    }
+    const float p = expf(scale * dot - slope * fabsf((float)(lane - j)) - lse[(int64_t)h * T + start + lane]);
+    sp[lane] = p;
+    sds[lane] = p * (dp - delta[(int64_t)h * T + start + lane]);
+  }
+  __syncthreads();
+  for (int d = lane; d < D; d += 64) {
+    float av = 0.f, ak = 0.f;
+    for (int i = 0; i < n; ++i) {
+      av = fmaf(sp[i], to_f32(dout[tok_row(rows, start + i) * dos + h * D + d]), av);
+      ak = fmaf(sds[i], to_f32(q[tok_row(rows, start + i) * qs + h * D + d]), ak);
+    }
+    from_f32(&dv[tok_row(rows, t) * dvs + h * D + d], av);
+    from_f32(&dk[tok_row(rows, t) * dks + h * D + d], scale * ak);
+  }
+}
+
+// Longest sequence the launch has to expect, and whether the per-token kernels are the faster ones for it.
+int longest_of(const AttnShape& s) { return s.max_seqlen < s.T ? s.max_seqlen : s.T; }
+// The line is drawn where neither forward nor backward loses by taking the tile kernels; T * H waves is what the token
+// kernels start.  Replayed, us, token kernels | tile kernels.  fp32, D = 64, 4 heads, forward; backward:
+//   2048 sequences of 1 token 8.6; 24 | 48; 157     of 6 tokens 52; 133 | 55; 167        of 8 tokens 70; 192 | 56; 169
+//   4 sequences of 8 tokens 4.6; 9.1 | 4.7; 10.4    of 12 tokens 4.9; 10.0 | 4.7; 10.7   of 16 tokens 5.1; 10.8 | 4.8; 10.5
+// bf16, D = 128: 2048 sequences of 12 tokens 171; 490 | 140; 549    of 16 tokens 260; 765 | 135; 514.
+bool per_token(const AttnShape& s, mb_dtype dt) {
+  const int n = longest_of(s);
+  const int64_t waves = (int64_t)s.T * s.H;
+  const bool wide_bf16 = dt == MB_BF16 && s.D > 64;   // where the tile kernels have one workgroup per compute unit
+  if (n <= 4) return true;
+  if (n > kTokenMax || s.D <= 16) return false;
+  if (n <= 6) return true;
+  if (n <= 8) return s.D > 64 || waves <= 8192;
+  if (n <= 12) return wide_bf16 || (s.D > 32 && waves <= 2048);
+  return wide_bf16 && waves <= 512;
+}
+
+template <typename E>
+mb_status fwd_token_t(const AttnShape& s, const void* q, const void* k, const void* v, int64_t qs, int64_t ks, int64_t vs,
+                      void* o, int64_t os, float* lse, hipStream_t stream) {
+  fwd_token_kernel<E><<<dim3(s.T, s.H), dim3(64), 0, stream>>>((const E*)q, (const E*)k, (const E*)v, qs, ks, vs,
+                                                             s.cu_seqlens, s.B, s.T, s.D, s.slopes, s.scale, (E*)o, os,
+                                                             lse, s.token_rows, longest_of(s), s.misuse);
+  return check_launch("fwd_token_kernel");
+}
+
+template <typename E>
+mb_status bwd_token_t(const AttnShape& s, const void* dout, const void* q, const void* k, const void* v, const void* o,
+                      const float* lse, int64_t dos, int64_t qs, int64_t ks, int64_t vs, int64_t os, void* dq, void* dk,
+                      void* dv, int64_t dqs, int64_t dks, int64_t dvs, float* delta, hipStream_t stream) {
+  bwd_token_dq_kernel<E><<<dim3(s.T, s.H), dim3(64), 0, stream>>>(
+      (const E*)dout, (const E*)q, (const E*)k, (const E*)v, (const E*)o, lse, dos, qs, ks, vs, os, s.cu_seqlens, s.B,
+      s.T, s.D, s.slopes, s.scale, (E*)dq, dqs, delta, s.token_rows, longest_of(s), s.misuse);
+  const mb_status st = check_launch("bwd_token_dq_kernel");
+  if (st != MB_OK) return st;
+  bwd_token_dkv_kernel<E><<<dim3(s.T, s.H), dim3(64), 0, stream>>>(
+      (const E*)dout, (const E*)q, (const E*)k, (const E*)v, lse, delta, dos, qs, ks, vs, s.cu_seqlens, s.B, s.T, s.D,
+      longest_of(s), s.slopes, s.scale, (E*)dk, (E*)dv, dks, dvs, s.token_rows, s.misuse);
+  return check_launch("bwd_token_dkv_kernel");
+}
+
 // fn<E, NB>(args...) with the head size rounded up to the next instantiated number of 16-column blocks.
 #define MB_BY_HEAD_SIZE(fn, E, ...)                       \
   ((s.D <= 16)   ? fn<E, 1>(s, __VA_ARGS__)               \
@@ -515,6 +726,9 @@ mb_status bwd_t(const AttnShape& s, const void* dout, const void* q, const void*
 mb_status launch_attn_fwd_generic(const AttnShape& s, mb_dtype dt, const void* q, const void* k, const void* v,
                                   int64_t qs, int64_t ks, int64_t vs, void* o, int64_t os, float* lse,
                                   hipStream_t stream) {
+  if (per_token(s, dt))
+    return dt == MB_F32 ? fwd_token_t<float>(s, q, k, v, qs, ks, vs, o, os, lse, stream)
+                        : fwd_token_t<uint16_t>(s, q, k, v, qs, ks, vs, o, os, lse, stream);
   return dt == MB_F32 ? MB_BY_HEAD_SIZE(fwd_t, float, q, k, v, qs, ks, vs, o, os, lse, stream)
                       : MB_BY_HEAD_SIZE(fwd_t, uint16_t, q, k, v, qs, ks, vs, o, os, lse, stream);
 }
@@ -523,6 +737,11 @@ mb_status launch_attn_bwd_generic(const AttnShape& s, mb_dtype dt, const void* d
                                   const void* v, const void* o, const float* lse, int64_t dos, int64_t qs,
                                   int64_t ks, int64_t vs, int64_t os, void* dq, void* dk, void* dv, int64_t dqs,
                                   int64_t dks, int64_t dvs, float* delta_ws, hipStream_t stream) {
+  if (per_token(s, dt))
+    return dt == MB_F32 ? bwd_token_t<float>(s, dout, q, k, v, o, lse, dos, qs, ks, vs, os, dq, dk, dv, dqs, dks, dvs,
+                                             delta_ws, stream)
+                        : bwd_token_t<uint16_t>(s, dout, q, k, v, o, lse, dos, qs, ks, vs, os, dq, dk, dv, dqs, dks, dvs,
+                                                delta_ws, stream);
   return dt == MB_F32 ? MB_BY_HEAD_SIZE(bwd_t, float, dout, q, k, v, o, lse, dos, qs, ks, vs, os, dq, dk, dv, dqs, dks,
                                         dvs, delta_ws, stream)
                       : MB_BY_HEAD_SIZE(bwd_t, uint16_t, dout, q, k, v, o, lse, dos, qs, ks, vs, os, dq, dk, dv, dqs,

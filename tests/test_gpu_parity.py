@@ -190,6 +190,55 @@ def test_generic_tile_edges(mb, bf16, D):
                       "generic edges D=%d bf16=%s" % (D, bf16))
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("D", [8, 16, 24, 32, 64, 72, 128])
+@pytest.mark.parametrize("L,B", [(1, 3), (4, 9), (5, 70), (6, 9), (7, 9), (8, 1030), (9, 9), (12, 90), (13, 5), (16, 5), (17, 5)])
+def test_generic_very_short_sequences(mb, L, B, D, bf16):
+    """Both sides of every line between the kernels of a wave per token and the tile kernels (the longest length and how
+    many waves there are), every length up to the longest among the sequences, empty ones too; bf16 storage with head
+    size 64 reaches them through a negative scale.  Tolerances as for the other fp32 / bf16 cases.  A sequence of one token
+    has P = 1 and dS = dP - Delta = 0: its dQ and dK are what rounding leaves of a difference of two equal sums (fp32: D
+    terms of at most about 10, 2^-24 each; bf16: O is rounded to 2^-9 first), so they are held to the absolute bound only."""
+    lengths = [L, 0] + [1 + i % L for i in range(B - 2)]
+    print("generic short L=%d B=%d D=%d bf16=%s" % (L, B, D, bf16), flush=True)
+    c = wl.random_attention_case(26, lengths, L, 2, D, std=0.5, bf16=bf16)
+    slopes = mb.mb_alibi_slopes(2)
+    scale = -0.2 if bf16 and D == 64 else c["scale"]
+    got = run_hip_path(mb, c, slopes, bf16=bf16, scale=scale)
+    ref = run_oracle(c, orc.alibi_slopes(2), scale=scale)
+    tol = BF16_TOL if bf16 else F32_TOL
+    if L == 1:
+        for key in ("dq", "dk"):
+            assert np.max(np.abs(ref[key])) < 1e-12 and np.max(np.abs(got[key])) <= tol[0]
+            got[key] = ref[key]
+    compare_attention(got, ref, c["mask"], tol, 1e-3 if bf16 else 1e-4,
+                      "generic short L=%d D=%d bf16=%s" % (L, D, bf16))
+
+
+@pytest.mark.parametrize("bf16,D", [(False, 64), (True, 128)])
+def test_generic_time_of_very_short_sequences(mb, bf16, D):
+    """2048 tokens in 2048 sequences of one: a wave per token and head (33 us forward + backward, fp32, D = 64) and not a
+    workgroup and a tile of products (204 us).  Bound: 2.5 times the time of the same tokens in sequences of 16 (23 us)."""
+    def us(n):
+        H, B = 4, 2048 // n
+        qkv = torch.randn((2048, 3, H, D), device="cuda").to(torch.bfloat16 if bf16 else torch.float32)
+        do = torch.randn((2048, H, D), device="cuda").to(qkv.dtype)
+        cu = torch.arange(B + 1, dtype=torch.int32, device="cuda") * n
+        slopes, scale = mb.mb_alibi_slopes(H).cuda(), D ** -0.5
+        o, lse, d = torch.empty_like(do), torch.empty((H, 2048), device="cuda"), torch.empty_like(qkv)
+        ws = torch.empty(mb.mb_alibi_attn_bwd_workspace_bytes(B, 2048, n, H, D, mb.MB_BF16 if bf16 else mb.MB_F32),
+                         dtype=torch.uint8, device="cuda")
+        q, k, v = (qkv[:, i] for i in range(3))
+
+        def call():
+            mb.mb_alibi_attn_fwd(q, k, v, cu, n, slopes, scale, out=o, lse=lse)
+            mb.mb_alibi_attn_bwd(do, q, k, v, o, lse, cu, n, slopes, scale, dq=d[:, 0], dk=d[:, 1], dv=d[:, 2], workspace=ws)
+        return replay_us(call)
+    one, sixteen = us(1), us(16)
+    print("generic short: sequences of 1 %.1f us, of 16 %.1f us" % (one, sixteen), flush=True)
+    assert one <= 2.5 * sixteen
+
+
 def test_generic_token_rows_with_holes_and_more_sequences_than_blocks(mb):
     """Rows looked up per token, a capacity T, and a batch of mostly empty sequences (more work slots than tokens)."""
     B, L, H, D = 400, 24, 3, 20
@@ -474,7 +523,9 @@ def test_all_sequences_empty_and_single_token_batches(mb):
 
 @pytest.mark.parametrize("bf16,D,lengths,promised", [(True, 64, [100, 140, 64], 128),     # single-tile kernels
                                                      (True, 64, [100, 300, 600], 384),   # any-length kernels
-                                                     (False, 16, [20, 50, 7], 32)])       # generic kernels
+                                                     (False, 16, [20, 50, 7], 32),        # generic kernels
+                                                     (False, 16, [3, 5, 2], 4),           # a wave per token
+                                                     (True, 128, [6, 40, 8, 9], 8)])
 def test_sequence_longer_than_max_seqlen_is_skipped_and_reported(mb, bf16, D, lengths, promised):
     """An understated max_seqlen must not truncate silently: the sequences that fit are computed as usual, a
     longer one is skipped (its rows of o and of the gradients untouched, its rows of lse NaN) and
