@@ -73,16 +73,6 @@ constexpr int kGatedFwd = 1;   // out = GeLU(x W1) (*) x V on the accumulators (
 constexpr int kPartial = 3;    // out = fp32 sums of one of several splits of the contraction
 constexpr int kGateBwd = 2;    // the product is dA; with h | g read from `aux`: out = dA g GeLU'(h) | dA GeLU(h)
 
-// One wave moves 64 x 16 bytes from global memory straight into LDS: lane l's piece lands at byte `lds` + 16 l.  Lanes
-// whose offset lies outside the descriptor deposit zeros.  (Inline assembly on purpose: it writes no register, and the
-// compiler, which cannot tell one part of LDS from another, would wait for every such load before any LDS read if it
-// knew of it.  The waits are the kernel's own, see stage_ready; m0 is no register the compiler keeps values in.)
-__device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t lane_off, u32x4 rsrc, uint32_t scalar_off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(lds), "v"(lane_off), "s"(rsrc), "s"(scalar_off)
-               : "memory");
-}
 // Descriptor of `bytes` bytes from `base` (both wave-uniform).
 __device__ __forceinline__ u32x4 raw_rsrc(const uint16_t* base, uint32_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(base);

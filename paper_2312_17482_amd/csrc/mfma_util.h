@@ -84,6 +84,23 @@ __device__ __forceinline__ bf16x8 join_tr(s16x4 lo, s16x4 hi) {
   return __builtin_bit_cast(bf16x8, r);
 }
 
+// One wave moves 64 x 16 bytes from global memory straight into LDS: lane l's piece lands at byte `lds` + 16 l.  Lanes
+// whose offset lies outside the descriptor deposit zeros.  (Inline assembly on purpose: it writes no register, and the
+// compiler, which cannot tell one part of LDS from another, would wait for every such load before any LDS read if it
+// knew of it.  The waits are the kernel's own.  m0 is a result of it: the compiler has to know that it changed.)
+// A scalar register that a vector instruction wrote (a descriptor word kept in a vector lane and read back) may be used by
+// the load five wait states later at the earliest, and the compiler does not see the load.  Five waits here would cost
+// 1 to 5 % of every product (T = 1000, 4096 -> 1024: 18.0 to 18.4 us; 12000, 3072 -> 768: 54.4 to 56.9), so the built code is
+// looked through instead: tests/test_lds_load.py finds every such load that comes too early.
+__device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t lane_off, u32x4 rsrc, uint32_t scalar_off) {
+  uint32_t m0;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds"
+               : "=&{m0}"(m0)
+               : "s"(lds), "v"(lane_off), "s"(rsrc), "s"(scalar_off)
+               : "memory");
+  (void)m0;
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 }  // namespace mb
