@@ -32,6 +32,7 @@ namespace mb {
 namespace {
 
 constexpr int kBK = 64;                               // k per stage
+constexpr int kComputeUnits = 256;
 constexpr int kGroupM = 4;                            // token panels walked together (L2 reuse of the weight tiles)
 
 // GeLU(h) = h * Phi(h), the exact (error-function) form, with Phi evaluated by the classic five-term
@@ -89,6 +90,11 @@ __device__ __forceinline__ void stage_ready() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(kNewer) : "memory");
 }
 
+constexpr int kSlabElems = 32 * 32;   // per wave: 32 tokens x 32 columns on their way out
+// LDS of a tile shape, elements: kStages stages of 64 kMB token rows and 32 kWN kNB weight rows, and the waves' slabs.
+template <int kMB, int kWN, int kNB, int kStages>
+constexpr int kGemmLds = kStages * (64 * kMB + 32 * kWN * kNB) * kBK + 2 * kWN * kSlabElems;
+
 // One workgroup of 2 kWN waves (2 along the tokens by kWN along the weight rows) per compute unit walks the tiles
 // blockIdx.x, + gridDim.x, ...  A tile is 64 kMB tokens x 32 kWN kNB weight rows; a wave computes 32 kMB x 32 kNB of it.
 // Wide (4 x 2 blocks, two stages): 64 to 320 tokens x 256.  Narrow (2 x 1 blocks, eight stages): 64 x 64 for products of
@@ -96,23 +102,17 @@ __device__ __forceinline__ void stage_ready() {
 // X rows and W rows are both K elements long.  kPartial: the contraction is split, tile id = split * tiles + tile, and
 // the split's fp32 sums go to out (as float) + split * T_cap * ldo.
 template <int kMode, int kMB, int kWN, int kNB, int kStages>
-__global__ __launch_bounds__(128 * kWN, kWN / 2) void ffn_gemm_kernel(const uint16_t* __restrict__ X,
-                                                          const uint16_t* __restrict__ W, int K, int n_tiles,
-                                                          int splits, int gate_row, int w_rows, int T_cap,
-                                                          const int32_t* __restrict__ meta,
-                                                          uint16_t* __restrict__ out, int ldo,
-                                                          const uint16_t* __restrict__ aux, int gate_col) {
+__device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int K,
+                                           int n_tiles, int splits, int gate_row, int w_rows, int T, int T_cap,
+                                           uint16_t* __restrict__ out, int ldo, const uint16_t* __restrict__ aux,
+                                           int gate_col, uint16_t* __restrict__ smem) {
   constexpr bool kGated = kMode == kGatedFwd;
   constexpr int kBM = 64 * kMB, kBN = 32 * kWN * kNB, kWaves = 2 * kWN;
   static_assert(!kGated || kNB == 2, "the gated epilogue pairs the wave's two weight blocks");
   constexpr int kRows = kBM + kBN;                  // rows of a stage: tokens, then weight rows
   constexpr int kStageElems = kRows * kBK;
   constexpr int kLoads = kRows / (8 * kWaves);      // 8-row loads per wave and k step
-  constexpr int kSlabElems = 32 * 32;               // per wave: 32 tokens x 32 columns on their way out
-  __shared__ __attribute__((aligned(1024))) uint16_t smem[kStages * kStageElems + kWaves * kSlabElems];
 
-  // (readfirstlane: tells the compiler the value is wave-uniform, so descriptors built from it stay scalar)
-  const int T = __builtin_amdgcn_readfirstlane(meta ? min(meta[0], T_cap) : T_cap);
   // (the grid is sized for T_cap rows; the tile map uses the token panels that hold tokens, so that the
   // idle workgroups are the last ones and not the share of one XCD)
   const int m_tiles = (T + kBM - 1) / kBM;
@@ -187,11 +187,21 @@ __global__ __launch_bounds__(128 * kWN, kWN / 2) void ffn_gemm_kernel(const uint
   constexpr int kWaveCols = kGated ? 32 : 32 * kNB;   // output columns per wave
   const uint32_t wrow = (kBM + wn * kWaveCols) * kBK;
   constexpr uint32_t kWBlock = (kGated ? kBN / 2 : 32) * kBK;   // from the first weight block of the wave to the second
+  // (Narrow: a step is a chain of latencies, so the sums are kept and one addition per read is left.  1000 x 768, K = 3072:
+  // 13.9 us with the additions as the compiler orders them, 13.3 us so.)
+  constexpr bool kKeepSums = kStages > 2;
+  uint32_t xfrag[4], wfrag[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    xfrag[kk] = xrow + frag[kk];
+    wfrag[kk] = wrow + frag[kk];
+    if (kKeepSums) asm volatile("" : "+v"(xfrag[kk]), "+v"(wfrag[kk]));
+  }
   bf16x8 xf[2][kMB], wf[2][kNB];
   auto read_frag = [&](int stage, int kk, int i) {   // weight fragments first
     const uint16_t* cur = smem + stage * kStageElems;
-    if (i < kNB) wf[kk & 1][i] = lds_read8(cur + wrow + i * kWBlock + frag[kk]);
-    else xf[kk & 1][i - kNB] = lds_read8(cur + xrow + (i - kNB) * 32 * kBK + frag[kk]);
+    if (i < kNB) wf[kk & 1][i] = lds_read8(cur + wfrag[kk] + i * kWBlock);
+    else xf[kk & 1][i - kNB] = lds_read8(cur + xfrag[kk] + (i - kNB) * 32 * kBK);
   };
   constexpr int kFrags = kMB + kNB, kMfma = kMB * kNB;
   f32x16 acc[kNB][kMB];
@@ -366,6 +376,90 @@ __global__ __launch_bounds__(128 * kWN, kWN / 2) void ffn_gemm_kernel(const uint
     }
   }
   stage_ready<0>();   // no load may still be on its way to LDS that the next workgroup owns
+}
+
+template <int kMode, int kMB, int kWN, int kNB, int kStages>
+__global__ __launch_bounds__(128 * kWN, kWN / 2) void ffn_gemm_kernel(const uint16_t* __restrict__ X,
+                                                                      const uint16_t* __restrict__ W, int K, int n_tiles,
+                                                                      int splits, int gate_row, int w_rows, int T_cap,
+                                                                      const int32_t* __restrict__ meta,
+                                                                      uint16_t* __restrict__ out, int ldo,
+                                                                      const uint16_t* __restrict__ aux, int gate_col) {
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kGemmLds<kMB, kWN, kNB, kStages>];
+  // (readfirstlane: tells the compiler the value is wave-uniform, so descriptors built from it stay scalar)
+  const int T = __builtin_amdgcn_readfirstlane(meta ? min(meta[0], T_cap) : T_cap);
+  gemm_tiles<kMode, kMB, kWN, kNB, kStages>(X, W, K, n_tiles, splits, gate_row, w_rows, T, T_cap, out, ldo, aux, gate_col,
+                                            smem);
+}
+
+// The tile height (in 64 tokens, up to 320) with the least estimated time for T tokens, n_tiles weight tiles of 256 rows
+// and `splits` shares of the contraction: rounds over the compute units times a k step's hundredths of a microsecond.  A
+// k step of a tile took 0.31 (mb + 1) us with all compute units busy (26963 x 768, K = 6144: mb = 1 .. 4 68, 89, 120,
+// 152 us a round) and no less than 0.7 us alone, where the loads' latency shows.  A tile count just above a multiple of
+// 256 leaves the last round nearly empty (26963 x 768, K = 3072: tiles of 256 tokens 132 us, of 320 tokens 101 us;
+// 945 x 6144, K = 768: 256 tokens 20 us, 128 tokens 14 us).
+static inline int64_t height_cost(int T, int n_tiles, int splits, int mb) {
+  const int64_t tiles = (int64_t)((T + 64 * mb - 1) / (64 * mb)) * n_tiles * splits;
+  const int step = 31 * (mb + 1);
+  return (tiles + kComputeUnits - 1) / kComputeUnits * (step < 70 ? 70 : step);
+}
+static inline int tile_height(int T, int n_tiles, int splits) {
+  int best = 5;
+  int64_t least = height_cost(T, n_tiles, splits, 5);
+#pragma unroll
+  for (int mb = 4; mb > 0; --mb) {
+    const int64_t cost = height_cost(T, n_tiles, splits, mb);
+    if (cost < least) {
+      least = cost;
+      best = mb;
+    }
+  }
+  return best;
+}
+
+// The heights for up to 64 stretches of row counts, 1 << shift rows each, that reach up to a capacity: four bits for each
+// (made in 0.5 us of host time).
+struct TileHeights {
+  uint64_t word[4];
+  int shift;
+};
+static TileHeights tile_heights(int T_cap, int n_tiles, int splits) {
+  TileHeights h{{0, 0, 0, 0}, 6};
+  while ((T_cap - 1) >> h.shift > 63) ++h.shift;
+  for (int i = 0; i <= (T_cap - 1) >> h.shift; ++i) {
+    const int64_t last = (int64_t)(i + 1) << h.shift;
+    h.word[i >> 4] |= (uint64_t)tile_height(last < T_cap ? (int)last : T_cap, n_tiles, splits) << (4 * (i & 15));
+  }
+  return h;
+}
+
+// For a row count that only the device knows: the height that suits that count is chosen here and not for the capacity
+// on the host, whose choice is the worse the emptier the buffers are (in 32768 rows: 16384 tokens, K = 3072, 768 columns, 87
+// and 69 us; 945 tokens, K = 768, 2304 columns, 21.2 and 9.7 us).  Out of a table and not by the estimates: their code is
+// cold and took 1 us in front of every product.
+template <int kMode>
+__global__ __launch_bounds__(512, 2) void ffn_gemm_counted_kernel(const uint16_t* __restrict__ X,
+                                                                  const uint16_t* __restrict__ W, int K, int n_tiles,
+                                                                  int splits, int gate_row, int w_rows, int T_cap,
+                                                                  const int32_t* __restrict__ meta,
+                                                                  uint16_t* __restrict__ out, int ldo,
+                                                                  const uint16_t* __restrict__ aux, int gate_col,
+                                                                  TileHeights heights) {
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kGemmLds<5, 4, 2, 2>];
+  const int T = __builtin_amdgcn_readfirstlane(min(meta[0], T_cap));
+#define MB_TILE(n) \
+  gemm_tiles<kMode, n, 4, 2, 2>(X, W, K, n_tiles, splits, gate_row, w_rows, T, T_cap, out, ldo, aux, gate_col, smem)
+  const int at = (max(T, 1) - 1) >> heights.shift;
+  const uint64_t word = at < 32 ? (at < 16 ? heights.word[0] : heights.word[1])
+                                : (at < 48 ? heights.word[2] : heights.word[3]);
+  switch ((int)(word >> (4 * (at & 15))) & 7) {
+    case 1: MB_TILE(1); break;
+    case 2: MB_TILE(2); break;
+    case 3: MB_TILE(3); break;
+    case 4: MB_TILE(4); break;
+    default: MB_TILE(5);
+  }
+#undef MB_TILE
 }
 
 // a = GeLU(h) (*) g, elementwise over [T, inter]: the separate activation pass of the unfused arrangements
@@ -575,8 +669,6 @@ __global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* __restri
 
 }  // namespace
 
-constexpr int kComputeUnits = 256;
-
 template <int kMode, int kMB, int kWN, int kNB, int kStages>
 static void launch_gemm_tile(const void* x, const void* wt, int K, int n_cols, int splits, int gate_row, int w_rows,
                              int T_cap, const int32_t* meta, void* out, int ldo, const uint16_t* aux, int gate_col,
@@ -590,31 +682,27 @@ static void launch_gemm_tile(const void* x, const void* wt, int K, int n_cols, i
           meta, static_cast<uint16_t*>(out), ldo, aux, gate_col);
 }
 
-// Estimated microseconds of a product with tiles of 64 mb tokens and `splits` shares of the contraction.  A k step of a
-// tile took 0.31 (mb + 1) us with all compute units busy (26963 x 768, K = 6144: mb = 1 .. 4 68, 89, 120, 152 us a
-// round) and no less than 0.7 us alone, where the loads' latency shows.
-static double gemm_cost(int T_cap, int n_cols, int K, int mb, int splits) {
-  const int64_t tiles = (int64_t)((T_cap + 64 * mb - 1) / (64 * mb)) * ((n_cols + 255) / 256) * splits;
-  const double step = 0.31 * (mb + 1);
-  return (double)((tiles + kComputeUnits - 1) / kComputeUnits) * (K / (kBK * splits)) * (step < 0.7 ? 0.7 : step);
-}
-
-// The tile height (64 to 320 tokens) with the least cost: a tile count just above a multiple of 256 leaves the last
-// round nearly empty (26963 x 768, K = 3072: tiles of 256 tokens 132 us, of 320 tokens 101 us; 945 x 6144, K = 768:
-// 256 tokens 20 us, 128 tokens 14 us).
-static int tile_height(int T_cap, int n_cols, int K, int splits) {
-  int best = 5;
-  for (int mb = 4; mb > 0; --mb)
-    if (gemm_cost(T_cap, n_cols, K, mb, splits) < gemm_cost(T_cap, n_cols, K, best, splits)) best = mb;
-  return best;
+// Estimated microseconds of a product in tiles of the best height, `splits` shares of the contraction.
+static double gemm_cost(int T_cap, int n_cols, int K, int splits) {
+  const int n_tiles = (n_cols + 255) / 256;
+  return 0.01 * (double)height_cost(T_cap, n_tiles, splits, tile_height(T_cap, n_tiles, splits)) * (K / (kBK * splits));
 }
 
 template <int kMode>
 static void launch_gemm(const void* x, const void* wt, int K, int n_cols, int splits, int gate_row, int w_rows, int T_cap,
                         const int32_t* meta, void* out, int ldo, const uint16_t* aux, int gate_col, hipStream_t stream) {
+  const int n_tiles = (n_cols + 255) / 256;
+  if (meta) {
+    // as many workgroups as the lowest tiles of a full buffer would take, one per compute unit at most
+    const int64_t most = (int64_t)((T_cap + 63) / 64) * n_tiles * splits;
+    ffn_gemm_counted_kernel<kMode><<<dim3((unsigned)(most < kComputeUnits ? most : kComputeUnits)), dim3(512), 0, stream>>>(
+        static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_tiles, splits, gate_row, w_rows, T_cap,
+        meta, static_cast<uint16_t*>(out), ldo, aux, gate_col, tile_heights(T_cap, n_tiles, splits));
+    return;
+  }
 #define MB_TILE(n) \
   launch_gemm_tile<kMode, n, 4, 2, 2>(x, wt, K, n_cols, splits, gate_row, w_rows, T_cap, meta, out, ldo, aux, gate_col, stream)
-  switch (tile_height(T_cap, n_cols, K, splits)) {
+  switch (tile_height(T_cap, n_tiles, splits)) {
     case 1: MB_TILE(1); break;
     case 2: MB_TILE(2); break;
     case 3: MB_TILE(3); break;
@@ -631,7 +719,7 @@ static void launch_plain(const void* x, const void* wt, int T_cap, const int32_t
                          hipStream_t stream) {
   const int64_t narrow = (int64_t)((T_cap + 63) / 64) * (n_out / 64);
   const double cost = (double)((narrow + kComputeUnits - 1) / kComputeUnits) * (0.23 * (n_in / kBK) + 1.5);
-  if (cost < gemm_cost(T_cap, n_out, n_in, tile_height(T_cap, n_out, n_in, 1), 1)) {
+  if (cost < gemm_cost(T_cap, n_out, n_in, 1)) {
     launch_gemm_tile<kPlain, 1, 2, 1, 8>(x, wt, n_in, n_out, 1, 0, n_out, T_cap, meta, y, n_out, nullptr, 0, stream);
     return;
   }
@@ -742,7 +830,7 @@ mb_status launch_geglu_bwd(const void* dy, const void* x, const void* w1v, const
     double least = 1e300;
     for (int s = 1; s <= 8; s *= 2) {   // (2 inter / 64 is a multiple of 8)
       if ((size_t)s * T_cap > (size_t)kWgradSplits * 2 * inter) break;
-      const double cost = gemm_cost(T_cap, hidden, 2 * inter, tile_height(T_cap, hidden, 2 * inter, s), s) +
+      const double cost = gemm_cost(T_cap, hidden, 2 * inter, s) +
                           (s > 1 ? 6.0 + 8.0 * s * T_cap * hidden / 4.5e6 : 0.0);   // launch, write and read at 4.5 TB/s
       if (cost < least) {
         least = cost;

@@ -11,7 +11,7 @@ import torch
 
 from oracle import mosaic_oracle as orc
 from paper_2312_17482_amd import workloads as wl
-from tests.helpers import err_stats
+from tests.helpers import err_stats, replay_us
 
 pytestmark = pytest.mark.gpu
 
@@ -133,6 +133,39 @@ def test_linear_every_tile_height_and_several_tiles_per_workgroup(mb, T, T_cap, 
     ref = x[:T].float() @ wt.float().T
     assert torch.all(y[T:] == 7.0)
     assert torch.all((y[:T].float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4)
+
+
+@pytest.mark.parametrize("n_in,n_out", [(128, 2304), (384, 768), (128, 1344)])
+def test_linear_device_side_row_count_takes_every_tile_height(mb, n_in, n_out):
+    """One capacity, row counts from none to all of it: the tile height follows the count (64 to 320 tokens), whose ends
+    lie on both sides of a stretch of the table that it is looked up in.  Bounds as above."""
+    T_cap = 16000
+    print("linear row counts n_in=%d n_out=%d" % (n_in, n_out), flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n_out)
+    x = torch.randn((T_cap, n_in), generator=gen, device="cuda").bfloat16()
+    wt = (torch.randn((n_out, n_in), generator=gen, device="cuda") * 0.02).bfloat16()
+    ref = x.float() @ wt.float().T
+    for T in (0, 1, 64, 256, 257, 1000, 1024, 1025, 2300, 3328, 3329, 4700, 7000, 9000, 12000, 15872, 15873, 16000):
+        xx = x.clone()
+        xx[T:] = float("nan")
+        y = torch.full((T_cap + 3, n_out), 7.0, dtype=torch.bfloat16, device="cuda")
+        meta = torch.tensor([T, 0], dtype=torch.int32, device="cuda")
+        mb.mb_linear_fwd(xx, wt, T_cap=T_cap, meta=meta, y=y[:T_cap])
+        assert torch.all(y[T:] == 7.0), T
+        assert torch.all((y[:T].float() - ref[:T]).abs() <= 2.0 ** -8 * ref[:T].abs() + 1e-4), T
+
+
+@pytest.mark.parametrize("T,n_in,n_out", [(945, 768, 2304), (16384, 3072, 768), (4096, 768, 2304)])
+def test_device_side_row_count_costs_what_the_rows_cost(mb, T, n_in, n_out):
+    """The rows of a nearly empty buffer take about as long as the same rows given exactly: a quarter more and 2 us."""
+    x = torch.randn((32768, n_in), device="cuda").bfloat16()
+    wt = (torch.randn((n_out, n_in), device="cuda") * 0.02).bfloat16()
+    y = torch.empty((32768, n_out), dtype=torch.bfloat16, device="cuda")
+    meta = torch.tensor([T, 0], dtype=torch.int32, device="cuda")
+    exact = replay_us(lambda: mb.mb_linear_fwd(x[:T], wt, y=y))
+    counted = replay_us(lambda: mb.mb_linear_fwd(x, wt, meta=meta, y=y))
+    print("linear T=%d %d->%d: exact %.1f us, counted %.1f us" % (T, n_in, n_out, exact, counted), flush=True)
+    assert counted <= 1.25 * exact + 2
 
 
 def test_gelu_gate_parity_and_unfused_arrangements(mb):
