@@ -271,3 +271,54 @@ def test_geglu_backward_device_side_row_count_and_empty(mb):
     _, dw1v0, dw20 = mb.mb_geglu_bwd(dyd, xd, wd, w2d, act, meta=meta0, dx=dx0)
     torch.cuda.synchronize()
     assert torch.all(dx0 == 9.0) and torch.all(dw1v0 == 0) and torch.all(dw20 == 0)
+
+
+def backward_in_64_bits(x, w1v, w2, dy, act):
+    """dx, d(W1 | V)^T, dW2^T by the textbook derivative in float64 on the device, from the bf16 operands of the call."""
+    x, w1v, w2, dy, act = (t.double() for t in (x, w1v, w2, dy, act))
+    inter = w2.shape[1]
+    h, g = x @ w1v[:inter].T, x @ w1v[inter:].T
+    phi = 0.5 * torch.erfc(-h * 0.5 ** 0.5)
+    da = dy @ w2
+    dhg = torch.cat((da * g * (phi + h * torch.exp(-0.5 * h * h) * (2.0 * np.pi) ** -0.5), da * h * phi), 1)
+    return dhg @ w1v, dhg.T @ x, dy.T @ act
+
+
+# (T, hidden, inter): the gate backward's tiles are 128, 192, 256, 320 tokens high and more than there are compute units,
+# so a workgroup goes from one tile to the next; weight gradients in 7, 7, 7, 7, 5, 2 splits; the partial tiles lie over
+# h | g (T > 14 hidden).  The last is the benchmark's feed-forward.
+@pytest.mark.parametrize("T,hidden,inter", [(7000, 256, 1024), (8100, 256, 3072), (12000, 256, 2048), (13001, 256, 2048),
+                                            (17003, 256, 2048), (9000, 512, 2048), (26963, 768, 3072)])
+@pytest.mark.parametrize("counted", [False, True])
+def test_geglu_backward_of_many_tiles(mb, T, hidden, inter, counted):
+    """The backward where a workgroup has several tiles and the partial tiles reuse the place of h | g, with the row count
+    given exactly and on the device (rows beyond it hold NaN and are not to be touched).  Bounds as above; dW2 in
+    addition against 64 bits on its own operands: fp32 sums of products of bf16 values, in one chain of at most T / 16
+    additions, each 2^-24 of what has been added up: for terms of either sign 2^-24 sqrt(T / 32) at most, 1.8e-6."""
+    print("geglu backward T=%d hidden=%d inter=%d counted=%s" % (T, hidden, inter, counted), flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    rows = T + 700 if counted else T
+
+    def normal(*shape, std=1.0):
+        return (torch.randn(shape, generator=gen, device="cuda") * std).bfloat16()
+    x, w1v, w2, dy = normal(rows, hidden), normal(2 * inter, hidden, std=0.03), normal(hidden, inter, std=0.03), normal(rows, hidden)
+    x[T:], dy[T:] = float("nan"), float("nan")
+    meta = torch.tensor([T, 0], dtype=torch.int32, device="cuda") if counted else None
+    act = torch.full((rows, inter), float("nan"), dtype=torch.bfloat16, device="cuda")
+    mb.mb_geglu_fwd(x, w1v, w2, meta=meta, act=act)
+    hg = mb.mb_linear_fwd(x, w1v, meta=meta, y=torch.full((rows, 2 * inter), float("nan"), dtype=torch.bfloat16, device="cuda"))
+    ref = backward_in_64_bits(x[:T], w1v, w2, dy[:T], act[:T])
+    first = None
+    for given in (None, None, hg):   # twice recomputed, once with the stored projections: the same bits
+        dx = torch.full((rows + 2, hidden), 9.0, dtype=torch.bfloat16, device="cuda")
+        _, dw1v, dw2 = mb.mb_geglu_bwd(dy, x, w1v, w2, act, hg=given, meta=meta, dx=dx[:rows])
+        assert torch.all(dx[T:] == 9.0)
+        got = (dx[:T].clone(), dw1v, dw2)
+        first = first or got
+        assert all(torch.equal(a, b) for a, b in zip(got, first))
+    for name, a, b in zip(("dx", "dw1v", "dw2"), first, ref):
+        err = (a.double() - b).abs().max().item() / b.abs().max().item()
+        rel = ((a.double() - b).norm() / b.norm()).item()
+        print("  %s rel_fro %.2e max %.2e" % (name, rel, err), flush=True)
+        assert rel <= 1e-2 and err <= 2.0 ** -6, name
+    assert ((dw2.double() - ref[2]).norm() / ref[2].norm()).item() <= 2.0 ** -24 * (T / 32) ** 0.5
