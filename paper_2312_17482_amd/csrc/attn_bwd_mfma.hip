@@ -955,9 +955,10 @@ mb_status launch_attn_bwd_mfma(const AttnShape& s, const void* dout, const void*
     int64_t widest = 0;
     for (const int64_t st : {dos, qs, ks, vs, os, dqs, dks, dvs}) widest = st > widest ? st : widest;
     const bool narrow = (int64_t)kTile * widest * 2 < ((int64_t)1 << 31);
-    // Up to 512 units all fit the chip at once, two workgroups per compute unit: then a second unit per workgroup only makes
-    // the chain longer (8 x 128 positions, 96 units: 16.7 us with two, 10.4 us with one).
-    if (units <= 512) {
+    // Up to two units per compute unit all fit the chip at once, a workgroup each: then a second unit per workgroup only
+    // makes the chain longer (128 positions, two and one, replayed: 96 units 15.0 and 8.8 us, 252 units 16.8 and 10.7, 384
+    // units 18.1 and 14.8, 512 units 18.9 and 16.1).  From 516 on two are taken: 20.7 us.
+    if (units <= 2 * kComputeUnits) {
       if (!narrow) MB_LAUNCH_FUSED(kRowsPerLane, 1);
       else if (s.token_rows) MB_LAUNCH_FUSED(kRowsMaybeContiguous, 1);
       else MB_LAUNCH_FUSED(kRowsIdentity, 1);

@@ -16,6 +16,10 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 inline size_t elem_size(mb_dtype dt) { return dt == MB_F32 ? 4 : 2; }
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Compute units of the MI355X this library is built for: what the rules for grids and splits count on.  (Results do not
+// depend on it.)
+static constexpr int kComputeUnits = 256;
+
 struct AttnShape {
   int B, T, max_seqlen, H, D;
   const int32_t* cu_seqlens;

@@ -32,7 +32,6 @@ namespace mb {
 namespace {
 
 constexpr int kBK = 64;                               // k per stage
-constexpr int kComputeUnits = 256;
 constexpr int kGroupM = 4;                            // token panels walked together (L2 reuse of the weight tiles)
 
 // GeLU(h) = h * Phi(h), the exact (error-function) form, with Phi evaluated by the classic five-term
