@@ -277,9 +277,9 @@ def main():
     # ([T,H,D] elements) plus the row log-sum-exp read ([H,T] float)
     bwd_bytes = 8 * T_host * H * D * esize + 4 * H * T_host
     if bf16 and D == 64:
-        bwd_kernel = "attn_bwd_fused128_kernel" if L <= 128 else "attn_bwd_dkv_kernel + attn_bwd_dq_kernel + attn_bwd_delta_kernel"
+        bwd_kernel = "attn_bwd_fused128_kernel" if L <= 128 else "attn_bwd_dq_kernel + attn_bwd_dkv_kernel"
     else:
-        bwd_kernel = "bwd_generic_row_kernel + bwd_generic_col_kernel"
+        bwd_kernel = "bwd_f32_dq_kernel + bwd_f32_dkv_kernel"
     roof_hbm = {
         "kernel": bwd_kernel, "bound": "hbm",
         "achieved": round(bwd_bytes / (bwd_ms * 1e-3) * 1e-9, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",

@@ -4,7 +4,7 @@
 // Two launches of one tiled GEMM kernel, both of the form  out[t, n] = sum_k X[t, k] * Wt[n, k]
 // (token rows and weight rows are both contiguous along k, the storage of a linear layer):
 //   1. gated:  the weight is the fused [2*inter, hidden] matrix of the appendix on GLU implementations
-//      (rows 0..inter-1 = W1^T, rows inter.. = V^T).  A workgroup computes, for 256 tokens, 128 columns
+//      (rows 0..inter-1 = W1^T, rows inter.. = V^T).  A tile is, for its 64 to 320 tokens, 128 columns
 //      of x W1 and THE SAME 128 columns of x V, so the slice and the product GeLU(.) (*) (.) happen on
 //      the accumulators: neither projection is ever written to memory.
 //   2. plain:  y = a W2 with the [hidden, inter] matrix W2^T.
@@ -497,8 +497,8 @@ __global__ __launch_bounds__(256) void gelu_gate_kernel(const uint16_t* __restri
 // units better together); the tokens are split over `splits` workgroups per tile, and a second kernel adds the partial
 // tiles in a fixed order, so the result is deterministic.
 // Bound like the projections by the loads into LDS and the power limit.  At 26963 tokens, 768 x 3072 (381 GFLOP, two
-// splits) 366 us and 13 us for adding up, where two launches of seven splits each, staged through registers, took 425 and
-// 41 us; at 945 tokens (one split, no adding up) 25 us instead of 66 and 33.
+// splits) 405 us and 13 us for adding up, where two launches of seven splits each, staged through registers, took 430 and
+// 40 us (means of 20 passes in one run); at 945 tokens (one split, no adding up) 31 us instead of 66 and 34.
 constexpr int kWgRows = 64;                         // tokens per k step
 constexpr int kWgStage = 2 * kWgRows * 256;         // elements: P rows, then Q rows
 
@@ -779,6 +779,9 @@ static void launch_wgrad(const void* dy, const void* act, const void* dhg, const
   // The split with the least estimated time: rounds over the compute units (about 1.5 us a step of 64 tokens and 6 us
   // before and after), and the partial tiles' way through memory at 4.5 TB/s.  (The whole backward at 26963 tokens with
   // 1, 2, 3, 4 splits: 1354, 1165, 1239, 1185 us; at 945 tokens 92, 105, 116, 121 us.)
+  // Fewer splits are longer chains of fp32 additions, T / (16 splits) of them: against 64 bits on its own bf16 operands dW2
+  // is off by 1.8e-7 (945 tokens, one split) and 7.4e-7 (26963, two) where seven splits gave 0.9e-7 and 3.9e-7.  Both are a
+  // thousandth and less of the 2^-9 that the operands were rounded by.
   const int tiles_a = hidden / 256 * (inter / 256), tiles = 3 * tiles_a, steps = (T_cap + kWgRows - 1) / kWgRows;
   int splits = 1;
   double least = 1e300;
