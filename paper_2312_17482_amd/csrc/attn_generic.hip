@@ -679,6 +679,7 @@ int longest_of(const AttnShape& s) { return s.max_seqlen < s.T ? s.max_seqlen : 
 bool per_token(const AttnShape& s, mb_dtype dt) {
   const int n = longest_of(s);
   const int64_t waves = (int64_t)s.T * s.H;
+  if (s.T > (1 << 25)) return false;   // a launch holds fewer than 2^32 threads per dimension: T waves of 64
   const bool wide_bf16 = dt == MB_BF16 && s.D > 64;   // where the tile kernels have one workgroup per compute unit
   if (n <= 4) return true;
   if (n > kTokenMax || s.D <= 16) return false;

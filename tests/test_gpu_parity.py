@@ -239,9 +239,30 @@ def test_generic_time_of_very_short_sequences(mb, bf16, D):
     assert one <= 2.5 * sixteen
 
 
-def test_generic_token_rows_with_holes_and_more_sequences_than_blocks(mb):
+def test_generic_short_sequences_in_a_capacity_beyond_one_launch(mb):
+    """A capacity T of which a wave per token would be more threads than one launch takes (2^32): the call is served all
+    the same, and gives what the exact T gives."""
+    H, D, T = 1, 16, (1 << 26) + 64
+    lengths = [4, 1, 0, 3, 2, 4]
+    cu = torch.tensor([0] + list(np.cumsum(lengths)), dtype=torch.int32, device="cuda")
+    n = sum(lengths)
+    qkv, do = torch.randn((n, 3, H, D), device="cuda"), torch.randn((n, H, D), device="cuda")
+    q, k, v = (qkv[:, i] for i in range(3))
+    slopes = mb.mb_alibi_slopes(H).cuda()
+    o, lse = mb.mb_alibi_attn_fwd(q, k, v, cu, 4, slopes, 0.25)
+    grads = mb.mb_alibi_attn_bwd(do, q, k, v, o, lse, cu, 4, slopes, 0.25)
+    big = torch.full((H, T), 7.0, device="cuda")
+    o2, _ = mb.mb_alibi_attn_fwd(q, k, v, cu, 4, slopes, 0.25, lse=big, T=T)
+    grads2 = mb.mb_alibi_attn_bwd(do, q, k, v, o2, big, cu, 4, slopes, 0.25, T=T)
+    assert torch.all(big[:, n:] == 7.0) and (big[:, :n] - lse).abs().max() <= 1e-5
+    for a, b in zip((o, *grads), (o2, *grads2)):   # (two kernels with fp32 arithmetic: F32_TOL)
+        assert (a - b).abs().max() <= F32_TOL[0] and (a - b).norm() <= F32_TOL[1] * a.norm()
+
+
+@pytest.mark.parametrize("L", [24, 4])
+def test_generic_token_rows_with_holes_and_more_sequences_than_blocks(mb, L):
     """Rows looked up per token, a capacity T, and a batch of mostly empty sequences (more work slots than tokens)."""
-    B, L, H, D = 400, 24, 3, 20
+    B, H, D = 400, 3, 20
     mask = wl.random_mask(24, B, L, 0.5)
     mask[np.random.default_rng(5).random(B) < 0.7] = 0
     rng = np.random.default_rng(25)
