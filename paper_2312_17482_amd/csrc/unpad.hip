@@ -103,16 +103,13 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(const int32_t* __rest
   compact_row(mask + (size_t)b * L, L, b * L, prefix, indices, wave_count);
 }
 
-// Index maps of a small batch in one launch: every row's block counts the mask in front of its row itself instead of
-// waiting for a launch that counts each row, and block 0 finds the longest row, a wave per row.  That wave is the
-// longest chain: a load per 64 entries of each of its rows, and the sum over its lanes, which takes as long as two loads.
-// Up to 20 such steps one launch is the faster (replayed, two launches and one: 8 x 128 4.9 and 3.6 us, 16 x 128 4.9 and
-// 4.4, 1 x 1024 5.6 and 5.3, 4 x 1024 5.9 and 5.3, 8 x 512 5.4 and 5.1); from 24 on it is the slower (16 x 256 4.9 and
-// 5.3, 32 x 64 5.0 and 5.3, 64 x 16 5.0 and 8.1, 64 x 128 5.0 and 9.9, 1 x 8192 16 and 26).
-constexpr int kSmallSteps = 20;
-static bool index_in_one_launch(int B, int L) {
-  return (int64_t)((B + kWaves - 1) / kWaves) * (((int64_t)L + 63) / 64 + 2) <= kSmallSteps;
-}
+// Index maps of a small batch in one launch (at most kSmallRows rows and kSmallMask mask entries): every row's block counts
+// the mask in front of its row itself instead of waiting for a launch that counts each row, and block 0, which has nothing
+// in front of it, finds the longest row meanwhile, an equal share of its threads per row.  Replayed, two launches and one:
+// 8 x 128 4.9 and 3.5 us, 32 x 128 5.0 and 3.6, 64 x 64 5.0 and 3.7, 64 x 128 5.0 and 4.1, 8 x 1024 5.9 and 4.7, 1 x 8192 16.0 and 13.0.
+// (With a wave of block 0 per row, one row after the other, 64 x 128 took 9.9 us.)  Beyond, the repeated counting costs
+// what the second launch does.
+constexpr int kSmallRows = 64, kSmallMask = 8192;
 __global__ __launch_bounds__(kThreads) void index_small_kernel(const int32_t* __restrict__ mask, int B, int L,
                                                                int32_t* __restrict__ seqlens,
                                                                int32_t* __restrict__ cu_seqlens,
@@ -126,13 +123,20 @@ __global__ __launch_bounds__(kThreads) void index_small_kernel(const int32_t* __
   for (int i = tid; i < b * L; i += kThreads) part += mask[i] != 0;
   const int prefix = block_reduce<false>(part, lds);
   if (b == 0) {
-    int longest = 0;
-    for (int r = tid >> 6; r < B; r += kWaves) {
-      int n = 0;
-      for (int l = tid & 63; l < L; l += 64) n += mask[r * L + l] != 0;
-      longest = max(longest, wave_sum(n));
+    __shared__ int count[kSmallRows];
+    int per = kThreads;   // threads per row, a power of two
+    while (per * B > kThreads) per >>= 1;
+    if (tid < kSmallRows) count[tid] = 0;
+    __syncthreads();
+    const int r = tid / per;
+    int n = 0;
+    if (r < B) {
+#pragma unroll 8
+      for (int l = tid % per; l < L; l += per) n += mask[r * L + l] != 0;
+      atomicAdd(&count[r], n);
     }
-    longest = block_reduce<true>(longest, lds);
+    __syncthreads();
+    const int longest = block_reduce<true>(tid < B ? count[tid] : 0, lds);
     if (tid == 0) meta[1] = longest;
   }
   const int end = compact_row(mask + b * L, L, b * L, prefix, indices, wave_count);
@@ -283,7 +287,7 @@ __global__ __launch_bounds__(kThreads) void zero_padding_kernel(const int32_t* _
 
 mb_status launch_unpad_index(const int32_t* mask, int B, int L, int32_t* seqlens, int32_t* cu_seqlens,
                              int32_t* indices, int32_t* meta, hipStream_t stream) {
-  if (B > 0 && index_in_one_launch(B, L)) {
+  if (B > 0 && B <= kSmallRows && (int64_t)B * L <= kSmallMask) {
     hipLaunchKernelGGL(index_small_kernel, dim3(B), dim3(kThreads), 0, stream, mask, B, L, seqlens, cu_seqlens, indices,
                        meta);
     return check_launch("index_small_kernel");
