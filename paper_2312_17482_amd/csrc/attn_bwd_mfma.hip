@@ -18,8 +18,11 @@
 // Masking costs nothing: rows beyond the sequence end are staged as zeros and their lse as +inf
 // (P = 0); zero K/V rows make the products with out-of-range keys vanish.
 #include "attn_plan.h"
+#include "attn_stage.h"
 #include "common.h"
 #include "mfma_util.h"
+
+#include <type_traits>
 
 namespace mb {
 namespace {
@@ -29,16 +32,26 @@ constexpr int kTile = 128;
 constexpr int kPitch = 72;   // LDS row pitch in bf16 (144 B)
 
 // ------------------------------------------------------------------------------------------------ any length
-// Both kernels below stream their second operand in tiles of 64 rows through two LDS buffers: while
-// one tile is consumed the next travels HBM -> registers -> the other buffer (one barrier per tile).
+// Both kernels below stream their second operand in tiles of 64 rows.  dQ: through two LDS buffers; while one tile is
+// consumed the next travels HBM -> registers -> the other buffer (one barrier per tile).  dK/dV: see there.
 // Global memory is touched only as full 128-byte rows of one head; fragments and output rows pass
 // through LDS.  Which workgroup does what is read from the work plan (attn_plan.h).
 constexpr int kTileS = 64;                          // rows of a streamed tile
 constexpr int kHalf = kTileS * kPitch;              // elements of one streamed operand tile (4608)
 constexpr int kBuf = 2 * kHalf;                     // one buffer: two operand tiles (= 128 rows of pitch 72)
+constexpr int kRing = 4;                            // regions that the tiles of dK/dV go through
+constexpr int kRegion = 2 * kTileS * kD;            // elements of a region: two operand tiles as attn_stage.h stages them
 
 // ------------------------------------------------------------------------------------------------ dK, dV
 // One workgroup per (sequence, head, 128 keys); wave w owns keys 32w.. and streams all queries.
+// What bounds it: a wave issues an instruction every 5 cycles at best, and with 236 registers a SIMD holds two waves, so
+// what counts is how few instructions and waits stand between the matrix instructions.  Hence tiles that go straight to LDS,
+// three steps ahead, in a layout without bank conflicts (conflicts were a fifth of all LDS cycles), one barrier per 64
+// queries, and the exponentials of one block written among the matrix instructions of the blocks before and behind it
+// (two waves together take 1240 cycles for 32 matrix instructions of 32 cycles).  16 sequences of 2048 tokens, 16 heads:
+// 620 -> 519 us (550 GFLOP); 64 of 64 .. 512 tokens, 12 heads: 90 -> 77 us; 64 of 512 with a key mask: 158 -> 130 us.
+// Of the 519 us the loads cost 30, the tables of lse and Delta 15, the vector instructions 60 (each left out in turn).
+// Tried: four steps unrolled so that every LDS address is a constant (1100 registers spilled).
 //
 // kMode (both kernels; see kRowsIdentity .. in common.h): for a sequence whose tokens sit in consecutive
 // rows of the activation buffers, spanning fewer than 2^31 bytes, the rows of a streamed tile are fetched
@@ -56,10 +69,12 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
     float scale, uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int64_t dks, int64_t dvs, int T,
     const int32_t* __restrict__ token_rows, const int32_t* __restrict__ plan, int64_t plan_cap) {
   const int32_t* rows = kMode == kRowsIdentity ? nullptr : token_rows;
-  __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kBuf];   // per buffer: Q tile, dO tile
-  __shared__ __attribute__((aligned(16))) float sL[2][3][kTileS];    // -lse / scale (-inf past the end): alone, with the
-                                                                     // row's bias left and right of the diagonal
-  __shared__ __attribute__((aligned(16))) float sD[2][kTileS];       // -Delta
+  // regions of a Q and a dO tile each; at the start the last two carry this workgroup's K and V rows
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kRing * kRegion];
+  __shared__ __attribute__((aligned(16))) float sRaw[3][kRing][kTileS];  // lse and Delta as they come, by tile; unused
+  __shared__ __attribute__((aligned(16))) float sL[kRing][3][kTileS];    // -lse / scale (-inf past the end): alone, with the
+                                                                         // row's bias left and right of the diagonal
+  __shared__ __attribute__((aligned(16))) float sD[kRing][kTileS];       // -Delta
 
   int start, n, nk, ktile, h;   // nk <= n: the sequence's first nk tokens are its keys
   if (!plan_fetch(plan, plan_cap, &start, &n, &nk, &ktile, &h)) return;   // this XCD's list is shorter
@@ -87,185 +102,283 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
   const int kj = kw + c;                      // this lane's key
   const int kblk = (kv0 >> 5) + wave;         // index of this wave's block of 32 keys
   const int ntiles = (n + kTileS - 1) / kTileS;
-  const int st_row = tid >> 3, st_col = (tid & 7) * 8;
   const float cs = scale * kLog2e;
   const float k1 = slopes[h] / scale, inv_scale = 1.f / scale;
 
-  // ---- K, V rows of this workgroup's 128 keys (coalesced) -> LDS -> K^T, V^T fragments
-  bf16x8 bk[4], bv[4];
+  // ---- loads: this wave's K and V rows, then its share of the Q / dO tiles
+  const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t*)smem);
   {
-    u32x4 tk[4], tv[4];
+    const u32x4 k_rsrc = stage_rsrc(k + row0 * ks + h * kD, ks, nk), v_rsrc = stage_rsrc(v + row0 * vs + h * kD, vs, nk);
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      tk[it] = tv[it] = u32x4{0u, 0u, 0u, 0u};
-      const int j = kv0 + 32 * it + st_row;
-      if (j < nk) {
-        const int64_t gr = tok_row(rows, start + j);
-        tk[it] = *reinterpret_cast<const u32x4*>(k + gr * ks + h * kD + st_col);
-        tv[it] = *reinterpret_cast<const u32x4*>(v + gr * vs + h * kD + st_col);
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t at = lds0 + (2 * kRegion + (32 * wave + 8 * j) * kD) * 2;
+      if (contig) {
+        const uint32_t row = kw + 8 * j;
+        stage_rows(at, stage_lane_off(lane, j & 1, ks) + row * (uint32_t)ks * 2u, k_rsrc);
+        stage_rows(at + kRegion * 2, stage_lane_off(lane, j & 1, vs) + row * (uint32_t)vs * 2u, v_rsrc);
+      } else {
+        stage_each(at, stage_address(k + h * kD, ks, rows, start, kw + 8 * j, nk, lane, j & 1));
+        stage_each(at + kRegion * 2, stage_address(v + h * kD, vs, rows, start, kw + 8 * j, nk, lane, j & 1));
       }
     }
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      *reinterpret_cast<u32x4*>(&smem[(32 * it + st_row) * kPitch + st_col]) = tk[it];
-      *reinterpret_cast<u32x4*>(&smem[kBuf + (32 * it + st_row) * kPitch + st_col]) = tv[it];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      bk[s] = lds_read8(&smem[(32 * wave + c) * kPitch + 16 * s + 8 * g]);
-      bv[s] = lds_read8(&smem[kBuf + (32 * wave + c) * kPitch + 16 * s + 8 * g]);
-    }
-    __syncthreads();
   }
-
-  // ---- streamed Q / dO tiles
-  const uint16_t* qh = q + h * kD + st_col;
-  const uint16_t* gh = dout + h * kD + st_col;
-  u32x4 tq[2], tg[2];
-  float tl = 0.f, td = 0.f;
-  const uint32_t qoff = ((uint32_t)st_row * (uint32_t)qs + (uint32_t)(h * kD + st_col)) * 2u;
-  const uint32_t goff = ((uint32_t)st_row * (uint32_t)dos + (uint32_t)(h * kD + st_col)) * 2u;
-  auto issue_tile = [&](int i0) {
+  const u32x4 q_rsrc = stage_rsrc(q + row0 * qs + h * kD, qs, n), g_rsrc = stage_rsrc(dout + row0 * dos + h * kD, dos, n);
+  // the wave's first 8 rows of the tile to load next; its second 8 rows lie 32 behind them
+  uint32_t q_off = stage_lane_off(lane, wave & 1, qs) + 8u * wave * (uint32_t)qs * 2u;
+  uint32_t g_off = stage_lane_off(lane, wave & 1, dos) + 8u * wave * (uint32_t)dos * 2u;
+  // The j-th of the wave's four loads of tile t into `region`; the tiles are taken in order.
+  auto issue_row = [&](int t, int region, int j) {
+    const int i = j >> 1;
+    const bool is_q = (j & 1) == 0;
+    const uint32_t at = lds0 + (uint32_t)(region * kRegion + (is_q ? 0 : kTileS * kD) + 8 * (wave + 4 * i) * kD) * 2;
+    uint32_t& off = is_q ? q_off : g_off;
+    const int64_t stride = is_q ? qs : dos;
     if (contig) {
-      const int left = n - i0;      // > 0: rows i0 .. n-1 exist
-      const __amdgpu_buffer_rsrc_t qr = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<uint16_t*>(q) + (int64_t)(row0 + i0) * qs, 0, left * (int)qs * 2, kRsrcFlags);
-      const __amdgpu_buffer_rsrc_t gr = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<uint16_t*>(dout) + (int64_t)(row0 + i0) * dos, 0, left * (int)dos * 2, kRsrcFlags);
-#pragma unroll
-      for (int it = 0; it < 2; ++it) {
-        tq[it] = __builtin_amdgcn_raw_buffer_load_b128(qr, qoff + (uint32_t)it * 64u * (uint32_t)qs, 0, 0);
-        tg[it] = __builtin_amdgcn_raw_buffer_load_b128(gr, goff + (uint32_t)it * 64u * (uint32_t)dos, 0, 0);
-      }
+      stage_rows(at, off, is_q ? q_rsrc : g_rsrc);
+      off += 64u * (uint32_t)stride;
     } else {
+      stage_each(at, stage_address((is_q ? q : dout) + h * kD, stride, rows, start, t * kTileS + 8 * (wave + 4 * i), n,
+                                         lane, wave & 1));
+    }
+  };
+  constexpr int kRowLoads = 4;   // loads per wave and tile
+  auto issue_rows = [&](int t, int region) {
 #pragma unroll
-      for (int it = 0; it < 2; ++it) {
-        tq[it] = tg[it] = u32x4{0u, 0u, 0u, 0u};
-        const int i = i0 + 32 * it + st_row;
-        if (i < n) {
-          const int64_t gr = tok_row(rows, start + i);
-          tq[it] = *reinterpret_cast<const u32x4*>(qh + gr * qs);
-          tg[it] = *reinterpret_cast<const u32x4*>(gh + gr * dos);
-        }
+    for (int j = 0; j < kRowLoads; ++j) issue_row(t, region, j);
+  };
+  // lse and Delta of a tile: the first wave brings one and the second the other (the other waves' loads, which keep the
+  // number of loads the same, read nothing).
+  const u32x4 raw_rsrc = stage_rsrc_bytes((wave == 0 ? lse : delta) + ((int64_t)h * T + start), wave < 2 ? (uint32_t)n * 4u : 0u);
+  const uint32_t raw0_at = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) float*)&sRaw[0][0][0]) +
+                           min(wave, 2) * (kRing * kTileS * 4);
+  auto issue_raw = [&](int t, int region) {   // of tile t
+    const uint32_t at = raw0_at + region * (kTileS * 4);
+    stage_words(at, (uint32_t)(t * kTileS + lane) * 4u, raw_rsrc);
+  };
+  auto store_tables = [&](int t, int to, float raw) {   // of tile t; `raw`: this lane's lse or Delta
+    if (wave == 0) {
+      const float l = t * kTileS + lane < n ? -raw * inv_scale : -INFINITY;
+      sL[to][0][lane] = l;
+      sL[to][1][lane] = fmaf((float)lane, k1, l);
+      sL[to][2][lane] = fmaf((float)lane, -k1, l);
+    } else if (wave == 1) {
+      sD[to][lane] = t * kTileS + lane < n ? -raw : 0.f;
+    }
+  };
+  auto first_raw = [&](int t) {
+    const int i = min(t * kTileS + lane, n - 1);
+    return (wave == 0 ? lse : delta)[(int64_t)h * T + start + i];
+  };
+  issue_rows(0, 0);
+  issue_raw(2, 2);
+  issue_raw(3, 3);
+  const float raw0 = first_raw(0), raw1 = first_raw(1);
+  issue_rows(1, 1);
+  store_tables(0, 0, raw0);
+  store_tables(1, 1, raw1);
+
+  // ---- fragment addresses (bytes): rows for S and dP, transposed patches for dV and dK
+  uint32_t row_at[4], tr_at[2][2];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) row_at[s] = (uint32_t)(c * kD + ((2 * s + g) ^ stage_swizzle(c)) * 8) * 2;
+  {
+    const int tr_i = lane & 15, tr_q = lane >> 4;
+    const int tr_row = (tr_i >> 2) + 4 * (tr_q >> 1), tr_piece = 2 * (tr_q & 1) + ((tr_i & 3) >> 1);
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        const int r = tr_row + 8 * half;
+        tr_at[db][half] = (uint32_t)(r * kD + ((4 * db + tr_piece) ^ stage_swizzle(r)) * 8 + 4 * (tr_i & 1)) * 2;
       }
-    }
-    if (tid < kTileS) {
-      const bool ok = i0 + tid < n;
-      tl = ok ? -lse[(int64_t)h * T + start + i0 + tid] * inv_scale : -INFINITY;
-      td = ok ? -delta[(int64_t)h * T + start + i0 + tid] : 0.f;
-    }
-  };
-  auto store_tile = [&](int buf) {
-    uint16_t* bq_ = smem + buf * kBuf;
+  }
+  const char* const lds = reinterpret_cast<const char*>(smem);
+  // the wave's K^T, V^T fragments (B operands): lane = key column, 8 consecutive d per k-step
+  bf16x8 bk[4], bv[4];
+  staged_barrier<0>();
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      *reinterpret_cast<u32x4*>(&bq_[(32 * it + st_row) * kPitch + st_col]) = tq[it];
-      *reinterpret_cast<u32x4*>(&bq_[kHalf + (32 * it + st_row) * kPitch + st_col]) = tg[it];
-    }
-    if (tid < kTileS) {
-      sL[buf][0][tid] = tl;
-      sL[buf][1][tid] = fmaf((float)tid, k1, tl);
-      sL[buf][2][tid] = fmaf((float)tid, -k1, tl);
-      sD[buf][tid] = td;
-    }
-  };
+  for (int s = 0; s < 4; ++s) {
+    bk[s] = lds_read8(reinterpret_cast<const uint16_t*>(lds + row_at[s] + (2 * kRegion + 32 * wave * kD) * 2));
+    bv[s] = lds_read8(reinterpret_cast<const uint16_t*>(lds + row_at[s] + (3 * kRegion + 32 * wave * kD) * 2));
+  }
 
   f32x16 dkacc[2], dvacc[2];   // dK^T, dV^T: d along accumulator rows (two blocks of 32), keys along lanes
 #pragma unroll
   for (int i = 0; i < 16; ++i) { dkacc[0][i] = dkacc[1][i] = dvacc[0][i] = dvacc[1][i] = 0.f; }
-  const int tr_i = lane & 15, tr_q = lane >> 4;
-  const int tr_row = (tr_i >> 2) + 4 * (tr_q >> 1);
-  const int tr_col = 16 * (tr_q & 1) + 4 * (tr_i & 3);
-  float fj = (float)(kj - 4 * g);   // i - j = ci - fj with ci = i0 + 32ib + 8*(v/4) + v%4
-  asm volatile("" : "+v"(fj));
 
-  // The two blocks of 32 queries of a staged tile (rows 32ib..) against this wave's keys.  The S accumulator
-  // starts from -lse_i / scale plus the bias and the dP accumulator from -Delta_i, so that after the products
-  // P = exp2(acc_S * c) and dS = P * acc_dP.  Off the diagonal block |i-j| is linear in i and j: the query's part of the
-  // bias comes out of LDS together with lse_i (one of two tables, for either side), the key's part is the exponent's
-  // constant; no instruction per score is spent on either.  Rows past the sequence end are staged as zeros
-  // with lse = +inf, which makes their P and dS exact zeros: no branch around the accumulating code.
-  // Only the start values have variants (diagonal block or not); everything after it is one straight
-  // run of instructions for both blocks, so that the exponentials of one block can be issued between
-  // the matrix instructions of the other.
-  auto qtile = [&](const uint16_t* sQ, const uint16_t* sG, const float (*pl)[kTileS], const float* pd, int i0) {
-    f32x16 sacc[2], pacc[2];
-    float off[2];
+  // Blocks of 32 queries go through three stages: (1) S and dP, 8 matrix instructions; (2) P = exp2(S c + off) and
+  // dS = P dP on the vector unit; (3) dV += dO^T P and dK += Q^T dS, 8 matrix instructions.  The S accumulator
+  // starts from -lse_i / scale plus the query's part of the bias (off the diagonal block |i-j| is linear in i and j; one of
+  // two tables in LDS, for either side), the key's part is the exponent's constant; the dP accumulator starts from -Delta_i.
+  // Rows past the sequence end are staged as zeros with lse = +inf, which makes their P and dS exact zeros.
+  // A slot runs stage 2 of block b among the matrix instructions of stage 3 of block b - 1 and stage 1 of block b + 1: 16
+  // groups of one matrix instruction, the fragment reads of the matrix instruction four groups later and the vector
+  // instructions of one accumulator register, kept in this order.
+  struct Block {
+    f32x16 s, p;         // S, dP; then P, dS
+  };
+  struct Packed {
+    uint32_t p[8], s[8];   // P and dS as operands
+  };
+  auto operand = [](const uint32_t(&w)[8], int kk) {
+    return as_bf16x8(u32x4{w[4 * kk], w[4 * kk + 1], w[4 * kk + 2], w[4 * kk + 3]});
+  };
+  bf16x8 f[16];   // A operands by group
+  // group -> what its matrix instruction is: stage 3 (0: dV, 1: dK; db; kk) or stage 1 (0: S, 1: dP; k-step)
+  constexpr int kStage3[16] = {1, 1, 1, 1, 0, 0, 1, 0, 0, 1, 0, 0, 0, 0, 1, 1};
+  constexpr int kWhat[16] = {0, 1, 0, 1, 0, 1, 0, 0, 1, 1, 0, 1, 0, 1, 0, 1};
+  constexpr int kDb[16] = {0, 0, 1, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 1, 1};
+  constexpr int kStep[16] = {0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 2, 2, 3, 3, 1, 1};   // kk or k-step
+  struct Places {
+    uint32_t a[4];   // in a region: what the lane reads of Q rows by k-step, or of Q patches by d block and half
+  };
+  auto places_row = [&](uint32_t region_bytes) {
+    return Places{{row_at[0] + region_bytes, row_at[1] + region_bytes, row_at[2] + region_bytes, row_at[3] + region_bytes}};
+  };
+  auto places_tr = [&](uint32_t region_bytes) {
+    return Places{{tr_at[0][0] + region_bytes, tr_at[0][1] + region_bytes, tr_at[1][0] + region_bytes,
+                   tr_at[1][1] + region_bytes}};
+  };
+  auto read_tr = [&](const Places& at, int ib, int what, int db, int kk) {   // dO^T or Q^T of the tile's block ib
+    const uint32_t off = (32 * ib + 16 * kk + (what == 0 ? kTileS : 0)) * kD * 2;
+    return join_tr(lds_read_tr4(reinterpret_cast<const uint16_t*>(lds + at.a[2 * db] + off)),
+                   lds_read_tr4(reinterpret_cast<const uint16_t*>(lds + at.a[2 * db + 1] + off)));
+  };
+  auto read_row = [&](const Places& at, int ib, int what, int s) {
+    return lds_read8(reinterpret_cast<const uint16_t*>(lds + at.a[s] + (32 * ib + (what == 0 ? 0 : kTileS)) * kD * 2));
+  };
+  auto start_row = [&](Block& b, int what, int r, const float* table, const float* dl) {   // start values of S and dP
+    const float4 x = *reinterpret_cast<const float4*>((what == 0 ? table : dl) + 8 * r + 4 * g);
+    f32x16& a = what == 0 ? b.s : b.p;
+    a[4 * r] = x.x; a[4 * r + 1] = x.y; a[4 * r + 2] = x.z; a[4 * r + 3] = x.w;
+  };
+  auto table_of = [&](int region, int qb, int ib) -> const float* {   // of query block qb, block ib of tile `region`
+    return &sL[0][qb == kblk ? 0 : qb < kblk ? 1 : 2][0] + region * (3 * kTileS) + 32 * ib;
+  };
+  const float k1cs = k1 * cs, kjf = (float)kj;
+  // stage 2 of block qb in `b` -> `to`; stage 3 of the block before it (its LDS place `tr`, its operands `from`); stage 1
+  // of the block behind it (`row`, `nx`).  `i0f`: first query of block qb's tile.  `tr_next`: the place that stage 3 reads in the next slot.
+  auto slot = [&](auto with3, auto with1, Block& b, int qb, float i0f, Packed& to, const Places& tr, int tr_ib,
+                  const Packed& from, const Places& row, int row_ib, Block& nx, const float* table, const float* dl,
+                  const Places& tr_next, int tr_next_ib, auto load) {
+    constexpr bool k3 = decltype(with3)::value, k1st = decltype(with1)::value;
+    if (qb == kblk) {   // block with the diagonal
+      float d0 = (float)(32 * qb - kj + 4 * g);
+      asm volatile("" : "+v"(d0));   // (else the 16 distances are kept in registers all the time)
 #pragma unroll
-    for (int ib = 0; ib < 2; ++ib) {
-      const int qb = (i0 >> 5) + ib;
-      const float* table = pl[qb == kblk ? 0 : qb < kblk ? 1 : 2];
-      off[ib] = qb == kblk ? 0.f : (qb < kblk ? k1 : -k1) * (float)(i0 - kj) * cs;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float4 l4 = *reinterpret_cast<const float4*>(&table[32 * ib + 8 * r + 4 * g]);
-        sacc[ib][4 * r + 0] = l4.x; sacc[ib][4 * r + 1] = l4.y; sacc[ib][4 * r + 2] = l4.z; sacc[ib][4 * r + 3] = l4.w;
-      }
-      if (qb == kblk) {   // block with the diagonal
-        const float d0 = (float)(i0 + 32 * ib) - fj;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sacc[ib][i] = fmaf(-k1, fabsf(d0 + (float)(8 * (i >> 2) + (i & 3))), sacc[ib][i]);
-      }
+      for (int i = 0; i < 16; ++i) b.s[i] = fmaf(-k1, fabsf(d0 + (float)(8 * (i >> 2) + (i & 3))), b.s[i]);
     }
+    const float off = (i0f - kjf) * (qb == kblk ? 0.f : qb < kblk ? k1cs : -k1cs);
+    // (the empty assembly keeps the vector instructions in this slot: the compiler would move them to where their results
+    // are used, behind the next slot's branch)
+    auto put = [](uint32_t& to, float lo, float hi) {
+      to = pack_bf16(lo, hi);
+      asm volatile("" : "+v"(to));
+    };
+    auto second = [&](int i) {   // dS of register i, and the operand words that are complete
+      b.p[i] = b.s[i] * b.p[i];
+      if (i & 1) put(to.p[i >> 1], b.s[i - 1], b.s[i]);
+      if (i > 0 && !(i & 1)) put(to.s[(i >> 1) - 1], b.p[i - 2], b.p[i - 1]);
+    };
 #pragma unroll
-    for (int ib = 0; ib < 2; ++ib) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float4 d4 = *reinterpret_cast<const float4*>(&pd[32 * ib + 8 * r + 4 * g]);
-        pacc[ib][4 * r + 0] = d4.x; pacc[ib][4 * r + 1] = d4.y; pacc[ib][4 * r + 2] = d4.z; pacc[ib][4 * r + 3] = d4.w;
+    for (int x = 0; x < 16; ++x) {
+      if (k1st && x < 4) {
+        start_row(nx, 0, x, table, dl);
+        start_row(nx, 1, x, table, dl);
       }
-      const uint16_t* qrow = &sQ[(32 * ib + c) * kPitch + 8 * g];
-      const uint16_t* grow = &sG[(32 * ib + c) * kPitch + 8 * g];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        sacc[ib] = mfma32(lds_read8(qrow + 16 * s), bk[s], sacc[ib]);
-        pacc[ib] = mfma32(lds_read8(grow + 16 * s), bv[s], pacc[ib]);
+      if (x < 12) {
+        const int y = x + 4;
+        if (kStage3[y] ? k3 : k1st)
+          f[y] = kStage3[y] ? read_tr(tr, tr_ib, kWhat[y], kDb[y], kStep[y]) : read_row(row, row_ib, kWhat[y], kStep[y]);
+      } else {
+        f[x - 12] = read_tr(tr_next, tr_next_ib, kWhat[x - 12], kDb[x - 12], kStep[x - 12]);
       }
-    }
-#pragma unroll
-    for (int ib = 0; ib < 2; ++ib) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const float p = fast_exp2(fmaf(sacc[ib][i], cs, off[ib]));
-        sacc[ib][i] = p;
-        pacc[ib][i] = p * pacc[ib][i];
-      }
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        const bf16x8 bp = pack8(sacc[ib][8 * kk + 0], sacc[ib][8 * kk + 1], sacc[ib][8 * kk + 2], sacc[ib][8 * kk + 3],
-                                sacc[ib][8 * kk + 4], sacc[ib][8 * kk + 5], sacc[ib][8 * kk + 6], sacc[ib][8 * kk + 7]);
-        const bf16x8 bs = pack8(pacc[ib][8 * kk + 0], pacc[ib][8 * kk + 1], pacc[ib][8 * kk + 2], pacc[ib][8 * kk + 3],
-                                pacc[ib][8 * kk + 4], pacc[ib][8 * kk + 5], pacc[ib][8 * kk + 6], pacc[ib][8 * kk + 7]);
-        const int roff = (32 * ib + 16 * kk + tr_row) * kPitch + tr_col;
-#pragma unroll
-        for (int db = 0; db < 2; ++db) {
-          const bf16x8 ag = join_tr(lds_read_tr4(&sG[roff + 32 * db]), lds_read_tr4(&sG[roff + 32 * db + 8 * kPitch]));
-          dvacc[db] = mfma32(ag, bp, dvacc[db]);
-          const bf16x8 aq = join_tr(lds_read_tr4(&sQ[roff + 32 * db]), lds_read_tr4(&sQ[roff + 32 * db + 8 * kPitch]));
-          dkacc[db] = mfma32(aq, bs, dkacc[db]);
+      if (kStage3[x]) {
+        if (k3) {
+          f32x16& acc = kWhat[x] == 0 ? dvacc[kDb[x]] : dkacc[kDb[x]];
+          acc = mfma32(f[x], operand(kWhat[x] == 0 ? from.p : from.s, kStep[x]), acc);
         }
+      } else if (k1st) {
+        f32x16& acc = kWhat[x] == 0 ? nx.s : nx.p;
+        acc = mfma32(f[x], kWhat[x] == 0 ? bk[kStep[x]] : bv[kStep[x]], acc);
       }
+      b.s[x] = fast_exp2(fmaf(b.s[x], cs, off));
+      if (x > 0) second(x - 1);
+      if ((x & 3) == 1) load(x >> 2);
+      if (x == 15) {
+        second(15);
+        put(to.s[7], b.p[14], b.p[15]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
+  auto none = [](int) {};
+  using Yes = std::true_type;
+  using No = std::false_type;
+  constexpr uint32_t kRegionBytes = kRegion * 2;
 
-  issue_tile(0);
-  store_tile(0);
-#pragma unroll 1
-  for (int it = 0; it < ntiles; ++it) {
-    const int i0 = it * kTileS;
-    __syncthreads();   // tile `it` is complete in its buffer; the other buffer is no longer being read
-    if (it + 1 < ntiles) issue_tile(i0 + kTileS);
-    if (wave_active) {
-      const uint16_t* sQ = smem + (it & 1) * kBuf;
-      const uint16_t* sG = sQ + kHalf;
-      const float (*pl)[kTileS] = sL[it & 1];
-      const float* pd = sD[it & 1];
-      qtile(sQ, sG, pl, pd, i0);
+  Block b0, b1;
+  Packed w0, w1;
+  if (wave_active) {   // stage 1 of block 0, stage 2 of it beside stage 1 of block 1
+    const float* table = table_of(0, 0, 0);
+    const Places tr = places_tr(0), row = places_row(0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      start_row(b0, 0, r, table, sD[0]);
+      start_row(b0, 1, r, table, sD[0]);
     }
-    if (it + 1 < ntiles) store_tile((it + 1) & 1);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      b0.s = mfma32(read_row(row, 0, 0, s), bk[s], b0.s);
+      b0.p = mfma32(read_row(row, 0, 1, s), bv[s], b0.p);
+    }
+    slot(No{}, Yes{}, b0, 0, 0.f, w0, tr, 0, w1, row, 1, b1, table_of(0, 1, 1), sD[0] + 32, tr, 0, none);
   }
-  __syncthreads();   // the buffers are free: they now carry the output rows
+  // Step t: what the step before the last one requested has arrived (tile t + 1, and lse and Delta of tile t + 2, which
+  // become tables here), and tile t + 3 is requested.  Loads past the end are issued too: their number stays the same.
+  float i0f = 0.f;   // first query of tile t
+#pragma unroll 1
+  for (int t = 0; t + 1 < ntiles; ++t) {
+    const int here = t & (kRing - 1), next = (t + 1) & (kRing - 1), after = (t + 2) & (kRing - 1), to = (t + 3) & (kRing - 1);
+    staged_barrier<kRowLoads + 1>();
+    if (t == 0) issue_rows(2, 2);   // (the region of the K rows)
+    // Loads in one go take 32 cycles each and block the waves, so they are spread over the step's matrix instructions (not
+    // the ones with an address per lane: there are no registers left for those).
+    if (!wave_active || !contig) issue_rows(t + 3, to);
+    if (!wave_active) {
+      issue_raw(t + 4, here);
+      if (wave < 2) store_tables(t + 2, after, sRaw[wave][after][lane]);
+    } else {
+      const Places tr = places_tr(here * kRegionBytes), row = places_row(next * kRegionBytes);
+      float raw = 0.f;
+      auto first_half = [&](int j) {
+        if ((j == 0 || j == 2) && contig) issue_row(t + 3, to, j >> 1);
+        if (j == 3) issue_raw(t + 4, here);
+      };
+      auto second_half = [&](int j) {
+        if ((j == 0 || j == 2) && contig) issue_row(t + 3, to, 2 + (j >> 1));
+        if (j == 1 && wave < 2) raw = sRaw[wave][after][lane];
+        if (j == 3 && wave < 2) store_tables(t + 2, after, raw);
+      };
+      slot(Yes{}, Yes{}, b1, 2 * t + 1, i0f, w1, tr, 0, w0, row, 0, b0, table_of(next, 2 * t + 2, 0), sD[next], tr, 1,
+           first_half);
+      i0f += (float)kTileS;
+      slot(Yes{}, Yes{}, b0, 2 * t + 2, i0f, w0, tr, 1, w1, row, 1, b1, table_of(next, 2 * t + 3, 1), sD[next] + 32,
+           places_tr(next * kRegionBytes), 0, second_half);
+    }
+  }
+  if (wave_active) {   // the last tile's second block
+    const Places tr = places_tr(((ntiles - 1) & (kRing - 1)) * kRegionBytes);
+    slot(Yes{}, No{}, b1, 2 * ntiles - 1, i0f, w1, tr, 0, w0, tr, 0, b0, nullptr, nullptr, tr, 1, none);
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      if (!kStage3[x]) continue;
+      if (x >= 4) f[x] = read_tr(tr, 1, kWhat[x], kDb[x], kStep[x]);
+      f32x16& acc = kWhat[x] == 0 ? dvacc[kDb[x]] : dkacc[kDb[x]];
+      acc = mfma32(f[x], operand(kWhat[x] == 0 ? w1.p : w1.s, kStep[x]), acc);
+    }
+  }
+  staged_barrier<0>();   // the regions are free: they now carry the output rows
   const int orow = lane >> 3, ocol = (lane & 7) * 8;
   if (!wave_active) {   // tokens that are no keys (only when the call limits the keys): zero gradient rows
     const u32x4 zero = {0u, 0u, 0u, 0u};

@@ -101,6 +101,25 @@ __device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t lane_off, u32
   (void)m0;
 }
 
+// The same for 64 x 4 bytes.
+__device__ __forceinline__ void load_word_to_lds(uint32_t lds, uint32_t lane_off, u32x4 rsrc) {
+  uint32_t m0;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dword %2, %3, 0 offen lds"
+               : "=&{m0}"(m0)
+               : "s"(lds), "v"(lane_off), "s"(rsrc)
+               : "memory");
+  (void)m0;
+}
+// load_to_lds with a 64-bit address per lane.
+__device__ __forceinline__ void load_to_lds_each(uint32_t lds, const void* lane_ptr) {
+  uint32_t m0;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off"
+               : "=&{m0}"(m0)
+               : "s"(lds), "v"(lane_ptr)
+               : "memory");
+  (void)m0;
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 }  // namespace mb
