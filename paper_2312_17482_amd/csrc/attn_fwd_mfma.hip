@@ -12,6 +12,7 @@
 //     exchange with the partner lane l^32, and
 //   * the accumulator tile, rounded to bf16, is already the B operand of O^T += V^T P^T.
 #include "attn_plan.h"
+#include "attn_stage.h"
 #include "common.h"
 #include "mfma_util.h"
 
@@ -24,14 +25,19 @@ constexpr int kD = 64;
 constexpr int kKStride = 72;   // LDS row pitch of K in bf16 (144 B): 16-byte row reads spread over banks
 constexpr int kVStride = 80;   // LDS row pitch of V in bf16 (160 B): 4-row transposing reads spread over banks
 
-// Any sequence length: tiles of 64 keys with a running (online) softmax.  LDS holds two K/V tiles: while
-// one is consumed, the next travels HBM -> registers -> the other buffer, so a workgroup waits for memory
-// only on its first tile and there is one barrier per tile.  Registers are kept <= 128 so that four
-// workgroups share a compute unit.  Same arithmetic as the single-tile kernel below (bias pre-loaded
-// into the accumulator, scale folded into the exponent); the running output is rescaled only when some
-// query's maximum actually moved.
+// Any sequence length: tiles of 64 keys with a running (online) softmax.  The tiles go straight to LDS, two steps ahead,
+// through a ring of three regions (attn_stage.h): no registers and no vector instructions on the way, no bank conflicts,
+// one barrier per tile.  At most 168 registers and 48 KB of LDS, so that three workgroups share a compute unit.
+// Same arithmetic as the single-tile kernel below (bias in the accumulator's start value, scale folded into the exponent);
+// the running output is rescaled only when some query's maximum actually moved.
+// What bounds it at full length: the vector unit.  A tile costs a wave about 155 vector instructions of 4 cycles, 32
+// exponentials of 8 and 10 for each of 16 matrix instructions to be issued, 1030 cycles; it takes 1340.
+// With tiles through registers and padded rows (a quarter of the LDS cycles were conflicts), before and after: 16 x 2048 tokens,
+// 16 heads 340 and 328 us; 64 x 64 .. 512 tokens, 12 heads 53 and 48 us; 64 x 512 with a key mask 86 and 79 us.
+// Tried: the tile with the diagonal first and outwards from there, so that the maximum hardly moves: 328 -> 339 us.
 constexpr int kTileK = 64;                                        // keys per LDS tile
-constexpr int kBufElems = kTileK * kKStride + kTileK * kVStride;  // one K tile + one V tile
+constexpr int kRegion = 2 * kTileK * kD;                          // one K tile + one V tile, as attn_stage.h stages them
+constexpr int kRing = 3;                                          // regions
 
 // A sequence longer than the max_seqlen the launch was sized for: the sticky flag is raised and the
 // sequence's log-sum-exp rows (n of them, from `row`) become NaN, so the misuse shows in the result too.
@@ -61,11 +67,10 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(const int32_t* 
   }
 }
 
-// kMode (see kRowsIdentity .. in common.h): for a sequence whose tokens sit in consecutive rows of the
-// activation buffers, spanning fewer than 2^31 bytes, the K/V rows of a tile are fetched with buffer loads
-// whose descriptor starts at the tile's first row and ends at the sequence's last one: the address is
-// scalar arithmetic plus one constant per-lane offset, and rows past the end read as zeros without a
-// compare.  Otherwise every row's address is formed per lane (row index looked up in token_rows when given).
+// kMode (see kRowsIdentity .. in common.h): the rows of a sequence whose tokens sit in consecutive rows of the activation
+// buffers, spanning fewer than 2^31 bytes, are loaded through descriptors that start at its first row and end at its last
+// one: a lane's offset grows by a constant from tile to tile, and rows past the end arrive as zeros without a compare.
+// Otherwise every lane forms its own address (row index looked up in token_rows when given).
 template <int kMode>
 __global__ __launch_bounds__(256, 3) void attn_fwd_tiled_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, int64_t qs,
@@ -73,7 +78,7 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_tiled_kernel(
     float* __restrict__ lse, int T, const int32_t* __restrict__ token_rows, const int32_t* __restrict__ plan,
     int64_t plan_cap) {
   const int32_t* rows = kMode == kRowsIdentity ? nullptr : token_rows;
-  __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kBufElems];   // 38 KB; also stages Q and O rows
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kRing * kRegion];   // 48 KB; also stages Q and O rows
 
   int start, n, nk, qtile, h;   // nk <= n: the sequence's first nk tokens are its keys
   if (!plan_fetch(plan, plan_cap, &start, &n, &nk, &qtile, &h)) return;   // this XCD's list is shorter
@@ -92,75 +97,57 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_tiled_kernel(
   const int qi = qw + c;                  // this lane's query (position inside the sequence)
   const int qblk = (q0 >> 5) + wave;      // index of this wave's block of 32 queries
   const int ntiles = (nk + kTileK - 1) / kTileK;
-  const int st_row = tid >> 3, st_col = (tid & 7) * 8;
-  const uint16_t* kh = k + h * kD + st_col;
-  const uint16_t* vh = v + h * kD + st_col;
 
-  u32x4 tk[2], tv[2];
-  constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
-  const uint32_t koff = ((uint32_t)st_row * (uint32_t)ks + (uint32_t)(h * kD + st_col)) * 2u;
-  const uint32_t voff = ((uint32_t)st_row * (uint32_t)vs + (uint32_t)(h * kD + st_col)) * 2u;
-  auto issue_tile = [&](int j0) {   // rows j0 + 32it + st_row of K and V -> registers (zeros past the end)
-    if (contig) {
-      const int left = nk - j0;     // > 0: key rows j0 .. nk-1 exist
-      const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<uint16_t*>(k) + (int64_t)(row0 + j0) * ks, 0, left * (int)ks * 2, kRsrcFlags);
-      const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<uint16_t*>(v) + (int64_t)(row0 + j0) * vs, 0, left * (int)vs * 2, kRsrcFlags);
-#pragma unroll
-      for (int it = 0; it < 2; ++it) {
-        tk[it] = __builtin_amdgcn_raw_buffer_load_b128(kr, koff + (uint32_t)it * 64u * (uint32_t)ks, 0, 0);
-        tv[it] = __builtin_amdgcn_raw_buffer_load_b128(vr, voff + (uint32_t)it * 64u * (uint32_t)vs, 0, 0);
-      }
-      return;
-    }
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      tk[it] = tv[it] = u32x4{0u, 0u, 0u, 0u};
-      const int j = j0 + 32 * it + st_row;
-      if (j < nk) {
-        const int64_t gr = tok_row(rows, start + j);
-        tk[it] = *reinterpret_cast<const u32x4*>(kh + gr * ks);
-        tv[it] = *reinterpret_cast<const u32x4*>(vh + gr * vs);
-      }
-    }
-  };
-  auto store_tile = [&](int buf) {
-    uint16_t* bk_ = smem + buf * kBufElems;
-    uint16_t* bv_ = bk_ + kTileK * kKStride;
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      *reinterpret_cast<u32x4*>(&bk_[(32 * it + st_row) * kKStride + st_col]) = tk[it];
-      *reinterpret_cast<u32x4*>(&bv_[(32 * it + st_row) * kVStride + st_col]) = tv[it];
-    }
-  };
-
-  // ---- Q rows (coalesced) -> LDS -> Q^T fragments; the first K/V tile is already on its way
+  // ---- loads: this wave's Q rows, then its share of the K / V tiles
+  const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t*)smem);
   {
-    u32x4 tq[4];
+    const u32x4 q_rsrc = stage_rsrc(q + row0 * qs + h * kD, qs, n);
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      tq[it] = u32x4{0u, 0u, 0u, 0u};
-      const int i = q0 + 32 * it + st_row;
-      if (i < n) tq[it] = *reinterpret_cast<const u32x4*>(q + tok_row(rows, start + i) * qs + h * kD + st_col);
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t at = lds0 + (2 * kRegion + (32 * wave + 8 * j) * kD) * 2;
+      if (contig) stage_rows(at, stage_lane_off(lane, j & 1, qs) + (uint32_t)(qw + 8 * j) * (uint32_t)qs * 2u, q_rsrc);
+      else stage_each(at, stage_address(q + h * kD, qs, rows, start, qw + 8 * j, n, lane, j & 1));
     }
-    issue_tile(0);
-#pragma unroll
-    for (int it = 0; it < 4; ++it)
-      *reinterpret_cast<u32x4*>(&smem[(32 * it + st_row) * kKStride + st_col]) = tq[it];
   }
-  __syncthreads();
-  bf16x8 bq[4];
+  const u32x4 k_rsrc = stage_rsrc(k + row0 * ks + h * kD, ks, nk), v_rsrc = stage_rsrc(v + row0 * vs + h * kD, vs, nk);
+  // the wave's first 8 rows of the tile to load next; its second 8 rows lie 32 behind them
+  uint32_t k_off = stage_lane_off(lane, wave & 1, ks) + 8u * wave * (uint32_t)ks * 2u;
+  uint32_t v_off = stage_lane_off(lane, wave & 1, vs) + 8u * wave * (uint32_t)vs * 2u;
+  constexpr int kRowLoads = 4;   // loads per wave and tile
+  auto issue_row = [&](int t, int region, int j) {   // the j-th of them, of tile t; the tiles are taken in order
+    const int i = j >> 1;
+    const bool is_k = (j & 1) == 0;
+    const uint32_t at = lds0 + (uint32_t)(region * kRegion + (is_k ? 0 : kTileK * kD) + 8 * (wave + 4 * i) * kD) * 2;
+    uint32_t& off = is_k ? k_off : v_off;
+    const int64_t stride = is_k ? ks : vs;
+    if (contig) {
+      stage_rows(at, off, is_k ? k_rsrc : v_rsrc);
+      off += 64u * (uint32_t)stride;
+    } else {
+      stage_each(at, stage_address((is_k ? k : v) + h * kD, stride, rows, start, t * kTileK + 8 * (wave + 4 * i), nk, lane,
+                                   wave & 1));
+    }
+  };
+  auto issue_tile = [&](int t, int region) {
 #pragma unroll
-  for (int s = 0; s < 4; ++s) bq[s] = lds_read8(&smem[(32 * wave + c) * kKStride + 16 * s + 8 * g]);
-  __syncthreads();
-  store_tile(0);
+    for (int j = 0; j < kRowLoads; ++j) issue_row(t, region, j);
+  };
+  issue_tile(0, 0);
+  issue_tile(1, 1);
+
+  // ---- places in a region (bytes): K rows, transposed patches of V
+  const char* const lds = reinterpret_cast<const char*>(smem);
+  uint32_t row_at[4], tr_at[2][2];
+  stage_row_places(lane, row_at);
+  stage_tr_places(lane, tr_at);
+  bf16x8 bq[4];   // Q^T fragments of the wave's own rows
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * kRowLoads) : "memory");
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+    bq[s] = lds_read8(reinterpret_cast<const uint16_t*>(lds + row_at[s] + (2 * kRegion + 32 * wave * kD) * 2));
 
   const float cs = scale * kLog2e;
   const float k1 = slopes[h] / scale;
-  const int tr_i = lane & 15, tr_q = lane >> 4;
-  const int tr_row = (tr_i >> 2) + 4 * (tr_q >> 1);
-  const int tr_col = 16 * (tr_q & 1) + 4 * (tr_i & 3);
 
   f32x16 oacc[2];
 #pragma unroll
@@ -176,10 +163,22 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_tiled_kernel(
   // One tile of 64 keys.  The code that touches the running output exists once, with no branch
   // around it: a ragged last tile is handled by setting the scores of the keys that do not exist to -inf (their
   // K rows are staged as zeros), and only the first product has variants.
-  auto tile = [&](int j0, int jt) {
-    const uint16_t* bufK = smem + (jt & 1) * kBufElems;
-    const uint16_t* bufV = bufK + kTileK * kKStride;
+  auto tile = [&](int jt, uint32_t region, auto load) {
+    const int j0 = jt * kTileK;
     const int rem = nk - j0;
+    uint32_t ka[4], va[2][2];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) ka[s] = row_at[s] + region;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) va[s >> 1][s & 1] = tr_at[s >> 1][s & 1] + region;
+    auto read_k = [&](int jb, int s) {
+      return lds_read8(reinterpret_cast<const uint16_t*>(lds + ka[s] + jb * (32 * kD * 2)));
+    };
+    auto read_v = [&](int jb, int kk, int db) {
+      const uint32_t at = (kTileK + 32 * jb + 16 * kk) * kD * 2;
+      return join_tr(lds_read_tr4(reinterpret_cast<const uint16_t*>(lds + va[db][0] + at)),
+                     lds_read_tr4(reinterpret_cast<const uint16_t*>(lds + va[db][1] + at)));
+    };
     float fi = (float)(qi - j0 - 4 * g);   // i - j = fi - cj with cj = 32jb + 8*(v/4) + v%4
     asm volatile("" : "+v"(fi));
     // Off the diagonal block |i-j| = +-(fi - cj) is linear: its part per accumulator row is the same in every block (up
@@ -187,11 +186,10 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_tiled_kernel(
     // lane, off[jb], is added to the block's maximum and to the exponent's constant.  No instruction per score.
     f32x16 sacc[2];
     float off[2];
-    const uint16_t* krow = &bufK[c * kKStride + 8 * g];
 #pragma unroll
     for (int jb = 0; jb < 2; ++jb) {
       const int kblk = 2 * jt + jb;
-      const bf16x8 ak = lds_read8(krow + 32 * jb * kKStride);
+      const bf16x8 ak = read_k(jb, 0);
       if (kblk == qblk) {   // the block that holds the diagonal; the ones behind it lie on its other side
         f32x16 diag;
 #pragma unroll
@@ -207,9 +205,11 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_tiled_kernel(
     }
 #pragma unroll
     for (int s = 1; s < 4; ++s) {
-      sacc[0] = mfma32(lds_read8(krow + 16 * s), bq[s], sacc[0]);
-      sacc[1] = mfma32(lds_read8(krow + 32 * kKStride + 16 * s), bq[s], sacc[1]);
+      sacc[0] = mfma32(read_k(0, s), bq[s], sacc[0]);
+      sacc[1] = mfma32(read_k(1, s), bq[s], sacc[1]);
     }
+    load(0);
+    load(1);
     if (rem < kTileK) {   // ragged end: keys that do not exist (or are masked out) get -inf
       const int lim = rem - 4 * g;
 #pragma unroll
@@ -250,29 +250,40 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_tiled_kernel(
         const bf16x8 bp = pack8(sacc[jb][8 * kk + 0], sacc[jb][8 * kk + 1], sacc[jb][8 * kk + 2],
                                 sacc[jb][8 * kk + 3], sacc[jb][8 * kk + 4], sacc[jb][8 * kk + 5],
                                 sacc[jb][8 * kk + 6], sacc[jb][8 * kk + 7]);
-        const uint16_t* vb = &bufV[(jb * 32 + 16 * kk + tr_row) * kVStride + tr_col];
 #pragma unroll
-        for (int db = 0; db < 2; ++db) {
-          const s16x4 lo = lds_read_tr4(vb + 32 * db);
-          const s16x4 hi = lds_read_tr4(vb + 32 * db + 8 * kVStride);
-          oacc[db] = mfma32(join_tr(lo, hi), bp, oacc[db]);
-        }
+        for (int db = 0; db < 2; ++db) oacc[db] = mfma32(read_v(jb, kk, db), bp, oacc[db]);
+      }
+      if (jb == 0) {
+        load(2);
+        load(3);
       }
     }
     l_run += (lsum[0] + lsum[1]) + (lsum[2] + lsum[3]);
   };
 
+  // Step jt: tile jt has arrived, the next one is on its way and the one behind that is requested.  Loads past the end are
+  // issued too: their number stays the same.
+  int region = 0;
+  if (!wave_active) {   // (a loop of its own: inside the other one the accumulators would be copied in every step)
+    for (int jt = 0; jt < ntiles; ++jt) {
+      staged_barrier<kRowLoads>();
+      issue_tile(jt + 2, region == 0 ? kRing - 1 : region - 1);
+      region = region == kRing - 1 ? 0 : region + 1;
+    }
+    staged_barrier<0>();
+    return;
+  }
 #pragma unroll 1
   for (int jt = 0; jt < ntiles; ++jt) {
-    const int j0 = jt * kTileK;
-    __syncthreads();   // tile jt is complete in its buffer; the other buffer is no longer being read
-    if (jt + 1 < ntiles) issue_tile(j0 + kTileK);
-
-    if (wave_active) tile(j0, jt);
-    if (jt + 1 < ntiles) store_tile((jt + 1) & 1);
+    const int to = region == 0 ? kRing - 1 : region - 1;   // of tile jt + 2: the region of tile jt - 1
+    staged_barrier<kRowLoads>();
+    if (!contig) issue_tile(jt + 2, to);
+    tile(jt, (uint32_t)region * (kRegion * 2), [&](int j) {
+      if (contig) issue_row(jt + 2, to, j);
+    });
+    region = region == kRing - 1 ? 0 : region + 1;
   }
-  __syncthreads();   // everyone is done with the K/V buffers: they now carry the output rows
-  if (!wave_active) return;
+  staged_barrier<0>();   // everyone is done with the K/V regions: they now carry the output rows
 
   const float l = sum_both_halves(l_run);
   const float inv = 1.f / l;
@@ -550,8 +561,9 @@ mb_status launch_attn_fwd_mfma(const AttnShape& s, const void* q, const void* k,
     if (st != MB_OK) return st;
     plan = static_cast<const int32_t*>(workspace);
   }
-  // buffer-load path: a sequence's K / V rows within 2^31 bytes of its first
-  const int64_t span = (int64_t)s.max_seqlen * (ks > vs ? ks : vs) * 2;
+  // descriptors: a sequence's rows within 2^31 bytes of its first
+  const int64_t widest = ks > vs ? (ks > qs ? ks : qs) : (vs > qs ? vs : qs);
+  const int64_t span = (int64_t)s.max_seqlen * widest * 2;
 #define MB_LAUNCH_TILED(M)                                                                                         \
   hipLaunchKernelGGL(attn_fwd_tiled_kernel<M>, dim3((unsigned)(cap * kPlanXcds)), dim3(256), 0, stream,            \
                      (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, qs, ks, vs, s.slopes, s.scale,    \

@@ -53,6 +53,26 @@ __device__ __forceinline__ const void* stage_address(const uint16_t* head, int64
   return p;
 }
 
+// Byte offsets of what a lane reads of a staged tile as matrix operands.  Rows (lds_read8): k-step s takes columns
+// 16 s + 8 g .. + 7 of row lane % 32, the next 32 rows lie 4096 bytes on.
+__device__ __forceinline__ void stage_row_places(int lane, uint32_t (&at)[4]) {
+  const int c = lane & 31, g = lane >> 5;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) at[s] = (uint32_t)(c * 64 + ((2 * s + g) ^ stage_swizzle(c)) * 8) * 2;
+}
+// Transposed patches (lds_read_tr4, two halves joined): columns 32 db .. + 31 of 16 rows, the next 16 rows 2048 bytes on.
+__device__ __forceinline__ void stage_tr_places(int lane, uint32_t (&at)[2][2]) {
+  const int i = lane & 15, q = lane >> 4;
+  const int row = (i >> 2) + 4 * (q >> 1), piece = 2 * (q & 1) + ((i & 3) >> 1);
+#pragma unroll
+  for (int db = 0; db < 2; ++db)
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int r = row + 8 * half;
+      at[db][half] = (uint32_t)(r * 64 + ((4 * db + piece) ^ stage_swizzle(r)) * 8 + 4 * (i & 1)) * 2;
+    }
+}
+
 // All but the newest `kNewer` loads of this wave have arrived and its LDS operations are done; then the workgroup's barrier.
 template <int kNewer>
 __device__ __forceinline__ void staged_barrier() {
