@@ -32,15 +32,13 @@ constexpr int kTile = 128;
 constexpr int kPitch = 72;   // LDS row pitch in bf16 (144 B)
 
 // ------------------------------------------------------------------------------------------------ any length
-// Both kernels below stream their second operand in tiles of 64 rows.  dQ: through two LDS buffers; while one tile is
-// consumed the next travels HBM -> registers -> the other buffer (one barrier per tile).  dK/dV: see there.
+// Both kernels below stream their second operand in tiles of 64 rows, straight to LDS through a ring of regions
+// (attn_stage.h), one barrier per tile.
 // Global memory is touched only as full 128-byte rows of one head; fragments and output rows pass
 // through LDS.  Which workgroup does what is read from the work plan (attn_plan.h).
 constexpr int kTileS = 64;                          // rows of a streamed tile
-constexpr int kHalf = kTileS * kPitch;              // elements of one streamed operand tile (4608)
-constexpr int kBuf = 2 * kHalf;                     // one buffer: two operand tiles (= 128 rows of pitch 72)
-constexpr int kRing = 4;                            // regions that the tiles of dK/dV go through
 constexpr int kRegion = 2 * kTileS * kD;            // elements of a region: two operand tiles as attn_stage.h stages them
+constexpr int kRing = 4;                            // regions that the tiles of dK/dV go through
 
 // ------------------------------------------------------------------------------------------------ dK, dV
 // One workgroup per (sequence, head, 128 keys); wave w owns keys 32w.. and streams all queries.
@@ -53,12 +51,10 @@ constexpr int kRegion = 2 * kTileS * kD;            // elements of a region: two
 // Of the 519 us the loads cost 30, the tables of lse and Delta 15, the vector instructions 60 (each left out in turn).
 // Tried: four steps unrolled so that every LDS address is a constant (1100 registers spilled).
 //
-// kMode (both kernels; see kRowsIdentity .. in common.h): for a sequence whose tokens sit in consecutive
-// rows of the activation buffers, spanning fewer than 2^31 bytes, the rows of a streamed tile are fetched
-// with buffer loads whose descriptor starts at the tile's first row and ends at the sequence's last one:
-// the address is scalar arithmetic plus one constant per-lane offset, and rows past the end read as
-// zeros without a compare.  Otherwise every row's address is formed per lane (row index looked up in
-// token_rows when given).
+// kMode (both kernels; see kRowsIdentity .. in common.h): the rows of a sequence whose tokens sit in consecutive
+// rows of the activation buffers, spanning fewer than 2^31 bytes, are loaded through descriptors that start at its first row
+// and end at its last one: a lane's offset grows by a constant from tile to tile, and rows past the end arrive as zeros
+// without a compare.  Otherwise every lane forms its own address (row index looked up in token_rows when given).
 constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
 
 template <int kMode>
@@ -177,21 +173,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
   store_tables(0, 0, raw0);
   store_tables(1, 1, raw1);
 
-  // ---- fragment addresses (bytes): rows for S and dP, transposed patches for dV and dK
+  // ---- places in a region (bytes): rows for S and dP, transposed patches for dV and dK
   uint32_t row_at[4], tr_at[2][2];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) row_at[s] = (uint32_t)(c * kD + ((2 * s + g) ^ stage_swizzle(c)) * 8) * 2;
-  {
-    const int tr_i = lane & 15, tr_q = lane >> 4;
-    const int tr_row = (tr_i >> 2) + 4 * (tr_q >> 1), tr_piece = 2 * (tr_q & 1) + ((tr_i & 3) >> 1);
-#pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const int r = tr_row + 8 * half;
-        tr_at[db][half] = (uint32_t)(r * kD + ((4 * db + tr_piece) ^ stage_swizzle(r)) * 8 + 4 * (tr_i & 1)) * 2;
-      }
-  }
+  stage_row_places(lane, row_at);
+  stage_tr_places(lane, tr_at);
   const char* const lds = reinterpret_cast<const char*>(smem);
   // the wave's K^T, V^T fragments (B operands): lane = key column, 8 consecutive d per k-step
   bf16x8 bk[4], bv[4];
@@ -336,6 +321,24 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
   }
   // Step t: what the step before the last one requested has arrived (tile t + 1, and lse and Delta of tile t + 2, which
   // become tables here), and tile t + 3 is requested.  Loads past the end are issued too: their number stays the same.
+  if (!wave_active) {   // (a loop of its own: inside the other one the accumulators would be copied in every step)
+    for (int t = 0; t + 1 < ntiles; ++t) {
+      staged_barrier<kRowLoads + 1>();
+      if (t == 0) issue_rows(2, 2);
+      issue_rows(t + 3, (t + 3) & (kRing - 1));
+      issue_raw(t + 4, t & (kRing - 1));
+      if (wave < 2) store_tables(t + 2, (t + 2) & (kRing - 1), sRaw[wave][(t + 2) & (kRing - 1)][lane]);
+    }
+    staged_barrier<0>();
+    // tokens that are no keys (only when the call limits the keys): zero gradient rows
+    for (int row = lane >> 3; row < 32 && kw + row < n; row += 8) {
+      const u32x4 zero = {0u, 0u, 0u, 0u};
+      const int64_t gr = tok_row(rows, start + kw + row);
+      *reinterpret_cast<u32x4*>(dk + gr * dks + h * kD + (lane & 7) * 8) = zero;
+      *reinterpret_cast<u32x4*>(dv + gr * dvs + h * kD + (lane & 7) * 8) = zero;
+    }
+    return;
+  }
   float i0f = 0.f;   // first query of tile t
 #pragma unroll 1
   for (int t = 0; t + 1 < ntiles; ++t) {
@@ -344,30 +347,25 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
     if (t == 0) issue_rows(2, 2);   // (the region of the K rows)
     // Loads in one go take 32 cycles each and block the waves, so they are spread over the step's matrix instructions (not
     // the ones with an address per lane: there are no registers left for those).
-    if (!wave_active || !contig) issue_rows(t + 3, to);
-    if (!wave_active) {
-      issue_raw(t + 4, here);
-      if (wave < 2) store_tables(t + 2, after, sRaw[wave][after][lane]);
-    } else {
-      const Places tr = places_tr(here * kRegionBytes), row = places_row(next * kRegionBytes);
-      float raw = 0.f;
-      auto first_half = [&](int j) {
-        if ((j == 0 || j == 2) && contig) issue_row(t + 3, to, j >> 1);
-        if (j == 3) issue_raw(t + 4, here);
-      };
-      auto second_half = [&](int j) {
-        if ((j == 0 || j == 2) && contig) issue_row(t + 3, to, 2 + (j >> 1));
-        if (j == 1 && wave < 2) raw = sRaw[wave][after][lane];
-        if (j == 3 && wave < 2) store_tables(t + 2, after, raw);
-      };
-      slot(Yes{}, Yes{}, b1, 2 * t + 1, i0f, w1, tr, 0, w0, row, 0, b0, table_of(next, 2 * t + 2, 0), sD[next], tr, 1,
-           first_half);
-      i0f += (float)kTileS;
-      slot(Yes{}, Yes{}, b0, 2 * t + 2, i0f, w0, tr, 1, w1, row, 1, b1, table_of(next, 2 * t + 3, 1), sD[next] + 32,
-           places_tr(next * kRegionBytes), 0, second_half);
-    }
+    if (!contig) issue_rows(t + 3, to);
+    const Places tr = places_tr(here * kRegionBytes), row = places_row(next * kRegionBytes);
+    float raw = 0.f;
+    auto first_half = [&](int j) {
+      if ((j == 0 || j == 2) && contig) issue_row(t + 3, to, j >> 1);
+      if (j == 3) issue_raw(t + 4, here);
+    };
+    auto second_half = [&](int j) {
+      if ((j == 0 || j == 2) && contig) issue_row(t + 3, to, 2 + (j >> 1));
+      if (j == 1 && wave < 2) raw = sRaw[wave][after][lane];
+      if (j == 3 && wave < 2) store_tables(t + 2, after, raw);
+    };
+    slot(Yes{}, Yes{}, b1, 2 * t + 1, i0f, w1, tr, 0, w0, row, 0, b0, table_of(next, 2 * t + 2, 0), sD[next], tr, 1,
+         first_half);
+    i0f += (float)kTileS;
+    slot(Yes{}, Yes{}, b0, 2 * t + 2, i0f, w0, tr, 1, w1, row, 1, b1, table_of(next, 2 * t + 3, 1), sD[next] + 32,
+         places_tr(next * kRegionBytes), 0, second_half);
   }
-  if (wave_active) {   // the last tile's second block
+  {   // the last tile's second block
     const Places tr = places_tr(((ntiles - 1) & (kRing - 1)) * kRegionBytes);
     slot(Yes{}, No{}, b1, 2 * ntiles - 1, i0f, w1, tr, 0, w0, tr, 0, b0, nullptr, nullptr, tr, 1, none);
 #pragma unroll
@@ -380,20 +378,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
   }
   staged_barrier<0>();   // the regions are free: they now carry the output rows
   const int orow = lane >> 3, ocol = (lane & 7) * 8;
-  if (!wave_active) {   // tokens that are no keys (only when the call limits the keys): zero gradient rows
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int row = 8 * it + orow;
-      if (kw + row < n) {
-        const int64_t gr = tok_row(rows, start + kw + row);
-        *reinterpret_cast<u32x4*>(dk + gr * dks + h * kD + ocol) = zero;
-        *reinterpret_cast<u32x4*>(dv + gr * dvs + h * kD + ocol) = zero;
-      }
-    }
-    return;
-  }
-
   uint16_t* slab = &smem[(32 * wave) * kPitch];   // 32 rows private to this wave
   auto store_rows = [&](const f32x16(&acc)[2], float mul, uint16_t* __restrict__ out, int64_t stride) {
 #pragma unroll
@@ -420,7 +404,11 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
 
 // ------------------------------------------------------------------------------------------------ dQ
 // One workgroup per (sequence, head, 128 queries); wave w owns queries 32w.. and streams all keys.
-// (at most 168 registers, so that three workgroups share a compute unit)
+// At most 168 registers, so that three workgroups share a compute unit; the tiles arrive two steps ahead.
+// Bound by vector issue as the forward is: 57 vector instructions and 16 exponentials a block of 32 keys, beside 12 matrix
+// instructions.  -Delta is the start value of dP out of registers that hold it 16 times (16 instructions a block less).  With
+// tiles through registers, before and after: 16 x 2048 tokens, 16 heads 455 and 400 us; 64 x 64 .. 512 tokens, 12 heads 70
+// and 62 us; 64 x 512 with a key mask 112 and 102 us.
 template <int kMode>
 __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
     const uint16_t* __restrict__ dout, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
@@ -429,7 +417,7 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
     const float* __restrict__ slopes, float scale, uint16_t* __restrict__ dq, int64_t dqs, int T,
     const int32_t* __restrict__ token_rows, const int32_t* __restrict__ plan, int64_t plan_cap) {
   const int32_t* rows = kMode == kRowsIdentity ? nullptr : token_rows;
-  __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kBuf];   // per buffer: K tile, V tile
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[3 * kRegion];   // regions of a K and a V tile each
   __shared__ __attribute__((aligned(16))) float sDelta[kTile];       // -Delta of this workgroup's queries
 
   int start, n, nk, qtile, h;   // nk <= n: the sequence's first nk tokens are its keys
@@ -453,100 +441,105 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
   const float cs = scale * kLog2e;
   const float k1 = slopes[h] / scale;
 
-  // ---- Q, dO rows of this workgroup's 128 queries (coalesced) -> LDS -> Q^T, dO^T fragments; the O rows
-  //      only serve Delta_i = dO_i . O_i (8 lanes per row, 8 elements each), kept in LDS for this kernel and
-  //      written to [H, T] for the dK/dV kernel
-  bf16x8 bq[4], bg[4];
+  // ---- loads: this wave's Q and dO rows, then its share of the K / V tiles
+  const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t*)smem);
   {
-    u32x4 tq[4], tg[4], to[4];
+    const u32x4 q_rsrc = stage_rsrc(q + row0 * qs + h * kD, qs, n), g_rsrc = stage_rsrc(dout + row0 * dos + h * kD, dos, n);
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      tq[it] = tg[it] = to[it] = u32x4{0u, 0u, 0u, 0u};
-      const int i = q0 + 32 * it + st_row;
-      if (i < n) {
-        const int64_t gr = tok_row(rows, start + i);
-        tq[it] = *reinterpret_cast<const u32x4*>(q + gr * qs + h * kD + st_col);
-        tg[it] = *reinterpret_cast<const u32x4*>(dout + gr * dos + h * kD + st_col);
-        to[it] = *reinterpret_cast<const u32x4*>(o + gr * os + h * kD + st_col);
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t at = lds0 + (kRegion + (32 * wave + 8 * j) * kD) * 2;
+      if (contig) {
+        const uint32_t row = qw + 8 * j;
+        stage_rows(at, stage_lane_off(lane, j & 1, qs) + row * (uint32_t)qs * 2u, q_rsrc);
+        stage_rows(at + kRegion * 2, stage_lane_off(lane, j & 1, dos) + row * (uint32_t)dos * 2u, g_rsrc);
+      } else {
+        stage_each(at, stage_address(q + h * kD, qs, rows, start, qw + 8 * j, n, lane, j & 1));
+        stage_each(at + kRegion * 2, stage_address(dout + h * kD, dos, rows, start, qw + 8 * j, n, lane, j & 1));
       }
     }
+  }
+  const u32x4 k_rsrc = stage_rsrc(k + row0 * ks + h * kD, ks, nk), v_rsrc = stage_rsrc(v + row0 * vs + h * kD, vs, nk);
+  // the wave's first 8 rows of the tile to load next; its second 8 rows lie 32 behind them
+  uint32_t k_off = stage_lane_off(lane, wave & 1, ks) + 8u * wave * (uint32_t)ks * 2u;
+  uint32_t v_off = stage_lane_off(lane, wave & 1, vs) + 8u * wave * (uint32_t)vs * 2u;
+  constexpr int kRowLoads = 4;   // loads per wave and tile
+  auto issue_row = [&](int t, int region, int j) {   // the j-th of them, of tile t; the tiles are taken in order
+    const int i = j >> 1;
+    const bool is_k = (j & 1) == 0;
+    const uint32_t at = lds0 + (uint32_t)(region * kRegion + (is_k ? 0 : kTileS * kD) + 8 * (wave + 4 * i) * kD) * 2;
+    uint32_t& off = is_k ? k_off : v_off;
+    const int64_t stride = is_k ? ks : vs;
+    if (contig) {
+      stage_rows(at, off, is_k ? k_rsrc : v_rsrc);
+      off += 64u * (uint32_t)stride;
+    } else {
+      stage_each(at, stage_address((is_k ? k : v) + h * kD, stride, rows, start, t * kTileS + 8 * (wave + 4 * i), nk, lane,
+                                   wave & 1));
+    }
+  };
+  auto issue_tile = [&](int t, int region) {
+#pragma unroll
+    for (int j = 0; j < kRowLoads; ++j) issue_row(t, region, j);
+  };
+  issue_tile(0, 0);
+
+  // ---- places in a region (bytes): K and V rows, transposed patches of K
+  const char* const lds = reinterpret_cast<const char*>(smem);
+  uint32_t row_at[4], tr_at[2][2];
+  stage_row_places(lane, row_at);
+  stage_tr_places(lane, tr_at);
+  // The O rows only serve Delta_i = dO_i . O_i (8 lanes per row, 8 elements each), kept in LDS for this kernel and written to
+  // [H, T] for the dK/dV kernel.
+  {
+    u32x4 to[4];
+    // (row st_row + 32 it of the workgroup: as staged)
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
-      *reinterpret_cast<u32x4*>(&smem[(32 * it + st_row) * kPitch + st_col]) = tq[it];
-      *reinterpret_cast<u32x4*>(&smem[kBuf + (32 * it + st_row) * kPitch + st_col]) = tg[it];
+      to[it] = u32x4{0u, 0u, 0u, 0u};
+      const int i = q0 + 32 * it + st_row;
+      if (i < n) to[it] = *reinterpret_cast<const u32x4*>(o + tok_row(rows, start + i) * os + h * kD + st_col);
+    }
+    staged_barrier<0>();
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const int row = 32 * it + st_row;
+      const u32x4 tg = *reinterpret_cast<const u32x4*>(
+          lds + (2 * kRegion + row * kD) * 2 + (((st_col >> 3) ^ stage_swizzle(row)) * 16));
       float acc = 0.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        acc = fmaf(__uint_as_float(tg[it][e] << 16), __uint_as_float(to[it][e] << 16), acc);
-        acc = fmaf(__uint_as_float(tg[it][e] & 0xffff0000u), __uint_as_float(to[it][e] & 0xffff0000u), acc);
+        acc = fmaf(__uint_as_float(tg[e] << 16), __uint_as_float(to[it][e] << 16), acc);
+        acc = fmaf(__uint_as_float(tg[e] & 0xffff0000u), __uint_as_float(to[it][e] & 0xffff0000u), acc);
       }
       acc += __shfl_xor(acc, 1, 64);
       acc += __shfl_xor(acc, 2, 64);
       acc += __shfl_xor(acc, 4, 64);
-      const int i = q0 + 32 * it + st_row;
       if ((tid & 7) == 0) {
-        sDelta[32 * it + st_row] = -acc;
-        if (i < n) delta[(int64_t)h * T + start + i] = acc;
+        sDelta[row] = -acc;
+        if (q0 + row < n) delta[(int64_t)h * T + start + q0 + row] = acc;
       }
     }
-    __syncthreads();
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      bq[s] = lds_read8(&smem[(32 * wave + c) * kPitch + 16 * s + 8 * g]);
-      bg[s] = lds_read8(&smem[kBuf + (32 * wave + c) * kPitch + 16 * s + 8 * g]);
-    }
-    __syncthreads();
   }
+  bf16x8 bq[4], bg[4];   // Q^T, dO^T fragments of the wave's own rows
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    bq[s] = lds_read8(reinterpret_cast<const uint16_t*>(lds + row_at[s] + (kRegion + 32 * wave * kD) * 2));
+    bg[s] = lds_read8(reinterpret_cast<const uint16_t*>(lds + row_at[s] + (2 * kRegion + 32 * wave * kD) * 2));
+  }
+  staged_barrier<0>();   // Delta is in LDS, and nobody reads Q or dO any more
+  issue_tile(1, 1);
   const float nlse2 = q_ok ? -lse[(int64_t)h * T + start + qi] * kLog2e : -INFINITY;   // -inf: P = 0
-  const float ndlt = q_ok ? sDelta[32 * wave + c] : 0.f;
-
-  // ---- streamed K / V tiles
-  const uint16_t* kh = k + h * kD + st_col;
-  const uint16_t* vh = v + h * kD + st_col;
-  u32x4 tk[2], tv[2];
-  const uint32_t koff = ((uint32_t)st_row * (uint32_t)ks + (uint32_t)(h * kD + st_col)) * 2u;
-  const uint32_t voff = ((uint32_t)st_row * (uint32_t)vs + (uint32_t)(h * kD + st_col)) * 2u;
-  auto issue_tile = [&](int j0) {
-    if (contig) {
-      const int left = nk - j0;     // > 0: key rows j0 .. nk-1 exist
-      const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<uint16_t*>(k) + (int64_t)(row0 + j0) * ks, 0, left * (int)ks * 2, kRsrcFlags);
-      const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<uint16_t*>(v) + (int64_t)(row0 + j0) * vs, 0, left * (int)vs * 2, kRsrcFlags);
+  f32x16 ndlt;               // -Delta of the lane's query: the start value of dP
+  {
+    const float d = q_ok ? sDelta[32 * wave + c] : 0.f;
 #pragma unroll
-      for (int it = 0; it < 2; ++it) {
-        tk[it] = __builtin_amdgcn_raw_buffer_load_b128(kr, koff + (uint32_t)it * 64u * (uint32_t)ks, 0, 0);
-        tv[it] = __builtin_amdgcn_raw_buffer_load_b128(vr, voff + (uint32_t)it * 64u * (uint32_t)vs, 0, 0);
-      }
-      return;
-    }
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      tk[it] = tv[it] = u32x4{0u, 0u, 0u, 0u};
-      const int j = j0 + 32 * it + st_row;
-      if (j < nk) {
-        const int64_t gr = tok_row(rows, start + j);
-        tk[it] = *reinterpret_cast<const u32x4*>(kh + gr * ks);
-        tv[it] = *reinterpret_cast<const u32x4*>(vh + gr * vs);
-      }
-    }
-  };
-  auto store_tile = [&](int buf) {
-    uint16_t* bk_ = smem + buf * kBuf;
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      *reinterpret_cast<u32x4*>(&bk_[(32 * it + st_row) * kPitch + st_col]) = tk[it];
-      *reinterpret_cast<u32x4*>(&bk_[kHalf + (32 * it + st_row) * kPitch + st_col]) = tv[it];
-    }
-  };
+    for (int i = 0; i < 16; ++i) ndlt[i] = d;
+    asm volatile("" : "+v"(ndlt));   // (16 registers, which save 16 instructions in every block)
+  }
 
   f32x16 dqacc[2];   // dQ^T: d along accumulator rows, queries along lanes
 #pragma unroll
   for (int i = 0; i < 16; ++i) { dqacc[0][i] = 0.f; dqacc[1][i] = 0.f; }
-  const int tr_i = lane & 15, tr_q = lane >> 4;
-  const int tr_row = (tr_i >> 2) + 4 * (tr_q >> 1);
-  const int tr_col = 16 * (tr_q & 1) + 4 * (tr_i & 3);
-
   f32x16 row_bias;      // (m_h / scale) * (accumulator row) left of the diagonal, its negative right of it
 #pragma unroll
   for (int i = 0; i < 16; ++i) row_bias[i] = k1 * (float)(8 * (i >> 2) + (i & 3));
@@ -557,14 +550,15 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
   // orientation: S^T = K Q^T (bias/scale in the C operand), dP^T = V dO^T (- Delta pre-loaded).  The code
   // that accumulates dQ exists once with no branch around it; a ragged last tile only zeroes the dS of
   // the keys that do not exist.
-  auto kblock = [&](const uint16_t* sK, const uint16_t* sV, int j0, int jb, int rem) {
+  auto kblock = [&](const uint32_t(&ra)[4], const uint32_t(&ta)[2][2], int j0, int jb, int rem) {
+    auto read_row = [&](int what, int s) {   // 0: K, 1: V
+      return lds_read8(reinterpret_cast<const uint16_t*>(lds + ra[s] + (32 * jb + what * kTileS) * (kD * 2)));
+    };
     float fi = (float)(qi - j0 - 4 * g);   // i - j = fi - cj with cj = 32jb + 8*(v/4) + v%4
     asm volatile("" : "+v"(fi));
     f32x16 sacc, pacc;
     const int kb = (j0 >> 5) + jb;
-    const uint16_t* krow = &sK[(32 * jb + c) * kPitch + 8 * g];
-    const uint16_t* vrow = &sV[(32 * jb + c) * kPitch + 8 * g];
-    const bf16x8 ak0 = lds_read8(krow);
+    const bf16x8 ak0 = read_row(0, 0);
     float e0 = nlse2;   // the exponent's constant
     if (kb == qblk) {
       f32x16 diag;
@@ -577,13 +571,11 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
       sacc = mfma32(ak0, bq[0], row_bias);
       e0 = fmaf((kb < qblk ? -k1 : k1) * (fi - (float)(32 * jb)), cs, e0);
     }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) pacc[i] = ndlt;
-    pacc = mfma32(lds_read8(vrow), bg[0], pacc);
+    pacc = mfma32(read_row(1, 0), bg[0], ndlt);
 #pragma unroll
     for (int s = 1; s < 4; ++s) {
-      sacc = mfma32(lds_read8(krow + 16 * s), bq[s], sacc);
-      pacc = mfma32(lds_read8(vrow + 16 * s), bg[s], pacc);
+      sacc = mfma32(read_row(0, s), bq[s], sacc);
+      pacc = mfma32(read_row(1, s), bg[s], pacc);
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) pacc[i] = fast_exp2(fmaf(sacc[i], cs, e0)) * pacc[i];
@@ -598,33 +590,52 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
     for (int kk = 0; kk < 2; ++kk) {
       const bf16x8 bs = pack8(pacc[8 * kk + 0], pacc[8 * kk + 1], pacc[8 * kk + 2], pacc[8 * kk + 3],
                               pacc[8 * kk + 4], pacc[8 * kk + 5], pacc[8 * kk + 6], pacc[8 * kk + 7]);
-      const int roff = (32 * jb + 16 * kk + tr_row) * kPitch + tr_col;
+      const uint32_t at = (32 * jb + 16 * kk) * kD * 2;
 #pragma unroll
       for (int db = 0; db < 2; ++db) {
-        const bf16x8 ak = join_tr(lds_read_tr4(&sK[roff + 32 * db]), lds_read_tr4(&sK[roff + 32 * db + 8 * kPitch]));
+        const bf16x8 ak = join_tr(lds_read_tr4(reinterpret_cast<const uint16_t*>(lds + ta[db][0] + at)),
+                                  lds_read_tr4(reinterpret_cast<const uint16_t*>(lds + ta[db][1] + at)));
         dqacc[db] = mfma32(ak, bs, dqacc[db]);
       }
     }
   };
 
-  issue_tile(0);
-  store_tile(0);
+  // Step jt: tile jt has arrived, the next one is on its way and the one behind that is requested.  Loads past the end are
+  // issued too: their number stays the same.
+  int region = 0;
+  if (!wave_active) {   // (a loop of its own: inside the other one the accumulators would be copied in every step)
+    for (int jt = 0; jt < ntiles; ++jt) {
+      staged_barrier<kRowLoads>();
+      issue_tile(jt + 2, region == 0 ? 2 : region - 1);
+      region = region == 2 ? 0 : region + 1;
+    }
+    staged_barrier<0>();
+    return;
+  }
 #pragma unroll 1
   for (int jt = 0; jt < ntiles; ++jt) {
-    const int j0 = jt * kTileS;
-    __syncthreads();
-    if (jt + 1 < ntiles) issue_tile(j0 + kTileS);
-    if (wave_active) {
-      const uint16_t* sK = smem + (jt & 1) * kBuf;
-      const uint16_t* sV = sK + kHalf;
-      const int rem = nk - j0;
-      kblock(sK, sV, j0, 0, rem);
-      kblock(sK, sV, j0, 1, rem);
+    const int j0 = jt * kTileS, to = region == 0 ? 2 : region - 1;   // of tile jt + 2: the region of tile jt - 1
+    staged_barrier<kRowLoads>();
+    if (!contig) issue_tile(jt + 2, to);
+    uint32_t ra[4], ta[2][2];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) ra[s] = row_at[s] + region * (kRegion * 2);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) ta[s >> 1][s & 1] = tr_at[s >> 1][s & 1] + region * (kRegion * 2);
+    const int rem = nk - j0;
+    if (contig) {
+      issue_row(jt + 2, to, 0);
+      issue_row(jt + 2, to, 1);
     }
-    if (jt + 1 < ntiles) store_tile((jt + 1) & 1);
+    kblock(ra, ta, j0, 0, rem);
+    if (contig) {
+      issue_row(jt + 2, to, 2);
+      issue_row(jt + 2, to, 3);
+    }
+    kblock(ra, ta, j0, 1, rem);
+    region = region == 2 ? 0 : region + 1;
   }
-  __syncthreads();
-  if (!wave_active) return;
+  staged_barrier<0>();
 
   uint16_t* slab = &smem[(32 * wave) * kPitch];
 #pragma unroll
