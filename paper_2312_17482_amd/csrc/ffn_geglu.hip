@@ -500,19 +500,22 @@ __global__ __launch_bounds__(256) void gelu_gate_kernel(const uint16_t* __restri
 // splits) 405 us and 13 us for adding up, where two launches of seven splits each, staged through registers, took 430 and
 // 40 us (means of 20 passes in one run); at 945 tokens (one split, no adding up) 31 us instead of 66 and 34.
 constexpr int kWgRows = 64;                         // tokens per k step
-constexpr int kWgStage = 2 * kWgRows * 256;         // elements: P rows, then Q rows
+// Tiles are 64 kMB x 256: 256 (two stages) or, where those are too few to occupy the compute units, 128 (three stages).
+template <int kMB>
+constexpr int kWgStage = kWgRows * (64 * kMB + 256);   // elements: P rows, then Q rows
 
 struct WgradProblem {
   const uint16_t* P;
   const uint16_t* Q;
   int ldp, ldq;
-  int n_tiles, tiles;   // 256-column tiles of Q, tiles in all
+  int n_tiles, tiles;   // 256-column tiles of Q, tiles in all (of the height at hand)
   float* out;           // its [M, N] floats of the first split
 };
 
+template <int kMB, int kStages>
 __global__ __launch_bounds__(512, 2) void ffn_wgrad_kernel(WgradProblem a, WgradProblem b, int splits, int T_cap,
                                                            const int32_t* __restrict__ meta, int64_t split_pitch) {
-  __shared__ __attribute__((aligned(1024))) uint16_t smem[2 * kWgStage];
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[kStages * kWgStage<kMB>];
   const int T = __builtin_amdgcn_readfirstlane(meta ? min(meta[0], T_cap) : T_cap);
   // workgroup -> split and tile, every XCD a contiguous run: its compute units stream the same token rows
   const int tiles = a.tiles + b.tiles, total = tiles * splits, run = total >> 3;
@@ -525,7 +528,8 @@ __global__ __launch_bounds__(512, 2) void ffn_wgrad_kernel(WgradProblem a, Wgrad
   const int tile = second ? at - a.tiles : at;
   const int n_tiles = pr.n_tiles, ldp = pr.ldp, ldq = pr.ldq;
   const int tile_m = __builtin_amdgcn_readfirstlane(tile / n_tiles);
-  const int m0 = tile_m * 256, n0 = (tile - tile_m * n_tiles) * 256, N = n_tiles * 256;
+  constexpr int kM = 64 * kMB, kLoads = kMB + 4, kMfma = 2 * kMB, kFrags = kMB + 2;
+  const int m0 = tile_m * kM, n0 = (tile - tile_m * n_tiles) * 256, N = n_tiles * 256;
   // steps of this split; steps past the last token read zeros and add nothing
   const int steps_total = (T + kWgRows - 1) / kWgRows;
   const int per = (steps_total + splits - 1) / splits;
@@ -537,77 +541,90 @@ __global__ __launch_bounds__(512, 2) void ffn_wgrad_kernel(WgradProblem a, Wgrad
   const int c = lane & 31, g = lane >> 5;
   const int wm = wave >> 2, wn = wave & 3;
 
-  // Load i of wave w: i < 4 rows 2 (w + 8 i), + 1 of P, else of Q.  Piece x (8 columns) of row r sits at position
-  // x ^ 4 (r % 4): the four rows a transposing read touches lie in different banks.  The descriptor ends with the last
-  // token row, so that rows past T deposit zeros.
-  const int lrow = lane >> 5, piece = (lane & 31) ^ (4 * (2 * (wave & 1) + lrow));
-  const uint32_t plane = ((uint32_t)lrow * (uint32_t)ldp + piece * 8) * 2u;
-  const uint32_t qlane = ((uint32_t)lrow * (uint32_t)ldq + piece * 8) * 2u;
+  // A load carries 1024 bytes, 512 / kM rows of P or two of Q.  Load i of wave w: i < kMB the (w + 8 i)-th of P, else the
+  // (w + 8 (i - kMB))-th of Q.  Piece x (8 columns) of row r sits at position x ^ 4 (r % 4): the four rows a transposing read
+  // touches lie in different banks.  The descriptor ends with the last token row, so that rows past T deposit zeros.
+  constexpr int kPRows = 512 / kM;
+  const int prow = lane / (kM / 8), qrow = lane >> 5;
+  const int ppiece = (lane % (kM / 8)) ^ (4 * ((kPRows * (wave & 1) + prow) & 3));
+  const int qpiece = (lane & 31) ^ (4 * (2 * (wave & 1) + qrow));
+  const uint32_t plane = ((uint32_t)prow * (uint32_t)ldp + ppiece * 8) * 2u;
+  const uint32_t qlane = ((uint32_t)qrow * (uint32_t)ldq + qpiece * 8) * 2u;
   const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t*)smem);
   auto fetch_one = [&](int i, int stage, int step) {
-    const int first = (s_begin + step) * kWgRows + 2 * (wave + 8 * (i & 3));
-    const int rows = max(min(T - first, 2), 0);
-    const int ld = i < 4 ? ldp : ldq;
-    const uint16_t* base = (i < 4 ? pr.P + m0 : pr.Q + n0) + (int64_t)min(first, T) * ld;
-    load_to_lds(lds0 + (stage * kWgStage + (i >> 2) * (kWgRows * 256) + 2 * (wave + 8 * (i & 3)) * 256) * 2,
-                i < 4 ? plane : qlane, raw_rsrc(base, rows > 0 ? (uint32_t)((rows - 1) * ld + 256) * 2u : 0u), 0);
+    const bool is_p = i < kMB;
+    const int per_load = is_p ? kPRows : 2, at = per_load * (wave + 8 * (is_p ? i : i - kMB));
+    const int first = (s_begin + step) * kWgRows + at;
+    int rows = min(T - first, per_load);
+    asm("" : "+s"(rows));   // (else both bounds are one vector instruction, and the descriptor comes out of it too late)
+    rows = max(rows, 0);
+    const int ld = is_p ? ldp : ldq, cols = is_p ? kM : 256;
+    const uint16_t* base = (is_p ? pr.P + m0 : pr.Q + n0) + (int64_t)min(first, T) * ld;
+    load_to_lds(lds0 + (stage * kWgStage<kMB> + (is_p ? 0 : kWgRows * kM) + at * cols) * 2, is_p ? plane : qlane,
+                raw_rsrc(base, rows > 0 ? (uint32_t)((rows - 1) * ld + cols) * 2u : 0u), 0);
   };
 
-  // Fragment reads: lane -> row tr_row (+ 8) and 4 columns of a 16 x 32 patch; P columns 128 wm + 32 mb, Q columns
+  // Fragment reads: lane -> row tr_row (+ 8) and 4 columns of a 16 x 32 patch; P columns 32 (kMB wm + mb), Q columns
   // 64 wn + 32 nb.
   const int tr_i = lane & 15, tr_q = lane >> 4;
   const int tr_row = (tr_i >> 2) + 4 * (tr_q >> 1);
   const int tr_piece = 2 * (tr_q & 1) + ((tr_i & 3) >> 1), tr_sub = 4 * (tr_i & 1);
-  uint32_t foff[6];
+  uint32_t foff[kFrags];
 #pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    const int x = (i < 4 ? 16 * wm + 4 * i : 8 * wn + 4 * (i - 4)) + tr_piece;
-    foff[i] = (i < 4 ? 0 : kWgRows * 256) + tr_row * 256 + ((x ^ (4 * (tr_i >> 2))) * 8) + tr_sub;
+  for (int i = 0; i < kFrags; ++i) {
+    const int x = (i < kMB ? 4 * (kMB * wm + i) : 8 * wn + 4 * (i - kMB)) + tr_piece;
+    foff[i] = (i < kMB ? 0 : kWgRows * kM) + tr_row * (i < kMB ? kM : 256) + ((x ^ (4 * (tr_i >> 2))) * 8) + tr_sub;
   }
-  bf16x8 pf[2][4], qf[2][2];
+  bf16x8 pf[2][kMB], qf[2][2];
   auto read_frag = [&](int stage, int kk, int i) {
-    const uint16_t* p = smem + stage * kWgStage + foff[i] + kk * (16 * 256);
-    const bf16x8 f = join_tr(lds_read_tr4(p), lds_read_tr4(p + 8 * 256));
-    if (i < 4) pf[kk & 1][i] = f;
-    else qf[kk & 1][i - 4] = f;
+    const int cols = i < kMB ? kM : 256;
+    const uint16_t* p = smem + stage * kWgStage<kMB> + foff[i] + kk * (16 * cols);
+    const bf16x8 f = join_tr(lds_read_tr4(p), lds_read_tr4(p + 8 * cols));
+    if (i < kMB) pf[kk & 1][i] = f;
+    else qf[kk & 1][i - kMB] = f;
   };
-  f32x16 acc[4][2];   // [m block][n block]
+  f32x16 acc[kMB][2];   // [m block][n block]
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+  for (int x = 0; x < kMB; ++x)
 #pragma unroll
     for (int y = 0; y < 2; ++y)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
 
 #pragma unroll
-  for (int i = 0; i < 8; ++i) fetch_one(i, 0, 0);
+  for (int st = 0; st < kStages; ++st)
 #pragma unroll
-  for (int i = 0; i < 8; ++i) fetch_one(i, 1, 1);
-  stage_ready<8>();
+    for (int i = 0; i < kLoads; ++i) fetch_one(i, st, st);
+  stage_ready<(kStages - 1) * kLoads>();
 #pragma unroll
-  for (int i = 0; i < 6; ++i) read_frag(0, 0, i);
+  for (int i = 0; i < kFrags; ++i) read_frag(0, 0, i);
   int stage = 0;
   // (the order within a step is that of the projection kernel)
 #pragma unroll 1
   for (int st = 0; st < nsteps; ++st) {
+    const int next = stage + 1 == kStages ? 0 : stage + 1;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      if (kk == 3) stage_ready<0>();
+      if (kk == 3) stage_ready<(kStages - 2) * kLoads>();
 #pragma unroll
-      for (int x = 0; x < 8; ++x) {
-        if (x < 6) read_frag(kk == 3 ? stage ^ 1 : stage, (kk + 1) & 3, x);
-        if (kk == 3) fetch_one(x, stage, st + 2);
+      for (int x = 0; x < kMfma; ++x) {
+#pragma unroll
+        for (int i = x; i < kFrags; i += kMfma) read_frag(kk == 3 ? next : stage, (kk + 1) & 3, i);
+        if (kk == 3) {
+#pragma unroll
+          for (int i = x; i < kLoads; i += kMfma) fetch_one(i, stage, st + kStages);
+        }
         __builtin_amdgcn_sched_barrier(0);
         acc[x >> 1][x & 1] = mfma32(pf[kk & 1][x >> 1], qf[kk & 1][x & 1], acc[x >> 1][x & 1]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    stage ^= 1;
+    stage = next;
   }
   // fp32 tile: register v of block (x, y) is row 8 (v / 4) + 4 g + v % 4, lane c is the column
-  float* dst = pr.out + split * split_pitch + (int64_t)(m0 + wm * 128) * N + n0 + wn * 64 + c;
+  float* dst = pr.out + split * split_pitch + (int64_t)(m0 + wm * (32 * kMB)) * N + n0 + wn * 64 + c;
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+  for (int x = 0; x < kMB; ++x)
 #pragma unroll
     for (int y = 0; y < 2; ++y)
 #pragma unroll
@@ -776,29 +793,42 @@ static void launch_wgrad(const void* dy, const void* act, const void* dhg, const
                          int T_cap, const int32_t* meta, float* partial, size_t room, float* dw2, float* dw1v,
                          hipStream_t stream) {
   const int64_t size_a = (int64_t)hidden * inter, size_b = 2 * size_a;
-  // The split with the least estimated time: rounds over the compute units (about 1.5 us a step of 64 tokens and 6 us
-  // before and after), and the partial tiles' way through memory at 4.5 TB/s.  (The whole backward at 26963 tokens with
-  // 1, 2, 3, 4 splits: 1354, 1165, 1239, 1185 us; at 945 tokens 92, 105, 116, 121 us.)
+  // The tile height and the split with the least estimated time: rounds over the compute units (about 1.5 us a step of 64
+  // tokens and 6 us before and after, 1.1 us a step in tiles of half the height), and the partial tiles' way through memory
+  // at 4.5 TB/s.  (The whole backward at 26963 tokens with 1, 2, 3, 4 splits: 1354, 1165, 1239, 1185 us; at 945 tokens 92,
+  // 105, 116, 121 us.)  Half the height occupies the compute units where the tiles are few: one split, 256 and 128 rows,
+  // 768 x 3072 (108 and 216 tiles) 200 tokens 14.2 and 11.8 us, 945 tokens 29.9 and 22.9, 2500 tokens 67.6 and 47.6; 8000 tokens
+  // in two splits 137 and 167; 256 x 1024 (12 and 24 tiles), 945 tokens in three splits 20.5 and 16.7.
   // Fewer splits are longer chains of fp32 additions, T / (16 splits) of them: against 64 bits on its own bf16 operands dW2
   // is off by 1.8e-7 (945 tokens, one split) and 7.4e-7 (26963, two) where seven splits gave 0.9e-7 and 3.9e-7.  Both are a
-  // thousandth and less of the 2^-9 that the operands were rounded by.
-  const int tiles_a = hidden / 256 * (inter / 256), tiles = 3 * tiles_a, steps = (T_cap + kWgRows - 1) / kWgRows;
-  int splits = 1;
+  // thousandth and less of the 2^-9 that the operands were rounded by.  So half the height comes with as many splits at
+  // least (4000 tokens in one split would be 73 us instead of 81).
+  const int tiles_a = hidden / 256 * (inter / 256), steps = (T_cap + kWgRows - 1) / kWgRows;
+  int splits = 1, height = 4;
   double least = 1e300;
-  for (int s = 1; s <= kWgradSplits && (size_t)s * (size_t)(size_a + size_b) <= room; ++s) {
-    const double cost = (double)((tiles * s + kComputeUnits - 1) / kComputeUnits) * (1.5 * ((steps + s - 1) / s) + 6.0) +
-                        (s > 1 ? 4.0 + 4.0 * (2 * s + 1) * (size_a + size_b) / 4.5e6 : 0.0);
-    if (cost < least) {
-      least = cost;
-      splits = s;
+  for (int mb = 4; mb >= 2; mb -= 2) {
+    const int tiles = 3 * tiles_a * (4 / mb);
+    for (int s = splits; s <= kWgradSplits && (size_t)s * (size_t)(size_a + size_b) <= room; ++s) {
+      const double cost =
+          (double)((tiles * s + kComputeUnits - 1) / kComputeUnits) * ((mb == 4 ? 1.5 : 1.1) * ((steps + s - 1) / s) + 6.0) +
+          (s > 1 ? 4.0 + 4.0 * (2 * s + 1) * (size_a + size_b) / 4.5e6 : 0.0);
+      if (cost < least) {
+        least = cost;
+        splits = s;
+        height = mb;
+      }
     }
   }
   const bool whole = splits == 1;   // the tiles are the result
+  const int per_256 = 4 / height, tiles = 3 * tiles_a * per_256;
   const WgradProblem a{static_cast<const uint16_t*>(dy), static_cast<const uint16_t*>(act), hidden, inter, inter / 256,
-                       tiles_a, whole ? dw2 : partial};
+                       tiles_a * per_256, whole ? dw2 : partial};
   const WgradProblem b{static_cast<const uint16_t*>(dhg), static_cast<const uint16_t*>(x), 2 * inter, hidden,
-                       hidden / 256, 2 * tiles_a, whole ? dw1v : partial + size_a};
-  ffn_wgrad_kernel<<<dim3(tiles * splits), dim3(512), 0, stream>>>(a, b, splits, T_cap, meta, size_a + size_b);
+                       hidden / 256, 2 * tiles_a * per_256, whole ? dw1v : partial + size_a};
+  if (height == 4)
+    ffn_wgrad_kernel<4, 2><<<dim3(tiles * splits), dim3(512), 0, stream>>>(a, b, splits, T_cap, meta, size_a + size_b);
+  else
+    ffn_wgrad_kernel<2, 3><<<dim3(tiles * splits), dim3(512), 0, stream>>>(a, b, splits, T_cap, meta, size_a + size_b);
   if (!whole)
     ffn_wgrad_reduce_kernel<<<dim3(2048), dim3(256), 0, stream>>>(partial, splits, size_a / 4, size_b / 4, dw2, dw1v);
 }

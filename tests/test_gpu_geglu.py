@@ -322,3 +322,29 @@ def test_geglu_backward_of_many_tiles(mb, T, hidden, inter, counted):
         print("  %s rel_fro %.2e max %.2e" % (name, rel, err), flush=True)
         assert rel <= 1e-2 and err <= 2.0 ** -6, name
     assert ((dw2.double() - ref[2]).norm() / ref[2].norm()).item() <= 2.0 ** -24 * (T / 32) ** 0.5
+
+
+# numbers of 64-token steps around the three stages of the half-height weight-gradient tiles, and their last rows
+@pytest.mark.parametrize("T", [1, 63, 64, 65, 128, 129, 192, 193, 257, 400])
+def test_weight_gradients_of_few_tokens(mb, T):
+    """dW2 against 64 bits on its own operands (a chain of fp32 sums, each at most 2^-24 of what has been added up: within
+    2^-22 of the norm for so few tokens), the other gradients as above; rows past the last token hold NaN."""
+    print("weight gradients T=%d" % T, flush=True)
+    hidden, inter = 512, 768
+    gen = torch.Generator(device="cuda").manual_seed(T)
+
+    def normal(*shape, std=1.0):
+        return (torch.randn(shape, generator=gen, device="cuda") * std).bfloat16()
+    x, w1v, w2, dy = normal(T + 70, hidden), normal(2 * inter, hidden, std=0.03), normal(hidden, inter, std=0.03), normal(T + 70, hidden)
+    x[T:], dy[T:] = float("nan"), float("nan")
+    act = torch.full((T + 70, inter), float("nan"), dtype=torch.bfloat16, device="cuda")
+    meta = torch.tensor([T, 0], dtype=torch.int32, device="cuda")
+    mb.mb_geglu_fwd(x, w1v, w2, meta=meta, act=act)
+    counted = mb.mb_geglu_bwd(dy, x, w1v, w2, act, meta=meta)
+    exact = mb.mb_geglu_bwd(dy[:T], x[:T], w1v, w2, act[:T])
+    ref = backward_in_64_bits(x[:T], w1v, w2, dy[:T], act[:T])
+    for got in (counted, exact):
+        for name, a, b in zip(("dx", "dw1v", "dw2"), got, ref):
+            a = a[:T] if name == "dx" else a
+            rel = ((a.double() - b).norm() / b.norm()).item()
+            assert rel <= (2.0 ** -22 if name == "dw2" else 1e-2), (name, rel)
