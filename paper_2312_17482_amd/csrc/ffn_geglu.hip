@@ -98,16 +98,21 @@ constexpr int kGemmLds = kStages * (64 * kMB + 32 * kWN * kNB) * kBK + 2 * kWN *
 // blockIdx.x, + gridDim.x, ...  A tile is 64 kMB tokens x 32 kWN kNB weight rows; a wave computes 32 kMB x 32 kNB of it.
 // Wide (4 x 2 blocks, two stages): 64 to 320 tokens x 256.  Narrow (2 x 1 blocks, eight stages): 64 x 64 for products of
 // few rows and columns, whose time is the latency of a step: a sixteenth of the bytes per step, seven steps in flight.
-// X rows and W rows are both K elements long.  kPartial: the contraction is split, tile id = split * tiles + tile, and
+// X rows are K elements long.  The weight is stored by output column, rows of K elements (kWT false), or the other way round,
+// K rows of ldw elements with the output columns along them (kWT: the weights of the forward, contracted over their other
+// index): then a stage holds 64 of its rows as they are, and the matrix-core operand (8 consecutive k of one column per
+// lane) comes out of transposing LDS reads, which take no longer (and no transposed copies are made of 14 MB of weights:
+// 10 us a call at 768 x 3072).  kPartial: the contraction is split, tile id = split * tiles + tile, and
 // the split's fp32 sums go to out (as float) + split * T_cap * ldo.
-template <int kMode, int kMB, int kWN, int kNB, int kStages>
-__device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int K,
+template <int kMode, bool kWT, int kMB, int kWN, int kNB, int kStages>
+__device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int K, int ldw,
                                            int n_tiles, int splits, int gate_row, int w_rows, int T, int T_cap,
                                            uint16_t* __restrict__ out, int ldo, const uint16_t* __restrict__ aux,
                                            int gate_col, uint16_t* __restrict__ smem) {
   constexpr bool kGated = kMode == kGatedFwd;
   constexpr int kBM = 64 * kMB, kBN = 32 * kWN * kNB, kWaves = 2 * kWN;
-  static_assert(!kGated || kNB == 2, "the gated epilogue pairs the wave's two weight blocks");
+  static_assert(!kGated || (kNB == 2 && !kWT), "the gated epilogue pairs the wave's two weight blocks");
+  static_assert(!kWT || kBN == 256 || kBN == 64, "swizzles of a weight row");
   constexpr int kRows = kBM + kBN;                  // rows of a stage: tokens, then weight rows
   constexpr int kStageElems = kRows * kBK;
   constexpr int kLoads = kRows / (8 * kWaves);      // 8-row loads per wave and k step
@@ -157,14 +162,30 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
       ((uint32_t)(lane >> 3) * (uint32_t)K + (((lane & 7) ^ (4 * (wave & 1) + (lane >> 4))) * 8)) * 2u;
   const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(
       (__attribute__((address_space(3))) uint16_t*)smem);
+  // kWT: a load of the weight carries 512 / kBN of its rows.  Piece x of row r sits at x ^ 4 (r % 4) (rows of 512 bytes)
+  // or x ^ 4 (r / 2 % 2) (rows of 128 bytes): the four rows that a transposing read touches lie in different banks.
+  constexpr int kTRows = 512 / kBN;
+  constexpr int kXLoads = kBM / (8 * kWaves);       // the first kXLoads of a wave's loads are token rows
+  const int trow = lane / (kBN / 8);
+  auto tr_swizzle = [](int r) { return kBN == 256 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); };
+  static_assert(!kWT || kTRows * kWaves % 4 == 0, "a lane's swizzle is the same in all its loads");
+  const uint32_t wlane_off = ((uint32_t)trow * (uint32_t)ldw +
+                              (((lane % (kBN / 8)) ^ tr_swizzle(kTRows * wave + trow)) * 8)) * 2u;
   u32x4 rsrc[kLoads];
-  uint32_t k_bytes = 0;              // scalar offset of the tile's first k step
+  uint32_t k_bytes = 0;              // scalar offset of the tile's first k step, in X and in a weight stored by column
+  uint32_t wk_bytes = 0;             // the same in a weight stored by k
   auto aim = [&](int id) {           // descriptors of this wave's share of a tile's rows
     int m0, n0, k0;
     locate(id, m0, n0, k0);
     k_bytes = (uint32_t)k0 * (kBK * 2);
+    wk_bytes = (uint32_t)k0 * (uint32_t)(kBK * 2) * (uint32_t)ldw;
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
+      if (kWT && i >= kXLoads) {   // (all K rows and all kBN columns exist)
+        const int row = kTRows * (wave + kWaves * (i - kXLoads));
+        rsrc[i] = raw_rsrc(W + (int64_t)row * ldw + n0, 0x7fffffffu);
+        continue;
+      }
       const int row = 8 * (wave + kWaves * i), r = row - kBM;   // r: row of the weight tile
       const bool token = row < kBM;
       const int first = token ? m0 + row : kGated ? (r < kBN / 2 ? n0 + r : gate_row + n0 + r - kBN / 2) : n0 + r;
@@ -173,7 +194,9 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
     }
   };
   auto fetch_one = [&](int i, int stage, int kt) {
-    load_to_lds(lds0 + (stage * kStageElems + 8 * (wave + kWaves * i) * kBK) * 2, lane_off, rsrc[i], k_bytes + kt * (kBK * 2));
+    const bool by_k = kWT && i >= kXLoads;
+    load_to_lds(lds0 + (stage * kStageElems + 8 * (wave + kWaves * i) * kBK) * 2, by_k ? wlane_off : lane_off, rsrc[i],
+                by_k ? wk_bytes + (uint32_t)kt * (uint32_t)(kBK * 2) * (uint32_t)ldw : k_bytes + kt * (kBK * 2));
   };
 
   // Fragments of this wave inside a stage: tokens at rows 0 .., weight rows from kBM on.  Gated: the first weight block
@@ -196,10 +219,24 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
     wfrag[kk] = wrow + frag[kk];
     if (kKeepSums) asm volatile("" : "+v"(xfrag[kk]), "+v"(wfrag[kk]));
   }
+  // kWT: weight columns 32 (kNB wn + i) .., rows 16 kk + 8 g .. of the stage; lane -> row (+ 4) and 4 columns
+  uint32_t tfrag[kNB];
+  {
+    const int tr_i = lane & 15, tr_q = lane >> 4;
+    const int r = (tr_i >> 2) + 8 * (tr_q >> 1);
+#pragma unroll
+    for (int i = 0; i < kNB; ++i) {
+      const int x = 4 * (kNB * wn + i) + 2 * (tr_q & 1) + ((tr_i & 3) >> 1);
+      tfrag[i] = kBM * kBK + r * kBN + ((x ^ tr_swizzle(r)) * 8) + 4 * (tr_i & 1);
+    }
+  }
   bf16x8 xf[2][kMB], wf[2][kNB];
   auto read_frag = [&](int stage, int kk, int i) {   // weight fragments first
     const uint16_t* cur = smem + stage * kStageElems;
-    if (i < kNB) wf[kk & 1][i] = lds_read8(cur + wfrag[kk] + i * kWBlock);
+    if (kWT && i < kNB) {
+      const uint16_t* p = cur + tfrag[i] + kk * (16 * kBN);
+      wf[kk & 1][i] = join_tr(lds_read_tr4(p), lds_read_tr4(p + 4 * kBN));
+    } else if (i < kNB) wf[kk & 1][i] = lds_read8(cur + wfrag[kk] + i * kWBlock);
     else xf[kk & 1][i - kNB] = lds_read8(cur + xfrag[kk] + (i - kNB) * 32 * kBK);
   };
   constexpr int kFrags = kMB + kNB, kMfma = kMB * kNB;
@@ -377,9 +414,10 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
   stage_ready<0>();   // no load may still be on its way to LDS that the next workgroup owns
 }
 
-template <int kMode, int kMB, int kWN, int kNB, int kStages>
+template <int kMode, bool kWT, int kMB, int kWN, int kNB, int kStages>
 __global__ __launch_bounds__(128 * kWN, kWN / 2) void ffn_gemm_kernel(const uint16_t* __restrict__ X,
-                                                                      const uint16_t* __restrict__ W, int K, int n_tiles,
+                                                                      const uint16_t* __restrict__ W, int K, int ldw,
+                                                                      int n_tiles,
                                                                       int splits, int gate_row, int w_rows, int T_cap,
                                                                       const int32_t* __restrict__ meta,
                                                                       uint16_t* __restrict__ out, int ldo,
@@ -387,7 +425,7 @@ __global__ __launch_bounds__(128 * kWN, kWN / 2) void ffn_gemm_kernel(const uint
   __shared__ __attribute__((aligned(1024))) uint16_t smem[kGemmLds<kMB, kWN, kNB, kStages>];
   // (readfirstlane: tells the compiler the value is wave-uniform, so descriptors built from it stay scalar)
   const int T = __builtin_amdgcn_readfirstlane(meta ? min(meta[0], T_cap) : T_cap);
-  gemm_tiles<kMode, kMB, kWN, kNB, kStages>(X, W, K, n_tiles, splits, gate_row, w_rows, T, T_cap, out, ldo, aux, gate_col,
+  gemm_tiles<kMode, kWT, kMB, kWN, kNB, kStages>(X, W, K, ldw, n_tiles, splits, gate_row, w_rows, T, T_cap, out, ldo, aux, gate_col,
                                             smem);
 }
 
@@ -436,9 +474,9 @@ static TileHeights tile_heights(int T_cap, int n_tiles, int splits) {
 // on the host, whose choice is the worse the emptier the buffers are (in 32768 rows: 16384 tokens, K = 3072, 768 columns, 87
 // and 69 us; 945 tokens, K = 768, 2304 columns, 21.2 and 9.7 us).  Out of a table and not by the estimates: their code is
 // cold and took 1 us in front of every product.
-template <int kMode>
+template <int kMode, bool kWT>
 __global__ __launch_bounds__(512, 2) void ffn_gemm_counted_kernel(const uint16_t* __restrict__ X,
-                                                                  const uint16_t* __restrict__ W, int K, int n_tiles,
+                                                                  const uint16_t* __restrict__ W, int K, int ldw, int n_tiles,
                                                                   int splits, int gate_row, int w_rows, int T_cap,
                                                                   const int32_t* __restrict__ meta,
                                                                   uint16_t* __restrict__ out, int ldo,
@@ -447,7 +485,7 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_counted_kernel(const uint16_t
   __shared__ __attribute__((aligned(1024))) uint16_t smem[kGemmLds<5, 4, 2, 2>];
   const int T = __builtin_amdgcn_readfirstlane(min(meta[0], T_cap));
 #define MB_TILE(n) \
-  gemm_tiles<kMode, n, 4, 2, 2>(X, W, K, n_tiles, splits, gate_row, w_rows, T, T_cap, out, ldo, aux, gate_col, smem)
+  gemm_tiles<kMode, kWT, n, 4, 2, 2>(X, W, K, ldw, n_tiles, splits, gate_row, w_rows, T, T_cap, out, ldo, aux, gate_col, smem)
   const int at = (max(T, 1) - 1) >> heights.shift;
   const uint64_t word = at < 32 ? (at < 16 ? heights.word[0] : heights.word[1])
                                 : (at < 48 ? heights.word[2] : heights.word[3]);
@@ -670,32 +708,19 @@ __global__ __launch_bounds__(256) void add_splits_kernel(const float* __restrict
   }
 }
 
-// out[c][r] = in[r][c] for a [R, C] bf16 matrix (R, C multiples of 64): 64 x 64 tiles through LDS.
-__global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* __restrict__ in, int R, int C,
-                                                        uint16_t* __restrict__ out) {
-  __shared__ uint16_t tile[64][66];
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) tile[4 * i + ty][tx] = in[(int64_t)(r0 + 4 * i + ty) * C + c0 + tx];
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 16; ++i) out[(int64_t)(c0 + 4 * i + ty) * R + r0 + tx] = tile[tx][4 * i + ty];
-}
-
 }  // namespace
 
-template <int kMode, int kMB, int kWN, int kNB, int kStages>
+template <int kMode, bool kWT, int kMB, int kWN, int kNB, int kStages>
 static void launch_gemm_tile(const void* x, const void* wt, int K, int n_cols, int splits, int gate_row, int w_rows,
                              int T_cap, const int32_t* meta, void* out, int ldo, const uint16_t* aux, int gate_col,
                              hipStream_t stream) {
   constexpr int kBN = 32 * kWN * kNB;
   const int m_tiles = (T_cap + 64 * kMB - 1) / (64 * kMB), n_tiles = (n_cols + kBN - 1) / kBN;
   const int64_t total = (int64_t)m_tiles * n_tiles * splits;
-  ffn_gemm_kernel<kMode, kMB, kWN, kNB, kStages>
+  ffn_gemm_kernel<kMode, kWT, kMB, kWN, kNB, kStages>
       <<<dim3((unsigned)(total < kComputeUnits ? total : kComputeUnits)), dim3(128 * kWN), 0, stream>>>(
-          static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_tiles, splits, gate_row, w_rows, T_cap,
-          meta, static_cast<uint16_t*>(out), ldo, aux, gate_col);
+          static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_cols, n_tiles, splits, gate_row, w_rows,
+          T_cap, meta, static_cast<uint16_t*>(out), ldo, aux, gate_col);
 }
 
 // Estimated microseconds of a product in tiles of the best height, `splits` shares of the contraction.
@@ -704,20 +729,20 @@ static double gemm_cost(int T_cap, int n_cols, int K, int splits) {
   return 0.01 * (double)height_cost(T_cap, n_tiles, splits, tile_height(T_cap, n_tiles, splits)) * (K / (kBK * splits));
 }
 
-template <int kMode>
+template <int kMode, bool kWT = false>
 static void launch_gemm(const void* x, const void* wt, int K, int n_cols, int splits, int gate_row, int w_rows, int T_cap,
                         const int32_t* meta, void* out, int ldo, const uint16_t* aux, int gate_col, hipStream_t stream) {
   const int n_tiles = (n_cols + 255) / 256;
   if (meta) {
     // as many workgroups as the lowest tiles of a full buffer would take, one per compute unit at most
     const int64_t most = (int64_t)((T_cap + 63) / 64) * n_tiles * splits;
-    ffn_gemm_counted_kernel<kMode><<<dim3((unsigned)(most < kComputeUnits ? most : kComputeUnits)), dim3(512), 0, stream>>>(
-        static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_tiles, splits, gate_row, w_rows, T_cap,
+    ffn_gemm_counted_kernel<kMode, kWT><<<dim3((unsigned)(most < kComputeUnits ? most : kComputeUnits)), dim3(512), 0, stream>>>(
+        static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_cols, n_tiles, splits, gate_row, w_rows, T_cap,
         meta, static_cast<uint16_t*>(out), ldo, aux, gate_col, tile_heights(T_cap, n_tiles, splits));
     return;
   }
 #define MB_TILE(n) \
-  launch_gemm_tile<kMode, n, 4, 2, 2>(x, wt, K, n_cols, splits, gate_row, w_rows, T_cap, meta, out, ldo, aux, gate_col, stream)
+  launch_gemm_tile<kMode, kWT, n, 4, 2, 2>(x, wt, K, n_cols, splits, gate_row, w_rows, T_cap, meta, out, ldo, aux, gate_col, stream)
   switch (tile_height(T_cap, n_tiles, splits)) {
     case 1: MB_TILE(1); break;
     case 2: MB_TILE(2); break;
@@ -731,15 +756,16 @@ static void launch_gemm(const void* x, const void* wt, int K, int n_cols, int sp
 // out[t, n] = sum_k x[t, k] * wt[n, k] with the plain epilogue; in narrow tiles where their estimate (0.23 us a step, 1.5 us
 // a tile) is less: 945 x 768, K = 3072: 37 us in tiles of 64 x 256, 14 us in 64 x 64; 300 x 768, K = 768: 8.0 and 6.0 us;
 // 2000 x 768, K = 768 (two rounds of narrow tiles): 8.7 and 9.9 us.
+template <bool kWT = false>
 static void launch_plain(const void* x, const void* wt, int T_cap, const int32_t* meta, int n_in, int n_out, void* y,
                          hipStream_t stream) {
   const int64_t narrow = (int64_t)((T_cap + 63) / 64) * (n_out / 64);
   const double cost = (double)((narrow + kComputeUnits - 1) / kComputeUnits) * (0.23 * (n_in / kBK) + 1.5);
   if (cost < gemm_cost(T_cap, n_out, n_in, 1)) {
-    launch_gemm_tile<kPlain, 1, 2, 1, 8>(x, wt, n_in, n_out, 1, 0, n_out, T_cap, meta, y, n_out, nullptr, 0, stream);
+    launch_gemm_tile<kPlain, kWT, 1, 2, 1, 8>(x, wt, n_in, n_out, 1, 0, n_out, T_cap, meta, y, n_out, nullptr, 0, stream);
     return;
   }
-  launch_gemm<kPlain>(x, wt, n_in, n_out, 1, 0, n_out, T_cap, meta, y, n_out, nullptr, 0, stream);
+  launch_gemm<kPlain, kWT>(x, wt, n_in, n_out, 1, 0, n_out, T_cap, meta, y, n_out, nullptr, 0, stream);
 }
 
 mb_status launch_geglu_fwd(const void* x, const void* w1v, const void* w2, int T_cap, const int32_t* meta,
@@ -768,22 +794,19 @@ mb_status launch_gelu_gate(const void* h, const void* gate, int64_t ld, int T_ca
   return check_launch("gelu_gate_kernel");
 }
 
-// Workspace of the backward: h|g recomputed, dh|dg, the two transposed weight matrices, the partial
-// weight-gradient tiles.
+// Workspace of the backward: h|g recomputed, dh|dg, the partial weight-gradient tiles.
 static constexpr int kWgradSplits = 7;
-static size_t bwd_ws_layout(int T_cap, int hidden, int inter, size_t off[5]) {
+static size_t bwd_ws_layout(int T_cap, int hidden, int inter, size_t off[3]) {
   size_t at = 0;
   const size_t rows = (size_t)T_cap * 2 * inter * 2;
   off[0] = at; at += align_up(rows, 256);                                   // hg   [T_cap, 2 inter] bf16
   off[1] = at; at += align_up(rows, 256);                                   // dhg  [T_cap, 2 inter] bf16
-  off[2] = at; at += align_up((size_t)inter * hidden * 2, 256);             // w2 transposed [inter, hidden]
-  off[3] = at; at += align_up((size_t)2 * inter * hidden * 2, 256);         // w1v transposed [hidden, 2 inter]
-  off[4] = at; at += align_up((size_t)kWgradSplits * 2 * inter * hidden * 4, 256);   // partial tiles, fp32
+  off[2] = at; at += align_up((size_t)kWgradSplits * 2 * inter * hidden * 4, 256);   // partial tiles, fp32
   return at;
 }
 
 size_t geglu_bwd_workspace_bytes(int T_cap, int hidden, int inter) {
-  size_t off[5];
+  size_t off[3];
   return bwd_ws_layout(T_cap, hidden, inter, off);
 }
 
@@ -836,24 +859,17 @@ static void launch_wgrad(const void* dy, const void* act, const void* dhg, const
 mb_status launch_geglu_bwd(const void* dy, const void* x, const void* w1v, const void* w2, const void* act,
                            const void* hg_saved, int T_cap, const int32_t* meta, int hidden, int inter, void* dx,
                            float* dw1v, float* dw2, void* workspace, hipStream_t stream) {
-  size_t off[5];
+  size_t off[3];
   bwd_ws_layout(T_cap, hidden, inter, off);
   char* ws = static_cast<char*>(workspace);
   const uint16_t* hg = hg_saved ? static_cast<const uint16_t*>(hg_saved) : reinterpret_cast<uint16_t*>(ws + off[0]);
   uint16_t* dhg = reinterpret_cast<uint16_t*>(ws + off[1]);
-  uint16_t* w2t = reinterpret_cast<uint16_t*>(ws + off[2]);
-  uint16_t* w1vt = reinterpret_cast<uint16_t*>(ws + off[3]);
-  float* partial = reinterpret_cast<float*>(ws + off[4]);
-  // the weight matrices the data gradients contract over their OTHER index
-  transpose_kernel<<<dim3(inter / 64, hidden / 64), dim3(256), 0, stream>>>(static_cast<const uint16_t*>(w2), hidden,
-                                                                           inter, w2t);
-  transpose_kernel<<<dim3(hidden / 64, 2 * inter / 64), dim3(256), 0, stream>>>(static_cast<const uint16_t*>(w1v),
-                                                                               2 * inter, hidden, w1vt);
+  float* partial = reinterpret_cast<float*>(ws + off[2]);
   if (T_cap > 0) {
     // h | g = x (W1 | V): handed over by a caller that stored it, else computed again
     if (!hg_saved) launch_plain(x, w1v, T_cap, meta, hidden, 2 * inter, ws + off[0], stream);
     // dA = dy W2^T, and on its way out  dh = dA g GeLU'(h),  dg = dA GeLU(h)
-    launch_gemm<kGateBwd>(dy, w2t, hidden, inter, 1, 0, inter, T_cap, meta, dhg, 2 * inter, hg, inter, stream);
+    launch_gemm<kGateBwd, true>(dy, w2, hidden, inter, 1, 0, inter, T_cap, meta, dhg, 2 * inter, hg, inter, stream);
     // dx = dh W1^T + dg V^T = (dh | dg) (W1 | V)^T: the longest contraction onto the fewest columns.  With few tokens its
     // tiles leave most compute units idle, so the contraction is split where that pays for adding up the shares
     // (945 tokens, 768 x 3072: 74 us in one piece, 25 us in 8 shares); the partial sums lie where the weight
@@ -870,9 +886,9 @@ mb_status launch_geglu_bwd(const void* dy, const void* x, const void* w1v, const
       }
     }
     if (splits == 1) {
-      launch_plain(dhg, w1vt, T_cap, meta, 2 * inter, hidden, dx, stream);
+      launch_plain<true>(dhg, w1v, T_cap, meta, 2 * inter, hidden, dx, stream);
     } else {
-      launch_gemm<kPartial>(dhg, w1vt, 2 * inter, hidden, splits, 0, hidden, T_cap, meta, partial, hidden, nullptr, 0,
+      launch_gemm<kPartial, true>(dhg, w1v, 2 * inter, hidden, splits, 0, hidden, T_cap, meta, partial, hidden, nullptr, 0,
                             stream);
       const int64_t pieces = (int64_t)T_cap * hidden / 4;
       add_splits_kernel<<<dim3((unsigned)(pieces < 256 * 1024 ? (pieces + 255) / 256 : 1024)), dim3(256), 0, stream>>>(
