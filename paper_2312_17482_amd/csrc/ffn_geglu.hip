@@ -10,7 +10,7 @@
 //   2. plain:  y = a W2 with the [hidden, inter] matrix W2^T.
 //
 // Tiling: 64 to 320 tokens x 256 weight rows per workgroup of 8 waves (2 x 4, each up to 160 x 64 = 10 accumulator tiles
-// of v_mfma_f32_32x32x16_bf16), k in steps of 64 through two LDS stages that are filled by loads straight from
+// of v_mfma_f32_32x32x16_bf16), k in steps of 64 through two or three LDS stages that are filled by loads straight from
 // global memory.  One workgroup per compute unit walks its tiles without a break in the stream of loads.
 // The products are formed transposed (weight rows along accumulator rows, tokens along lanes), so a
 // lane owns runs of 4 consecutive output columns of one token; the tile is turned into row segments through a
@@ -93,6 +93,13 @@ constexpr int kSlabElems = 32 * 32;   // per wave: 32 tokens x 32 columns on the
 // LDS of a tile shape, elements: kStages stages of 64 kMB token rows and 32 kWN kNB weight rows, and the waves' slabs.
 template <int kMB, int kWN, int kNB, int kStages>
 constexpr int kGemmLds = kStages * (64 * kMB + 32 * kWN * kNB) * kBK + 2 * kWN * kSlabElems;
+
+// Wide tiles of 64 and 128 tokens leave room for a third stage, which pays from this many k steps on where the weights come
+// from memory (two and three stages, 40 and more weights in turn; 64-token tiles: 8 steps 945 x 1536 8.6 and 7.5 us, 12 steps
+// 1500 x 768 11.5 and 9.2, 200 x 6144 15.5 and 12.1, 48 steps 4000 x 768 51 and 35, 4 steps 5.9 and 5.9; 128-token tiles: 12
+// steps 2500 x 2304 18.0 and 15.5, 945 x 6144 18.9 and 16.3, 16 steps 1500 x 3072 22.8 and 18.1).  Out of a warm L2 it costs
+// 0.3 us up to 12 steps.
+constexpr int kThirdStageFrom = 8;
 
 // One workgroup of 2 kWN waves (2 along the tokens by kWN along the weight rows) per compute unit walks the tiles
 // blockIdx.x, + gridDim.x, ...  A tile is 64 kMB tokens x 32 kWN kNB weight rows; a wave computes 32 kMB x 32 kNB of it.
@@ -211,7 +218,7 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
   constexpr uint32_t kWBlock = (kGated ? kBN / 2 : 32) * kBK;   // from the first weight block of the wave to the second
   // (Narrow: a step is a chain of latencies, so the sums are kept and one addition per read is left.  1000 x 768, K = 3072:
   // 13.9 us with the additions as the compiler orders them, 13.3 us so.)
-  constexpr bool kKeepSums = kStages > 2;
+  constexpr bool kKeepSums = kWN == 2;
   uint32_t xfrag[4], wfrag[4];
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
@@ -416,12 +423,11 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
 
 template <int kMode, bool kWT, int kMB, int kWN, int kNB, int kStages>
 __global__ __launch_bounds__(128 * kWN, kWN / 2) void ffn_gemm_kernel(const uint16_t* __restrict__ X,
-                                                                      const uint16_t* __restrict__ W, int K, int ldw,
-                                                                      int n_tiles,
+                                                                      const uint16_t* __restrict__ W, int K, int n_tiles,
                                                                       int splits, int gate_row, int w_rows, int T_cap,
                                                                       const int32_t* __restrict__ meta,
                                                                       uint16_t* __restrict__ out, int ldo,
-                                                                      const uint16_t* __restrict__ aux, int gate_col) {
+                                                                      const uint16_t* __restrict__ aux, int gate_col, int ldw) {
   __shared__ __attribute__((aligned(1024))) uint16_t smem[kGemmLds<kMB, kWN, kNB, kStages>];
   // (readfirstlane: tells the compiler the value is wave-uniform, so descriptors built from it stay scalar)
   const int T = __builtin_amdgcn_readfirstlane(meta ? min(meta[0], T_cap) : T_cap);
@@ -476,25 +482,32 @@ static TileHeights tile_heights(int T_cap, int n_tiles, int splits) {
 // cold and took 1 us in front of every product.
 template <int kMode, bool kWT>
 __global__ __launch_bounds__(512, 2) void ffn_gemm_counted_kernel(const uint16_t* __restrict__ X,
-                                                                  const uint16_t* __restrict__ W, int K, int ldw, int n_tiles,
+                                                                  const uint16_t* __restrict__ W, int K, int n_tiles,
                                                                   int splits, int gate_row, int w_rows, int T_cap,
                                                                   const int32_t* __restrict__ meta,
                                                                   uint16_t* __restrict__ out, int ldo,
                                                                   const uint16_t* __restrict__ aux, int gate_col,
-                                                                  TileHeights heights) {
+                                                                  TileHeights heights, int ldw) {
   __shared__ __attribute__((aligned(1024))) uint16_t smem[kGemmLds<5, 4, 2, 2>];
   const int T = __builtin_amdgcn_readfirstlane(min(meta[0], T_cap));
-#define MB_TILE(n) \
-  gemm_tiles<kMode, kWT, n, 4, 2, 2>(X, W, K, ldw, n_tiles, splits, gate_row, w_rows, T, T_cap, out, ldo, aux, gate_col, smem)
+#define MB_TILE(n, stages) \
+  gemm_tiles<kMode, kWT, n, 4, 2, stages>(X, W, K, ldw, n_tiles, splits, gate_row, w_rows, T, T_cap, out, ldo, aux, gate_col, smem)
+  const bool third = K >= kThirdStageFrom * kBK * splits;
   const int at = (max(T, 1) - 1) >> heights.shift;
   const uint64_t word = at < 32 ? (at < 16 ? heights.word[0] : heights.word[1])
                                 : (at < 48 ? heights.word[2] : heights.word[3]);
   switch ((int)(word >> (4 * (at & 15))) & 7) {
-    case 1: MB_TILE(1); break;
-    case 2: MB_TILE(2); break;
-    case 3: MB_TILE(3); break;
-    case 4: MB_TILE(4); break;
-    default: MB_TILE(5);
+    case 1:
+      if (third) MB_TILE(1, 3);
+      else MB_TILE(1, 2);
+      break;
+    case 2:
+      if (third) MB_TILE(2, 3);
+      else MB_TILE(2, 2);
+      break;
+    case 3: MB_TILE(3, 2); break;
+    case 4: MB_TILE(4, 2); break;
+    default: MB_TILE(5, 2);
   }
 #undef MB_TILE
 }
@@ -719,8 +732,8 @@ static void launch_gemm_tile(const void* x, const void* wt, int K, int n_cols, i
   const int64_t total = (int64_t)m_tiles * n_tiles * splits;
   ffn_gemm_kernel<kMode, kWT, kMB, kWN, kNB, kStages>
       <<<dim3((unsigned)(total < kComputeUnits ? total : kComputeUnits)), dim3(128 * kWN), 0, stream>>>(
-          static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_cols, n_tiles, splits, gate_row, w_rows,
-          T_cap, meta, static_cast<uint16_t*>(out), ldo, aux, gate_col);
+          static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_tiles, splits, gate_row, w_rows, T_cap,
+          meta, static_cast<uint16_t*>(out), ldo, aux, gate_col, n_cols);
 }
 
 // Estimated microseconds of a product in tiles of the best height, `splits` shares of the contraction.
@@ -737,18 +750,25 @@ static void launch_gemm(const void* x, const void* wt, int K, int n_cols, int sp
     // as many workgroups as the lowest tiles of a full buffer would take, one per compute unit at most
     const int64_t most = (int64_t)((T_cap + 63) / 64) * n_tiles * splits;
     ffn_gemm_counted_kernel<kMode, kWT><<<dim3((unsigned)(most < kComputeUnits ? most : kComputeUnits)), dim3(512), 0, stream>>>(
-        static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_cols, n_tiles, splits, gate_row, w_rows, T_cap,
-        meta, static_cast<uint16_t*>(out), ldo, aux, gate_col, tile_heights(T_cap, n_tiles, splits));
+        static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(wt), K, n_tiles, splits, gate_row, w_rows, T_cap,
+        meta, static_cast<uint16_t*>(out), ldo, aux, gate_col, tile_heights(T_cap, n_tiles, splits), n_cols);
     return;
   }
-#define MB_TILE(n) \
-  launch_gemm_tile<kMode, kWT, n, 4, 2, 2>(x, wt, K, n_cols, splits, gate_row, w_rows, T_cap, meta, out, ldo, aux, gate_col, stream)
+#define MB_TILE(n, stages) \
+  launch_gemm_tile<kMode, kWT, n, 4, 2, stages>(x, wt, K, n_cols, splits, gate_row, w_rows, T_cap, meta, out, ldo, aux, gate_col, stream)
+  const bool third = K >= kThirdStageFrom * kBK * splits;
   switch (tile_height(T_cap, n_tiles, splits)) {
-    case 1: MB_TILE(1); break;
-    case 2: MB_TILE(2); break;
-    case 3: MB_TILE(3); break;
-    case 4: MB_TILE(4); break;
-    default: MB_TILE(5);
+    case 1:
+      if (third) MB_TILE(1, 3);
+      else MB_TILE(1, 2);
+      break;
+    case 2:
+      if (third) MB_TILE(2, 3);
+      else MB_TILE(2, 2);
+      break;
+    case 3: MB_TILE(3, 2); break;
+    case 4: MB_TILE(4, 2); break;
+    default: MB_TILE(5, 2);
   }
 #undef MB_TILE
 }
