@@ -773,15 +773,18 @@ static void launch_gemm(const void* x, const void* wt, int K, int n_cols, int sp
 #undef MB_TILE
 }
 
-// out[t, n] = sum_k x[t, k] * wt[n, k] with the plain epilogue; in narrow tiles where their estimate (0.23 us a step, 1.5 us
-// a tile) is less: 945 x 768, K = 3072: 37 us in tiles of 64 x 256, 14 us in 64 x 64; 300 x 768, K = 768: 8.0 and 6.0 us;
+// The same in narrow tiles: 0.23 us a step, 1.5 us a tile.
+static double narrow_cost(int T_cap, int n_cols, int K) {
+  const int64_t tiles = (int64_t)((T_cap + 63) / 64) * (n_cols / 64);
+  return (double)((tiles + kComputeUnits - 1) / kComputeUnits) * (0.23 * (K / kBK) + 1.5);
+}
+
+// out[t, n] = sum_k x[t, k] * wt[n, k] with the plain epilogue; in narrow tiles where their estimate is less: 945 x 768, K = 3072: 37 us in tiles of 64 x 256, 14 us in 64 x 64; 300 x 768, K = 768: 8.0 and 6.0 us;
 // 2000 x 768, K = 768 (two rounds of narrow tiles): 8.7 and 9.9 us.
 template <bool kWT = false>
 static void launch_plain(const void* x, const void* wt, int T_cap, const int32_t* meta, int n_in, int n_out, void* y,
                          hipStream_t stream) {
-  const int64_t narrow = (int64_t)((T_cap + 63) / 64) * (n_out / 64);
-  const double cost = (double)((narrow + kComputeUnits - 1) / kComputeUnits) * (0.23 * (n_in / kBK) + 1.5);
-  if (cost < gemm_cost(T_cap, n_out, n_in, 1)) {
+  if (narrow_cost(T_cap, n_out, n_in) < gemm_cost(T_cap, n_out, n_in, 1)) {
     launch_gemm_tile<kPlain, kWT, 1, 2, 1, 8>(x, wt, n_in, n_out, 1, 0, n_out, T_cap, meta, y, n_out, nullptr, 0, stream);
     return;
   }
@@ -891,15 +894,16 @@ mb_status launch_geglu_bwd(const void* dy, const void* x, const void* w1v, const
     // dA = dy W2^T, and on its way out  dh = dA g GeLU'(h),  dg = dA GeLU(h)
     launch_gemm<kGateBwd, true>(dy, w2, hidden, inter, 1, 0, inter, T_cap, meta, dhg, 2 * inter, hg, inter, stream);
     // dx = dh W1^T + dg V^T = (dh | dg) (W1 | V)^T: the longest contraction onto the fewest columns.  With few tokens its
-    // tiles leave most compute units idle, so the contraction is split where that pays for adding up the shares
-    // (945 tokens, 768 x 3072: 74 us in one piece, 25 us in 8 shares); the partial sums lie where the weight
-    // gradients' partial tiles come later.
+    // tiles leave most compute units idle, so it is taken in narrow tiles, or the contraction is split where that pays for
+    // a second launch and for adding up the shares (the partial sums lie where the weight gradients' partial tiles come
+    // later).  768 x 3072, one piece in narrow tiles and 8 shares with the adding up: 60 tokens 21.6 and 14.8 us, 400 tokens
+    // 22.6 and 16.6, 945 tokens 24.0 and 24.5 and the gap between two launches; 256 x 1024: 945 tokens 10.1 and 14.6.
     int splits = 1;
-    double least = 1e300;
+    double least = narrow_cost(T_cap, hidden, 2 * inter) + 1.0;   // (weights by k: 2 us more than the estimate at 100 steps)
     for (int s = 1; s <= 8; s *= 2) {   // (2 inter / 64 is a multiple of 8)
       if ((size_t)s * T_cap > (size_t)kWgradSplits * 2 * inter) break;
       const double cost = gemm_cost(T_cap, hidden, 2 * inter, s) +
-                          (s > 1 ? 6.0 + 8.0 * s * T_cap * hidden / 4.5e6 : 0.0);   // launch, write and read at 4.5 TB/s
+                          (s > 1 ? 7.0 + 8.0 * s * T_cap * hidden / 6.0e6 : 0.0);   // launch, write and read
       if (cost < least) {
         least = cost;
         splits = s;
