@@ -360,17 +360,32 @@ __global__ __launch_bounds__(256, 4) void attn_fwd_short_kernel(
   u32x4 tq[4], tk[4], tv[4];
   // Rows listed in ascending order whose first and last differ by n - 1 are consecutive (the usual
   // case: padding is a suffix of each batch row); then no per-token index load is needed.
-  int row0 = 0;
+  int row0 = start;
   bool contig = true;
   if (kRows) {
-    row0 = rows[start];
-    contig = rows[start + n - 1] - row0 == n - 1;
+    row0 = __builtin_amdgcn_readfirstlane(rows[start]);
+    contig = __builtin_amdgcn_readfirstlane(rows[start + n - 1]) - row0 == n - 1;
   }
-  auto row_of = [&](int r) -> int64_t { return contig ? (int64_t)(row0 + r) : (int64_t)rows[start + r]; };
-  if (kRows) {
+  // Consecutive rows move with buffer instructions (256 x 128 positions, 16 heads, padded rows: 51 us with an address and a
+  // compare per lane, 48 so; packed rows the same either way): a descriptor per tensor from the unit's first row to its last, 32-bit
+  // offsets (127 rows of 2^24 elements stay below 2^32 bytes), zeros and dropped stores past the end without a compare.
+  auto rsrc = [&](const uint16_t* base, int64_t stride, int cnt) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base) + ((int64_t)row0 * stride + h * kD), 0,
+                                             (int)(((uint32_t)(cnt - 1) * (uint32_t)stride + kD) * 2u), 0x00020000);
+  };
+  auto piece = [&](int64_t stride, int row) { return ((uint32_t)row * (uint32_t)stride + (uint32_t)st_col) * 2u; };
+  if (contig) {
+    const __amdgpu_buffer_rsrc_t qr = rsrc(q, qs, n), kr = rsrc(k, ks, nk), vr = rsrc(v, vs, nk);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      tq[it] = __builtin_amdgcn_raw_buffer_load_b128(qr, piece(qs, 32 * it + st_row), 0, 0);
+      tk[it] = __builtin_amdgcn_raw_buffer_load_b128(kr, piece(ks, 32 * it + st_row), 0, 0);
+      tv[it] = __builtin_amdgcn_raw_buffer_load_b128(vr, piece(vs, 32 * it + st_row), 0, 0);
+    }
+  } else {
     int64_t gr[4];
 #pragma unroll
-    for (int it = 0; it < 4; ++it) gr[it] = 32 * it + st_row < n ? row_of(32 * it + st_row) : 0;
+    for (int it = 0; it < 4; ++it) gr[it] = 32 * it + st_row < n ? rows[start + 32 * it + st_row] : 0;
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
       tq[it] = tk[it] = tv[it] = u32x4{0u, 0u, 0u, 0u};
@@ -378,22 +393,6 @@ __global__ __launch_bounds__(256, 4) void attn_fwd_short_kernel(
       if (32 * it + st_row < nk) {
         tk[it] = *reinterpret_cast<const u32x4*>(k + gr[it] * ks + h * kD + st_col);
         tv[it] = *reinterpret_cast<const u32x4*>(v + gr[it] * vs + h * kD + st_col);
-      }
-    }
-  } else {
-    const uint16_t* qh = q + (int64_t)start * qs + h * kD;
-    const uint16_t* kh = k + (int64_t)start * ks + h * kD;
-    const uint16_t* vh = v + (int64_t)start * vs + h * kD;
-    const uint32_t qoff = (uint32_t)st_row * (uint32_t)qs + st_col;
-    const uint32_t koff = (uint32_t)st_row * (uint32_t)ks + st_col;
-    const uint32_t voff = (uint32_t)st_row * (uint32_t)vs + st_col;
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      tq[it] = tk[it] = tv[it] = u32x4{0u, 0u, 0u, 0u};
-      if (32 * it + st_row < n) tq[it] = *reinterpret_cast<const u32x4*>(qh + qoff + (uint32_t)(32 * it) * (uint32_t)qs);
-      if (32 * it + st_row < nk) {
-        tk[it] = *reinterpret_cast<const u32x4*>(kh + koff + (uint32_t)(32 * it) * (uint32_t)ks);
-        tv[it] = *reinterpret_cast<const u32x4*>(vh + voff + (uint32_t)(32 * it) * (uint32_t)vs);
       }
     }
   }
@@ -522,15 +521,17 @@ __global__ __launch_bounds__(256, 4) void attn_fwd_short_kernel(
     }
   }
   // (same wave wrote and reads the slab: LDS operations of one wave complete in order)
-  uint16_t* oh = o + (kRows ? (int64_t)0 : (int64_t)(start + 32 * wave) * os) + h * kD;
   const int orow = lane >> 3, ocol = (lane & 7) * 8;
+  const __amdgpu_buffer_rsrc_t orr = rsrc(o, os, n);
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
     const int row = 8 * it + orow;
     const u32x4 w = *reinterpret_cast<const u32x4*>(&slab[row * kKStride + ocol]);
-    if (32 * wave + row < n) {
-      if (kRows) *reinterpret_cast<u32x4*>(oh + row_of(32 * wave + row) * os + ocol) = w;
-      else *reinterpret_cast<u32x4*>(oh + (uint32_t)row * (uint32_t)os + ocol) = w;
+    if (contig) {
+      __builtin_amdgcn_raw_buffer_store_b128(
+          w, orr, ((uint32_t)(32 * wave + row) * (uint32_t)os + (uint32_t)ocol) * 2u, 0, 0);
+    } else if (32 * wave + row < n) {
+      *reinterpret_cast<u32x4*>(o + (int64_t)rows[start + 32 * wave + row] * os + h * kD + ocol) = w;
     }
   }
 }
