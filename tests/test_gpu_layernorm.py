@@ -146,3 +146,29 @@ def test_layernorm_reads_and_writes_a_padded_batch_directly(mb, bf16, W, holes):
     for name, g_, ref in (("dgamma", dg2, dg_ref), ("dbeta", db2, db_ref)):
         _, rf = err_stats(g_.double().cpu().numpy(), ref)
         assert rf <= (1e-4 if bf16 else 1e-5), "%s rel_fro=%.3e" % (name, rf)
+
+
+@pytest.mark.parametrize("W,bf16", [(8, True), (512, True), (520, True), (1024, True), (1032, True), (4, False), (256, False),
+                                    (260, False), (512, False), (516, False)])
+@pytest.mark.parametrize("T", [1, 2045, 2051, 8200])
+def test_rows_at_the_edges_of_a_lanes_pieces(mb, T, W, bf16):
+    """Widths on both sides of 64 and 128 pieces of 16 bytes; row counts that give the column sums one, just under and just over 512
+    partial rows, and every wave three rows.  Buffers end with the last row; what lies behind it stays as it is."""
+    print("layernorm edges T=%d W=%d bf16=%s" % (T, W, bf16), flush=True)
+    x, r, gamma, beta, dy = make(11, T, W, bf16)
+    y_ref, s_ref, mean_ref, rstd_ref = orc.add_layernorm_fwd(x, r, gamma, beta, EPS, round_sum=bf16)
+    ds_ref, dg_ref, db_ref = orc.add_layernorm_bwd(dy, s_ref, gamma, EPS)
+    xd, rd_, gd, bd, dyd = (dev(a, bf16) for a in (x, r, gamma, beta, dy))
+    y, s, ds = (torch.full((T + 1, W), 7.0, dtype=xd.dtype, device="cuda") for _ in range(3))
+    _, _, mean, rstd = mb.mb_add_layernorm_fwd(xd, rd_, gd, bd, EPS, y=y[:T], s=s[:T])
+    _, dgamma, dbeta = mb.mb_add_layernorm_bwd(dyd, s[:T], gd, mean, rstd, ds=ds[:T])
+    for t in (y, s, ds):
+        assert bool((t[T] == 7.0).all())
+    tol_abs, tol_rel = (2e-2, 1e-2) if bf16 else (1e-4, 1e-5)
+    for name, got, ref in (("y", y, y_ref), ("s", s, s_ref), ("ds", ds, ds_ref)):
+        ma, rf = err_stats(got[:T].double().cpu().numpy(), ref)
+        # relative to the largest value: bf16 rounds at 2^-9 of it, and ds of a narrow row is a difference of larger numbers
+        assert ma <= tol_abs * max(1.0, np.abs(ref).max()) and rf <= tol_rel, "%s max_abs=%.3e rel_fro=%.3e" % (name, ma, rf)
+    for name, got, ref in (("dgamma", dgamma, dg_ref), ("dbeta", dbeta, db_ref)):
+        _, rf = err_stats(got.double().cpu().numpy(), ref)
+        assert rf <= (1e-4 if bf16 else 1e-5), "%s rel_fro=%.3e" % (name, rf)
