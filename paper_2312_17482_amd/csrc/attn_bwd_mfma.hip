@@ -345,7 +345,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
     const int here = t & (kRing - 1), next = (t + 1) & (kRing - 1), after = (t + 2) & (kRing - 1), to = (t + 3) & (kRing - 1);
     staged_barrier<kRowLoads + 1>();
     if (t == 0) issue_rows(2, 2);   // (the region of the K rows)
-    // Loads in one go take 32 cycles each and block the waves, so they are spread over the step's matrix instructions (not
+    // Loads in one go block the waves for 300 to 500 cycles, so they are spread over the step's matrix instructions (not
     // the ones with an address per lane: there are no registers left for those).
     if (!contig) issue_rows(t + 3, to);
     const Places tr = places_tr(here * kRegionBytes), row = places_row(next * kRegionBytes);

@@ -53,7 +53,7 @@ __device__ __forceinline__ void store4(uint16_t* p, f32x4 x) {
 
 // e^x for the exponents of a softmax: 2^y for y = x log2(e) rounded, times 1 + ln2 (x log2(e) - y), the rounding of
 // the product put back (a weight e^-5 of 256 equal ones would otherwise be off by 2e-7 of itself).  Seven instructions
-// instead of expf's twelve or more; vector and matrix instructions of a SIMD do not overlap here, so they count.
+// instead of expf's twelve or more.
 // (x = -inf gives 0: the correction is then NaN or infinite, and is left out.)
 __device__ __forceinline__ float exp_neg(float x) {
   constexpr float kL = 1.4426950408889634f, kLlo = (float)(1.4426950408889634074 - (double)kL);

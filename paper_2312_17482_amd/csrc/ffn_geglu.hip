@@ -16,8 +16,8 @@
 // lane owns runs of 4 consecutive output columns of one token; the tile is turned into row segments through a
 // wave-private LDS slab before it is stored.
 //
-// What bounds it, measured: the loads into LDS (without them the k loop runs 1.2 to 1.5 times as fast; they take about
-// 32 cycles per KB and compute unit in 128-byte pieces and half as long again in 64-byte ones), and the power limit: at
+// What bounds it, measured: the loads into LDS (without them the k loop runs 1.2 to 1.5 times as fast; beside the LDS reads
+// they take 32 cycles per KB and compute unit, alone 16, in 64-byte pieces half as long again), and the power limit: at
 // 1380 TFLOP/s (8192^3) the clock is down to 1.7 GHz and the matrix cores are busy 72 % of the time.  Hence the largest
 // tile that fits the registers (fewest bytes per product), no pass of the operands through registers, and whole cache
 // lines.  Tried: 256 x 128 tiles, two workgroups per compute unit (1035 TFLOP/s at 8192^3), four waves of 128 x 128 (1210),
@@ -543,13 +543,13 @@ __global__ __launch_bounds__(256) void gelu_gate_kernel(const uint16_t* __restri
 // ROWS.  Rows of 256 columns go to LDS as they are and the matrix-core operands (8 consecutive tokens of one column per
 // lane) come out of transposing LDS reads (ds_read_b64_tr_b16).  The accumulator has m along registers and n along lanes,
 // so a store instruction writes 128 contiguous bytes of two output rows: fp32 tiles need no staging.  Same shape as
-// the projection kernel: 256 x 256 tiles, 8 waves of 128 x 64, steps of 64 tokens through two LDS stages that are filled
-// straight from global memory.  Both weight gradients of the sublayer are one launch (its few tiles fill the compute
+// the projection kernel: 256 x 256 tiles, 8 waves of 128 x 64, steps of 64 tokens through two LDS stages (or 128 x 256, three
+// stages) that are filled straight from global memory.  Both weight gradients of the sublayer are one launch (its few tiles fill the compute
 // units better together); the tokens are split over `splits` workgroups per tile, and a second kernel adds the partial
 // tiles in a fixed order, so the result is deterministic.
 // Bound like the projections by the loads into LDS and the power limit.  At 26963 tokens, 768 x 3072 (381 GFLOP, two
-// splits) 405 us and 13 us for adding up, where two launches of seven splits each, staged through registers, took 430 and
-// 40 us (means of 20 passes in one run); at 945 tokens (one split, no adding up) 31 us instead of 66 and 34.
+// splits) 380 us and 13 us for adding up, where two launches of seven splits each, staged through registers, took 430 and
+// 40 us (means of 20 passes); at 945 tokens (one split, no adding up) 23 us, in 256 x 256 tiles 30.
 constexpr int kWgRows = 64;                         // tokens per k step
 // Tiles are 64 kMB x 256: 256 (two stages) or, where those are too few to occupy the compute units, 128 (three stages).
 template <int kMB>
