@@ -618,8 +618,10 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
     staged_barrier<kRowLoads>();
     if (!contig) issue_tile(jt + 2, to);
     uint32_t ra[4], ta[2][2];
+    // (k-step s reads piece (2 s + g) ^ swizzle: the first one's place with bits 5 and 6 exchanged, so that one register and
+    // not four is kept from step to step: with four there were two too many)
 #pragma unroll
-    for (int s = 0; s < 4; ++s) ra[s] = row_at[s] + region * (kRegion * 2);
+    for (int s = 0; s < 4; ++s) ra[s] = (row_at[0] + region * (kRegion * 2)) ^ (32 * s);
 #pragma unroll
     for (int s = 0; s < 4; ++s) ta[s >> 1][s & 1] = tr_at[s >> 1][s & 1] + region * (kRegion * 2);
     const int rem = nk - j0;

@@ -89,6 +89,16 @@ __device__ __forceinline__ void stage_ready() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(kNewer) : "memory");
 }
 
+// The lane's number, counted afresh: unlike a copy it costs no register between two uses that are far apart.  The gate
+// backward in tiles of 320 tokens needs all 256 (160 sums, 28 of fragments, 48 of h and g): with the lane and the epilogue's
+// places kept across the products it had 3 and 4 (row count on the device) in memory, and taking them back made every
+// epilogue wait for all loads in flight.
+__device__ __forceinline__ int lane_again() {
+  uint32_t all = ~0u;
+  asm volatile("" : "+s"(all));   // (else the compiler keeps the first one)
+  return __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+}
+
 constexpr int kSlabElems = 32 * 32;   // per wave: 32 tokens x 32 columns on their way out
 // LDS of a tile shape, elements: kStages stages of 64 kMB token rows and 32 kWN kNB weight rows, and the waves' slabs.
 template <int kMB, int kWN, int kNB, int kStages>
@@ -115,7 +125,7 @@ template <int kMode, bool kWT, int kMB, int kWN, int kNB, int kStages>
 __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int K, int ldw,
                                            int n_tiles, int splits, int gate_row, int w_rows, int T, int T_cap,
                                            uint16_t* __restrict__ out, int ldo, const uint16_t* __restrict__ aux,
-                                           int gate_col, uint16_t* __restrict__ smem) {
+                                           int gate_col, uint16_t* __restrict__ smem, int wave) {
   constexpr bool kGated = kMode == kGatedFwd;
   constexpr int kBM = 64 * kMB, kBN = 32 * kWN * kNB, kWaves = 2 * kWN;
   static_assert(!kGated || (kNB == 2 && !kWT), "the gated epilogue pairs the wave's two weight blocks");
@@ -154,9 +164,7 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
     n0 = __builtin_amdgcn_readfirstlane(rem / gsize) * kOutCols;
   };
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = lane & 31, g = lane >> 5;
+  const int lane = kMode == kGateBwd ? lane_again() : (int)(threadIdx.x & 63), c = lane & 31, g = lane >> 5;
   const int wm = wave / kWN, wn = wave % kWN;
 
   // Global -> LDS: a row of a stage is 128 bytes = 8 pieces, a load carries 8 rows (whole cache lines: rows of 64 bytes,
@@ -342,7 +350,8 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
     // Epilogue: 32 tokens x 32 columns at a time through the wave's own slab, out of which rows leave as 64-byte
     // segments.  (Piece x of a row at position x ^ (row / 4) % 4; the LDS operations of one wave complete in order.)
     uint16_t* slab = smem + kStages * kStageElems + wave * kSlabElems;
-    const int orow = lane >> 2, opiece = lane & 3;
+    const int e_lane = kMode == kGateBwd ? lane_again() : lane;
+    const int orow = e_lane >> 2, opiece = e_lane & 3, ec = e_lane & 31, eg = e_lane >> 5;
     const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc(
         out + (int64_t)m0 * ldo, 0, (uint32_t)min(T - m0, kBM) * (uint32_t)ldo * 2u, 0x00020000);
     // Gate backward: h and g of a pass are requested kAhead passes before it (rows past the last token read the last one;
@@ -385,7 +394,7 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
           u32x2 w;
           w[0] = pack_bf16(r[0], r[1]);
           w[1] = pack_bf16(r[2], r[3]);
-          *reinterpret_cast<u32x2*>(&slab[c * 32 + ((j ^ ((c >> 2) & 3)) * 8) + 4 * g]) = w;
+          *reinterpret_cast<u32x2*>(&slab[ec * 32 + ((j ^ ((ec >> 2) & 3)) * 8) + 4 * eg]) = w;
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -432,7 +441,7 @@ __global__ __launch_bounds__(128 * kWN, kWN / 2) void ffn_gemm_kernel(const uint
   // (readfirstlane: tells the compiler the value is wave-uniform, so descriptors built from it stay scalar)
   const int T = __builtin_amdgcn_readfirstlane(meta ? min(meta[0], T_cap) : T_cap);
   gemm_tiles<kMode, kWT, kMB, kWN, kNB, kStages>(X, W, K, ldw, n_tiles, splits, gate_row, w_rows, T, T_cap, out, ldo, aux, gate_col,
-                                            smem);
+                                            smem, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
 // The tile height (in 64 tokens, up to 320) with the least estimated time for T tokens, n_tiles weight tiles of 256 rows
@@ -491,7 +500,8 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm_counted_kernel(const uint16_t
   __shared__ __attribute__((aligned(1024))) uint16_t smem[kGemmLds<5, 4, 2, 2>];
   const int T = __builtin_amdgcn_readfirstlane(min(meta[0], T_cap));
 #define MB_TILE(n, stages) \
-  gemm_tiles<kMode, kWT, n, 4, 2, stages>(X, W, K, ldw, n_tiles, splits, gate_row, w_rows, T, T_cap, out, ldo, aux, gate_col, smem)
+  gemm_tiles<kMode, kWT, n, 4, 2, stages>(X, W, K, ldw, n_tiles, splits, gate_row, w_rows, T, T_cap, out, ldo, aux, gate_col, smem, wave)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool third = K >= kThirdStageFrom * kBK * splits;
   const int at = (max(T, 1) - 1) >> heights.shift;
   const uint64_t word = at < 32 ? (at < 16 ? heights.word[0] : heights.word[1])
