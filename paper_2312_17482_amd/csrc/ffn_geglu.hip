@@ -105,10 +105,11 @@ template <int kMB, int kWN, int kNB, int kStages>
 constexpr int kGemmLds = kStages * (64 * kMB + 32 * kWN * kNB) * kBK + 2 * kWN * kSlabElems;
 
 // Wide tiles of 64 and 128 tokens leave room for a third stage, which pays from this many k steps on where the weights come
-// from memory (two and three stages, 40 and more weights in turn; 64-token tiles: 8 steps 945 x 1536 8.6 and 7.5 us, 12 steps
-// 1500 x 768 11.5 and 9.2, 200 x 6144 15.5 and 12.1, 48 steps 4000 x 768 51 and 35, 4 steps 5.9 and 5.9; 128-token tiles: 12
-// steps 2500 x 2304 18.0 and 15.5, 945 x 6144 18.9 and 16.3, 16 steps 1500 x 3072 22.8 and 18.1).  Out of a warm L2 it costs
-// 0.3 us up to 12 steps.
+// from memory (two and three stages, 48 weights in turn; 64-token tiles: 8 steps 945 x 1536 8.5 and 7.3 us, 12 steps
+// 1500 x 768 11.4 and 8.9, 200 x 6144 15.5 and 12.0, 48 steps 4000 x 768 38 and 26, 4 steps 5.9 and 5.9; 128-token tiles: 12
+// steps 2500 x 2304 15.1 and 14.0, 945 x 6144 18.7 and 15.6, 16 steps 1500 x 3072 22.7 and 17.5).  Out of a warm L2 it makes
+// no difference up to 12 steps (6.74 and 6.80, 8.19 and 8.24, 8.25 and 8.32, 14.3 and 13.8, 14.0 and 13.9); with the third
+// stage's loads in front of the first products and behind the last ones it cost 0.3 us.
 constexpr int kThirdStageFrom = 8;
 
 // One workgroup of 2 kWN waves (2 along the tokens by kWN along the weight rows) per compute unit walks the tiles
@@ -259,7 +260,8 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
 
   // The k steps of all the workgroup's tiles form one sequence; the loads run kStages steps ahead of the products, across
   // the end of a tile, so that the next tile's first steps arrive during this one's last products and its epilogue.
-  // (Past the last tile the loads repeat it: their number stays the same and nobody reads them.)
+  // (Past the last tile the loads repeat it: their number stays the same and nobody reads them.  With three stages that would
+  // be a step's bytes more, so there they load nothing: their descriptors become empty.)
   int f_tile = blockIdx.x, f_kt = 0;
   aim(f_tile);
   auto advance = [&]() {
@@ -268,17 +270,24 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
     if (f_tile + (int)gridDim.x < total) {
       f_tile += gridDim.x;
       aim(f_tile);
+    } else if (kStages == 3) {
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) rsrc[i][2] = 0u;
     }
   };
-#pragma unroll
-  for (int st = 0; st < kStages; ++st) {
+  auto fill = [&](int st) {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) fetch_one(i, st, f_kt);
     advance();
-  }
-  stage_ready<(kStages - 1) * kLoads>();
+  };
+  // (a third stage is requested once the first has arrived: in front of it its loads would only hold up the first products)
+  constexpr int kFirst = kStages == 3 ? 2 : kStages;
+#pragma unroll
+  for (int st = 0; st < kFirst; ++st) fill(st);
+  stage_ready<(kFirst - 1) * kLoads>();
 #pragma unroll
   for (int i = 0; i < kFrags; ++i) read_frag(0, 0, i);
+  if (kFirst < kStages) fill(kFirst);
 
   // store instructions of an epilogue, per wave (they are issued also where every lane is out of range)
   constexpr int kStores = kMode == kPartial ? 0 : kGated ? 2 * kMB : (kMode == kGateBwd ? 4 : 2) * kMB * kNB;
