@@ -75,6 +75,13 @@ struct Names {
 template <typename... T>
 Names(T...) -> Names<sizeof...(T)>;
 
+// What x.name() gives: the calls below take a bare pointer from any object that has the method.
+PyObject* asked(PyObject* x, const char* name) {
+  PyObject* r = PyObject_CallMethod(x, name, nullptr);
+  if (!r) throw Raised();
+  return r;
+}
+
 // The arguments of a call by their place in `names` (nullptr where not given).
 template <int N>
 struct Args {
@@ -113,7 +120,31 @@ struct Args {
     }
     return THPVariable_Unpack(v[i]);
   }
-  void* ptr(int i) const { return given(i) ? tensor(i).data_ptr() : nullptr; }
+  void* ptr(int i) const {
+    if (!given(i)) return nullptr;
+    if (THPVariable_Check(v[i])) return THPVariable_Unpack(v[i]).data_ptr();
+    PyObject* r = asked(v[i], "data_ptr");
+    void* p = r == Py_None ? nullptr : PyLong_AsVoidPtr(r);
+    Py_DECREF(r);
+    if (!p && PyErr_Occurred()) throw Raised();
+    return p;
+  }
+  int64_t numel(int i) const {
+    if (THPVariable_Check(v[i])) return THPVariable_Unpack(v[i]).numel();
+    PyObject* r = asked(v[i], "numel");
+    const int64_t n = PyLong_AsLongLong(r);
+    Py_DECREF(r);
+    if (n == -1 && PyErr_Occurred()) throw Raised();
+    return n;
+  }
+  bool contiguous(int i) const {
+    if (THPVariable_Check(v[i])) return THPVariable_Unpack(v[i]).is_contiguous();
+    PyObject* r = asked(v[i], "is_contiguous");
+    const int yes = PyObject_IsTrue(r);
+    Py_DECREF(r);
+    if (yes < 0) throw Raised();
+    return yes;
+  }
   int integer(int i) const {   // as ctypes converts to a C int
     PyObject* x = PyNumber_Index(v[i]);
     if (!x) throw Raised();
@@ -132,7 +163,7 @@ struct Args {
   }
 };
 
-// A result: the tensor that was given, or one made here.
+// A result: the object that was given, or a tensor made here.
 struct Result {
   PyObject* object = nullptr;   // borrowed, if given
   at::Tensor made;
@@ -141,13 +172,16 @@ struct Result {
   Result(const A& a, int i, Make make) {
     if (a.given(i)) {
       object = a.v[i];
-      ptr = a.tensor(i).data_ptr();
+      ptr = a.ptr(i);
     } else {
       made = make();
       ptr = made.data_ptr();
     }
   }
-  const at::Tensor& tensor() const { return object ? THPVariable_Unpack(object) : made; }
+  template <typename A>
+  const at::Tensor& tensor(const A& a, int i) const { return object ? a.tensor(i) : made; }
+  template <typename A>
+  size_t numel(const A& a, int i) const { return (size_t)(object ? a.numel(i) : made.numel()); }
   PyObject* take() {
     if (object) {
       Py_INCREF(object);
@@ -252,7 +286,7 @@ PyObject* unpad(Self s, Argv argv, Py_ssize_t n, PyObject* kw) {
   const int64_t W = padded.size(1);
   const int T_cap = a.integer(2);
   Result out(a, 4, [&] { return new_like(padded, {T_cap, W}, padded.scalar_type()); });
-  const at::Tensor& o = out.tensor();
+  const at::Tensor& o = out.tensor(a, 4);
   require(o.is_contiguous() && o.dim() >= 2 && o.size(1) == W && o.size(0) >= T_cap, "out must be contiguous, [>= T_cap, W]");
   const mb_dtype dt = (mb_dtype)dtype_code(padded);
   void* const stream = current_stream(s);
@@ -269,7 +303,7 @@ PyObject* pad(Self s, Argv argv, Py_ssize_t n, PyObject* kw) {
   const int64_t W = packed.size(1);
   const int B = a.integer(4), L = a.integer(5);
   Result out(a, 6, [&] { return new_like(packed, {(int64_t)B * L, W}, packed.scalar_type()); });
-  const at::Tensor& o = out.tensor();
+  const at::Tensor& o = out.tensor(a, 6);
   require(o.is_contiguous() && o.dim() == 2 && o.size(0) == (int64_t)B * L && o.size(1) == W, "out must be contiguous, [B * L, W]");
   const mb_dtype dt = (mb_dtype)dtype_code(packed);
   void* const stream = current_stream(s);
@@ -304,16 +338,16 @@ PyObject* attn_fwd(Self s, Argv argv, Py_ssize_t n, PyObject* kw) {
   static const Names names("q", "k", "v", "cu_seqlens", "max_seqlen", "slopes", "softmax_scale", "out", "lse",
                                       "token_rows", "T", "workspace", "key_lens", "plan");
   const Args<14> a("mb_alibi_attn_fwd", names, 7, argv, n, kw);
-  const at::Tensor &q = a.tensor(0), &k = a.tensor(1), &v = a.tensor(2), &cu = a.tensor(3);
+  const at::Tensor &q = a.tensor(0), &k = a.tensor(1), &v = a.tensor(2);
   int64_t R, H, D;
   attention_sizes(q, &R, &H, &D);
-  const int T = a.integer_or(10, R), max_seqlen = a.integer(4), B = (int)(cu.numel() - 1);
+  const int T = a.integer_or(10, R), max_seqlen = a.integer(4), B = (int)(a.numel(3) - 1);
   Result out(a, 7, [&] { return new_like(q, {R, H, D}, q.scalar_type()); });
   Result lse(a, 8, [&] { return new_like(q, {H, T}, at::kFloat); });
   const mb_dtype dt = (mb_dtype)dtype_code(q);
   at::Tensor own;
   void* workspace = a.ptr(11);
-  size_t workspace_bytes = a.given(11) ? (size_t)a.tensor(11).numel() : 0;
+  size_t workspace_bytes = a.given(11) ? (size_t)a.numel(11) : 0;
   if (!a.given(11) && !a.given(13)) {
     workspace_bytes = s->attn_fwd_bytes(B, T, max_seqlen, (int)H, (int)D, dt);
     if (workspace_bytes > 0) {
@@ -323,8 +357,8 @@ PyObject* attn_fwd(Self s, Argv argv, Py_ssize_t n, PyObject* kw) {
   }
   void* const stream = current_stream(s);
   run(s, s->attn_fwd, (const void*)q.data_ptr(), (const void*)k.data_ptr(), (const void*)v.data_ptr(), row_stride(q),
-      row_stride(k), row_stride(v), (const int32_t*)cu.data_ptr(), B, T, max_seqlen, (int)H, (int)D,
-      (const float*)a.ptr(5), a.number(6), dt, out.ptr, row_stride(out.tensor()), (float*)lse.ptr, workspace, workspace_bytes,
+      row_stride(k), row_stride(v), (const int32_t*)a.ptr(3), B, T, max_seqlen, (int)H, (int)D,
+      (const float*)a.ptr(5), a.number(6), dt, out.ptr, row_stride(out.tensor(a, 7)), (float*)lse.ptr, workspace, workspace_bytes,
       (const int32_t*)a.ptr(12), (const int32_t*)a.ptr(9), (const void*)a.ptr(13), stream);
   return tuple_of(out.take(), lse.take());
 }
@@ -333,11 +367,10 @@ PyObject* attn_bwd(Self s, Argv argv, Py_ssize_t n, PyObject* kw) {
   static const Names names("dout", "q", "k", "v", "o", "lse", "cu_seqlens", "max_seqlen", "slopes",
                                       "softmax_scale", "dq", "dk", "dv", "workspace", "token_rows", "T", "key_lens", "plan");
   const Args<18> a("mb_alibi_attn_bwd", names, 10, argv, n, kw);
-  const at::Tensor &dout = a.tensor(0), &q = a.tensor(1), &k = a.tensor(2), &v = a.tensor(3), &o = a.tensor(4),
-                   &cu = a.tensor(6);
+  const at::Tensor &dout = a.tensor(0), &q = a.tensor(1), &k = a.tensor(2), &v = a.tensor(3), &o = a.tensor(4);
   int64_t R, H, D;
   attention_sizes(q, &R, &H, &D);
-  const int T = a.integer_or(15, R), max_seqlen = a.integer(7), B = (int)(cu.numel() - 1);
+  const int T = a.integer_or(15, R), max_seqlen = a.integer(7), B = (int)(a.numel(6) - 1);
   auto make = [&] { return new_like(q, {R, H, D}, q.scalar_type()); };
   Result dq(a, 10, make), dk(a, 11, make), dv(a, 12, make);
   const mb_dtype dt = (mb_dtype)dtype_code(q);
@@ -347,9 +380,9 @@ PyObject* attn_bwd(Self s, Argv argv, Py_ssize_t n, PyObject* kw) {
   void* const stream = current_stream(s);
   run(s, s->attn_bwd, (const void*)dout.data_ptr(), (const void*)q.data_ptr(), (const void*)k.data_ptr(),
       (const void*)v.data_ptr(), (const void*)o.data_ptr(), (const float*)a.ptr(5), row_stride(dout), row_stride(q),
-      row_stride(k), row_stride(v), row_stride(o), (const int32_t*)cu.data_ptr(), B, T, max_seqlen, (int)H, (int)D,
-      (const float*)a.ptr(8), a.number(9), dt, dq.ptr, dk.ptr, dv.ptr, row_stride(dq.tensor()), row_stride(dk.tensor()),
-      row_stride(dv.tensor()), workspace.ptr, (size_t)workspace.tensor().numel(), (const int32_t*)a.ptr(16),
+      row_stride(k), row_stride(v), row_stride(o), (const int32_t*)a.ptr(6), B, T, max_seqlen, (int)H, (int)D,
+      (const float*)a.ptr(8), a.number(9), dt, dq.ptr, dk.ptr, dv.ptr, row_stride(dq.tensor(a, 10)), row_stride(dk.tensor(a, 11)),
+      row_stride(dv.tensor(a, 12)), workspace.ptr, workspace.numel(a, 13), (const int32_t*)a.ptr(16),
       (const int32_t*)a.ptr(14), (const void*)a.ptr(17), stream);
   return tuple_of(dq.take(), dk.take(), dv.take());
 }
@@ -390,7 +423,7 @@ PyObject* layernorm_bwd(Self s, Argv argv, Py_ssize_t n, PyObject* kw) {
   void* const stream = current_stream(s);
   run(s, s->layernorm_bwd, (const void*)a.ptr(0), (const void*)sum.data_ptr(), (const void*)a.ptr(2), (const float*)a.ptr(3),
       (const float*)a.ptr(4), a.integer_or(5, rows), (const int32_t*)a.ptr(6), (int)W, dt, ds.ptr,
-      (float*)dgamma.ptr, (float*)dbeta.ptr, workspace.ptr, (size_t)workspace.tensor().numel(), (const int32_t*)a.ptr(11),
+      (float*)dgamma.ptr, (float*)dbeta.ptr, workspace.ptr, workspace.numel(a, 10), (const int32_t*)a.ptr(11),
       stream);
   return tuple_of(ds.take(), dgamma.take(), dbeta.take());
 }
@@ -416,7 +449,7 @@ PyObject* geglu_fwd(Self s, Argv argv, Py_ssize_t n, PyObject* kw) {
 PyObject* geglu_bwd(Self s, Argv argv, Py_ssize_t n, PyObject* kw) {
   static const Names names("dy", "x", "w1v", "w2", "act", "hg", "T_cap", "meta", "dx", "dw1v", "dw2", "workspace");
   const Args<12> a("mb_geglu_bwd", names, 5, argv, n, kw);
-  require(!a.given(5) || a.tensor(5).is_contiguous(), "hg must be contiguous");
+  require(!a.given(5) || a.contiguous(5), "hg must be contiguous");
   const at::Tensor &x = a.tensor(1), &w2 = a.tensor(3);
   if (x.dim() != 2) raise(PyExc_ValueError, "x must be a matrix");
   if (w2.dim() < 2) raise(PyExc_IndexError, "w2 must be a matrix");
@@ -432,7 +465,7 @@ PyObject* geglu_bwd(Self s, Argv argv, Py_ssize_t n, PyObject* kw) {
   void* const stream = current_stream(s);
   run(s, s->geglu_bwd, (const void*)a.ptr(0), (const void*)x.data_ptr(), (const void*)a.ptr(2), (const void*)w2.data_ptr(),
       (const void*)a.ptr(4), (const void*)a.ptr(5), T_cap, (const int32_t*)a.ptr(7), (int)hidden, (int)inter, dt, dx.ptr,
-      (float*)dw1v.ptr, (float*)dw2.ptr, workspace.ptr, (size_t)workspace.tensor().numel(), stream);
+      (float*)dw1v.ptr, (float*)dw2.ptr, workspace.ptr, workspace.numel(a, 11), stream);
   return tuple_of(dx.take(), dw1v.take(), dw2.take());
 }
 
