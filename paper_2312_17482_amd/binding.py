@@ -17,10 +17,10 @@ import torch
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "lib", "libmosaicattn.so")
 _MARSHAL_PATH = os.path.join(os.path.dirname(_LIB_PATH), "_mosaic_marshal.so")
+_HOW_TO_BUILD = "Run `python -c 'import __graft_entry__ as g; g.build()'`."
 for _path in (_LIB_PATH, _MARSHAL_PATH):
     if not os.path.exists(_path):
-        raise ImportError("%s is not built (%s). Run `python -c 'import __graft_entry__ as g; g.build()'`."
-                          % (os.path.basename(_path), _path))
+        raise ImportError("%s is not built (%s). %s" % (os.path.basename(_path), _path, _HOW_TO_BUILD))
 _lib = ctypes.CDLL(_LIB_PATH)
 
 MB_OK, MB_ERR_INVALID_ARG, MB_ERR_UNSUPPORTED, MB_ERR_WORKSPACE, MB_ERR_HIP = range(5)
@@ -149,8 +149,14 @@ def _row_stride(t: torch.Tensor) -> int:
 def _load_calls():
     """The native calls of this module (its own object: another import of the binding has its own error class)."""
     loader = importlib.machinery.ExtensionFileLoader("_mosaic_marshal", _MARSHAL_PATH)
-    native = importlib.util.module_from_spec(importlib.util.spec_from_loader("_mosaic_marshal", loader))
-    loader.exec_module(native)
+    try:
+        native = importlib.util.module_from_spec(importlib.util.spec_from_loader("_mosaic_marshal", loader))
+        loader.exec_module(native)
+        if not torch.__version__.startswith(native.torch_version):   # may load all the same, with other layouts
+            raise ImportError("built for torch " + native.torch_version)
+    except ImportError as e:   # it is compiled against the headers of one Python and one torch
+        raise ImportError("%s does not load with torch %s; it was built for another one, or not whole. %s"
+                          % (_MARSHAL_PATH, torch.__version__, _HOW_TO_BUILD)) from e
     addresses = {name: ctypes.cast(getattr(_lib, name), c_void_p).value for name in EXPORTS}
     return native.Calls(addresses, MosaicAttnError, getattr(torch._C, "_cuda_getDevice", _current_device), _raw_stream,
                         _stream)

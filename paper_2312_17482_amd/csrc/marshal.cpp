@@ -11,6 +11,7 @@
 #include <ATen/ATen.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <cstdint>
 #include <utility>
@@ -621,6 +622,10 @@ extern "C" __attribute__((visibility("default"))) PyObject* PyInit__mosaic_marsh
   PyObject* type = PyType_FromSpec(&spec);
   if (!type || PyModule_AddObject(m, "Calls", type) < 0) {
     Py_XDECREF(type);
+    Py_DECREF(m);
+    return nullptr;
+  }
+  if (PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) < 0) {
     Py_DECREF(m);
     return nullptr;
   }

@@ -155,3 +155,17 @@ def test_given_outputs_errors_and_threads():
     thread.join()
     side.synchronize()
     assert torch.all(results[0] == 3.0)
+
+
+def test_a_native_part_that_does_not_load_says_what_to_do(tmp_path, monkeypatch):
+    """As after another torch was installed: the loader's own words name a symbol and nothing else."""
+    broken = tmp_path / "_mosaic_marshal.so"
+    broken.write_bytes(b"no library")
+    monkeypatch.setattr(mb, "_MARSHAL_PATH", str(broken))
+    with pytest.raises(ImportError, match=r"build\(\)") as e:
+        mb._load_calls()
+    assert str(broken) in str(e.value) and torch.__version__ in str(e.value) and isinstance(e.value.__cause__, ImportError)
+    monkeypatch.undo()
+    monkeypatch.setattr(torch, "__version__", "1.13.1")   # one that loads, for another torch
+    with pytest.raises(ImportError, match=r"torch 1\.13\.1.*build\(\)"):
+        mb._load_calls()
