@@ -47,7 +47,7 @@ def build(verbose: bool = True, jobs: int = 8) -> str:
     cmd = marshal_command()
     if verbose:
         print(" ".join(cmd), flush=True)
-    procs.append((cmd[-7], subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    procs.append((os.path.join(CSRC, "marshal.cpp"), subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src in sources:
         obj = os.path.join(objdir, os.path.basename(src)[:-4] + ".o")
         objs.append(obj)
