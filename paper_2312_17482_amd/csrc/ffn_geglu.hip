@@ -172,7 +172,7 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
   // with twice the stages, measured a fifth slower).  Piece x of row r sits at position x ^ (r / 2) % 8, so that a
   // fragment read (one piece of 16 consecutive rows per quarter wave) touches every bank once.  Row bounds are the
   // descriptors': token rows at or beyond T and weight rows past the matrix deposit zeros.
-  // (The k offset is the scalar operand, which takes no part in the range check.)
+  // (The k offset is the scalar operand.  The range check counts it, and it stays within a row of K elements.)
   // Load i of wave w carries rows 8 (w + kWaves i) .. of the stage.
   const uint32_t lane_off =
       ((uint32_t)(lane >> 3) * (uint32_t)K + (((lane & 7) ^ (4 * (wave & 1) + (lane >> 4))) * 8)) * 2u;
@@ -197,9 +197,10 @@ __device__ __forceinline__ void gemm_tiles(const uint16_t* __restrict__ X, const
     wk_bytes = (uint32_t)k0 * (uint32_t)(kBK * 2) * (uint32_t)ldw;
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
-      if (kWT && i >= kXLoads) {   // (all K rows and all kBN columns exist)
+      if (kWT && i >= kXLoads) {   // (all K rows and all kBN columns exist, and the weight is less than 2^32 bytes: the scalar
+        // offset counts in the range check, a descriptor of 2^31 bytes took what lies behind them for zeros)
         const int row = kTRows * (wave + kWaves * (i - kXLoads));
-        rsrc[i] = raw_rsrc(W + (int64_t)row * ldw + n0, 0x7fffffffu);
+        rsrc[i] = raw_rsrc(W + (int64_t)row * ldw + n0, 0xffffffffu);
         continue;
       }
       const int row = 8 * (wave + kWaves * i), r = row - kBM;   // r: row of the weight tile

@@ -348,3 +348,27 @@ def test_weight_gradients_of_few_tokens(mb, T):
             a = a[:T] if name == "dx" else a
             rel = ((a.double() - b).norm() / b.norm()).item()
             assert rel <= (2.0 ** -22 if name == "dw2" else 1e-2), (name, rel)
+
+
+@pytest.mark.parametrize("T,hidden,inter", [(64, 4096, 147456), (945, 1024, 589824)])
+def test_geglu_backward_of_weights_above_2_gib(mb, T, hidden, inter):
+    """dx contracts over the rows of W1 | V, whose byte offsets pass 2^31: in shares of the contraction, and in one piece."""
+    print("geglu backward of large weights T=%d hidden=%d inter=%d" % (T, hidden, inter), flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    x, dy = (torch.randn((T, hidden), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    w1v = torch.empty((2 * inter, hidden), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.03, generator=gen)
+    w2 = torch.empty((hidden, inter), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.03, generator=gen)
+    assert w1v.numel() * 2 > 1 << 31
+    _, act = mb.mb_geglu_fwd(x, w1v, w2)
+    dx, dw1v, dw2 = mb.mb_geglu_bwd(dy, x, w1v, w2, act)
+    ref, start = torch.zeros((T, hidden), dtype=torch.float64, device="cuda"), 0
+    while start < inter:   # by pieces of the intermediate columns, whose gradients are independent of one another
+        piece = slice(start, min(start + 32768, inter))
+        both = torch.cat((w1v[:inter][piece], w1v[inter:][piece]))
+        d, d1v, d2 = backward_in_64_bits(x, both, w2[:, piece], dy, act[:, piece])
+        ref += d
+        n = piece.stop - piece.start
+        for a, b in ((dw1v[:inter][piece], d1v[:n]), (dw1v[inter:][piece], d1v[n:]), (dw2[:, piece], d2)):
+            assert ((a.double() - b).norm() / b.norm()).item() <= 1e-2, start
+        start = piece.stop
+    assert ((dx.double() - ref).norm() / ref.norm()).item() <= 1e-2
