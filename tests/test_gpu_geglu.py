@@ -350,6 +350,58 @@ def test_weight_gradients_of_few_tokens(mb, T):
             assert rel <= (2.0 ** -22 if name == "dw2" else 1e-2), (name, rel)
 
 
+# (T, hidden, inter), and which forms of the backward's kernels they take that no size above does: dx in shares of the
+# contraction (shares x 64 tokens x stages), in one piece (64 tokens), weight gradients (64 rows x splits), gate backward
+# (64 tokens, one or several tiles per workgroup)
+@pytest.mark.parametrize("T,hidden,inter", [
+    (200, 768, 3072),      # dx in 8 x 1 x 3
+    (200, 768, 1536),      # dx in 8 x 1 x 2
+    (641, 768, 3072),      # dx in 8 x 2 x 3
+    (1357, 768, 2304),     # dx in 8 x 3 x 2
+    (3084, 1024, 4096),    # dx in 4 x 4 x 2, gate backward 4, weight gradients 4 x 1
+    (5467, 768, 3072),     # dx in 4 x 5 x 2
+    (4044, 768, 2304),     # dx in 2 x 2 x 3, gate backward 3, weight gradients 4 x 3
+    (10926, 768, 3072),    # dx in 2 x 5 x 2
+    (13845, 768, 768),     # dx 3, weight gradients 4 x 6
+    (12497, 1024, 1024),   # dx 4, weight gradients 4 x 4
+    (24790, 1024, 1024),   # dx 4, several tiles per workgroup
+    (8079, 768, 3072),     # gate backward 2, several tiles per workgroup, three stages
+    (961, 768, 768),       # weight gradients 2 x 2
+    (325, 256, 256),       # weight gradients 2 x 3
+    (945, 256, 1024),      # weight gradients 2 x 4
+    (3847, 256, 256),      # weight gradients 2 x 5
+    (4629, 256, 256),      # weight gradients 2 x 6
+])
+@pytest.mark.parametrize("counted", [False, True])
+def test_geglu_every_form_of_the_backward(mb, T, hidden, inter, counted):
+    """Forward and backward against 64 bits on the device.  dW2 on its own operands as in the tests above: 2^-22 of the norm,
+    or what one chain of T / 16 additions gives where that is more.  Rows past the last token hold NaN and stay untouched."""
+    print("geglu forms T=%d hidden=%d inter=%d counted=%s" % (T, hidden, inter, counted), flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    rows = T + 60 if counted else T
+
+    def normal(*shape, std=1.0):
+        return (torch.randn(shape, generator=gen, device="cuda") * std).bfloat16()
+    x, w1v, w2, dy = normal(rows, hidden), normal(2 * inter, hidden, std=0.03), normal(hidden, inter, std=0.03), normal(rows, hidden)
+    x[T:], dy[T:] = float("nan"), float("nan")
+    meta = torch.tensor([T, 0], dtype=torch.int32, device="cuda") if counted else None
+    act = torch.full((rows + 2, inter), 9.0, dtype=torch.bfloat16, device="cuda")
+    y, dx = (torch.full((rows + 2, hidden), 9.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    mb.mb_geglu_fwd(x, w1v, w2, meta=meta, act=act[:rows], y=y[:rows])
+    _, dw1v, dw2 = mb.mb_geglu_bwd(dy, x, w1v, w2, act[:rows], meta=meta, dx=dx[:rows])
+    assert all(torch.all(t[T:] == 9.0) for t in (act, y, dx))
+    h, g = x[:T].double() @ w1v[:inter].double().T, x[:T].double() @ w1v[inter:].double().T
+    ref = (0.5 * h * torch.erfc(-h * 0.5 ** 0.5) * g, act[:T].double() @ w2.double().T) + backward_in_64_bits(
+        x[:T], w1v, w2, dy[:T], act[:T])
+    rel = {}
+    for name, a, b in zip(("act", "y", "dx", "dw1v", "dw2"), (act[:T], y[:T], dx[:T], dw1v, dw2), ref):
+        rel[name] = ((a.double() - b).norm() / b.norm()).item()
+        err = (a.double() - b).abs().max().item() / b.abs().max().item()
+        assert rel[name] <= 1e-2 and err <= 2.0 ** -6, (name, rel, err)
+    print("  " + "  ".join("%s %.2e" % x for x in rel.items()), flush=True)
+    assert rel["dw2"] <= max(2.0 ** -22, 2.0 ** -24 * (T / 32) ** 0.5)
+
+
 @pytest.mark.parametrize("T,hidden,inter", [(64, 4096, 147456), (945, 1024, 589824)])
 def test_geglu_backward_of_weights_above_2_gib(mb, T, hidden, inter):
     """dx contracts over the rows of W1 | V, whose byte offsets pass 2^31: in shares of the contraction, and in one piece."""
