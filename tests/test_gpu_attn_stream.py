@@ -93,3 +93,102 @@ def test_no_load_of_the_attention_kernels_comes_too_early(tmp_path):
         loads, found = too_early(assembly(f, tmp_path / "code.s"))
         print(os.path.basename(f), loads, "loads into LDS", flush=True)
         assert loads > 0 and not found, found[:10]
+
+
+def packed_call(mb, q, k, v, do, cu, L, out, **opt):
+    """Forward and backward; `out`: views for o, dq, dk, dv.  Returns them and lse."""
+    H, T = q.shape[1], int(cu[-1])
+    lse = torch.zeros((H, T), device="cuda")
+    slopes = mb.mb_alibi_slopes(H).cuda()
+    mb.mb_alibi_attn_fwd(q, k, v, cu, L, slopes, 0.125, out=out[0], lse=lse, T=T, **opt)
+    mb.mb_alibi_attn_bwd(do, q, k, v, out[0], lse, cu, L, slopes, 0.125, dq=out[1], dk=out[2], dv=out[3], T=T, **opt)
+    mb.mb_device_status()
+    return list(out) + [lse]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [False, True])
+@pytest.mark.parametrize("L,lengths,stride", [(129, [129, 1, 128, 65], ((1 << 30) // 129 - 1) // 8 * 8), (128, [128, 1, 127, 33], (1 << 24) - 8)])
+def test_rows_as_far_apart_as_32_bit_offsets_allow(L, lengths, stride, rows):
+    """The any-length kernels with a span just under 2^31 bytes (tiles requested past the end wrap round 2^32), the single-tile
+    forward with units between 2^31 and 2^32 bytes: the same bits as from dense rows."""
+    from paper_2312_17482_amd import binding as mb
+    print("attention rows %d elements apart, L=%d rows=%s" % (stride, L, rows), flush=True)
+    H, D, T = 2, 64, sum(lengths)
+    assert L <= 128 or L * stride * 2 < 1 << 31
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lengths)]), dtype=torch.int32, device="cuda")
+    data = torch.randn((4, T, H, D), generator=gen, device="cuda").bfloat16()
+    dense = packed_call(mb, *data, cu, L, torch.zeros_like(data))
+    far = torch.empty(T * stride, dtype=torch.bfloat16, device="cuda").as_strided((T, 8, H, D), (stride, H * D, D, 1))
+    far[:, :4] = data.transpose(0, 1)
+    far[:, 4:] = 0.0
+    opt = {"token_rows": torch.arange(T, dtype=torch.int32, device="cuda")} if rows else {}
+    got = packed_call(mb, *(far[:, i] for i in range(4)), cu, L, [far[:, 4 + i] for i in range(4)], **opt)
+    for name, a, b in zip(("o", "dq", "dk", "dv", "lse"), got, dense):
+        assert torch.equal(a, b), name
+    assert torch.equal(far[:, :4], data.transpose(0, 1))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,lengths", [(200, [65, 130, 64, 193, 1, 129, 33, 200]), (128, [65, 128, 64, 31, 1, 127, 33, 96])])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_infinities_and_nan_stay_in_their_sequence(L, lengths, bad):
+    """A sequence that holds nothing else leaves its neighbours' bits alone: the rows behind a ragged end are the next sequence's.
+    The same for keys and values that the key limit masks out."""
+    from paper_2312_17482_amd import binding as mb
+    print("attention with %s, L=%d" % (bad, L), flush=True)
+    H, D, T = 3, 64, sum(lengths)
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    start = np.concatenate([[0], np.cumsum(lengths)])
+    cu = torch.tensor(start, dtype=torch.int32, device="cuda")
+    data = torch.randn((4, T, H, D), generator=gen, device="cuda").bfloat16()
+    clean = packed_call(mb, *data, cu, L, torch.zeros_like(data))
+    for b in (1, 3, 6):
+        spoilt, here = data.clone(), slice(int(start[b]), int(start[b + 1]))
+        spoilt[:, here] = bad
+        others = torch.ones(T, dtype=torch.bool, device="cuda")
+        others[here] = False
+        got = packed_call(mb, *spoilt, cu, L, torch.zeros_like(data))
+        for name, x, y in zip(("o", "dq", "dk", "dv"), got, clean):
+            assert torch.equal(x[others], y[others]), (name, b)
+            assert not torch.isfinite(x[here]).any(), (name, b)
+        assert torch.equal(got[4][:, others], clean[4][:, others])
+    # keys that do not count, at the end of their sequence
+    limit = torch.tensor([max(n - 30, 1) for n in lengths], dtype=torch.int32, device="cuda")
+    masked = torch.cat([torch.arange(n, device="cuda") >= int(m) for n, m in zip(lengths, limit)])
+    clean = packed_call(mb, *data, cu, L, torch.zeros_like(data), key_lens=limit)
+    spoilt = data.clone()
+    spoilt[1:3, masked] = bad
+    got = packed_call(mb, *spoilt, cu, L, torch.zeros_like(data), key_lens=limit)
+    for name, x, y in zip(("o", "dq", "dk", "dv", "lse"), got, clean):
+        assert torch.equal(x, y), name
+    assert torch.all(got[2][masked] == 0) and torch.all(got[3][masked] == 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [33, 65, 128, 129, 193])
+@pytest.mark.parametrize("tensor,bad", [("q", float("nan")), ("k", float("nan")), ("k", float("inf")), ("v", float("nan")),
+                                        ("v", float("-inf")), ("do", float("nan")), ("do", float("inf"))])
+def test_one_value_that_is_not_finite(n, tensor, bad):
+    """In the last token of a ragged sequence: what is finite and what is not is as in 64 bits, and the finite values agree."""
+    from paper_2312_17482_amd import binding as mb
+    H, D = 2, 64
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    data = torch.randn((4, n, H, D), generator=gen, device="cuda").bfloat16() * 0.5
+    data[("q", "k", "v", "do").index(tensor), n - 1, :, 5] = bad
+    cu = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    got = packed_call(mb, *data, cu, n, torch.zeros_like(data))
+    q, k, v, do = (t.double().cpu().transpose(0, 1) for t in data)
+    slopes = torch.tensor(orc.alibi_slopes(H))
+    at = torch.arange(n, dtype=torch.float64)
+    p = torch.softmax(q @ k.mT * 0.125 - slopes[:, None, None] * (at[:, None] - at).abs(), -1)
+    o = p @ v
+    ds = p * (do @ v.mT - (do * o).sum(-1, keepdim=True))
+    ref = (o, ds @ k * 0.125, ds.mT @ q * 0.125, p.mT @ do)
+    for name, x, y in zip(("o", "dq", "dk", "dv"), got, ref):
+        x = x.double().cpu().transpose(0, 1)
+        assert torch.equal(torch.isfinite(x), torch.isfinite(y)), name
+        where = torch.isfinite(y)
+        if where.any():
+            assert (x[where] - y[where]).abs().max() <= BF16_TOL[0] * max(1.0, float(y[where].abs().max())), name
