@@ -7,6 +7,7 @@ there is no CPU or PyTorch fallback.  The calls that a step makes many times are
 """
 from __future__ import annotations
 
+import copyreg
 import ctypes
 import importlib.machinery
 import importlib.util
@@ -165,6 +166,14 @@ def _load_calls():
 # Host time of a whole layer step of 8 x 128 positions, eight calls (33 us of kernels): 60 us with these calls marshalled in
 # Python; see csrc/marshal.cpp.
 _calls = _load_calls()
+
+
+def _calls_of_this_module():
+    return _calls
+
+
+copyreg.pickle(type(_calls), lambda _: (_calls_of_this_module, ()))   # its methods pickle by name, as functions do
+
 mb_unpad_index = _calls.mb_unpad_index
 mb_unpad = _calls.mb_unpad
 mb_pad = _calls.mb_pad

@@ -4,6 +4,7 @@ import importlib.machinery
 import importlib.util
 import inspect
 import os
+import pickle
 import re
 import threading
 
@@ -295,6 +296,13 @@ def test_signatures_and_argument_errors():
             f(*[torch.zeros(1)] * required, **{next(iter(parameters)): 1})
         with pytest.raises(TypeError):
             f(*[object()] * required)
+
+
+def test_the_calls_pickle_by_name():
+    """As a program's object that holds one of them is saved, or handed to another process."""
+    for name in NATIVE:
+        f = getattr(mb, name)
+        assert pickle.loads(pickle.dumps(f)) == f, name
 
 
 def test_shapes_and_types_are_checked():
