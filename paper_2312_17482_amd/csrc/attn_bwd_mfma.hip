@@ -71,6 +71,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
   __shared__ __attribute__((aligned(16))) float sL[kRing][3][kTileS];    // -lse / scale (-inf past the end): alone, with the
                                                                          // row's bias left and right of the diagonal
   __shared__ __attribute__((aligned(16))) float sD[kRing][kTileS];       // -Delta
+  __shared__ __attribute__((aligned(16))) int32_t sRows[kMode == kRowsIdentity ? 4 : StageRows::kWords];
 
   int start, n, nk, ktile, h;   // nk <= n: the sequence's first nk tokens are its keys
   if (!plan_fetch(plan, plan_cap, &start, &n, &nk, &ktile, &h)) return;   // this XCD's list is shorter
@@ -103,44 +104,70 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
 
   // ---- loads: this wave's K and V rows, then its share of the Q / dO tiles
   const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t*)smem);
-  {
-    const u32x4 k_rsrc = stage_rsrc(k + row0 * ks + h * kD, ks, nk), v_rsrc = stage_rsrc(v + row0 * vs + h * kD, vs, nk);
+  const StageRows where(rows, start, n, sRows, wave);
+  int first_row[4];   // without descriptors: rows of the wave's share of two tiles
+  if (!contig) {
+    int own_row[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) own_row[j] = stage_row_of(rows, start, kw + 8 * j + (lane >> 3), nk);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      first_row[j] = stage_row_of(rows, start, (j >> 1) * kTileS + 8 * (wave + 4 * (j & 1)) + (lane >> 3), n);
+    rows_known(own_row);
+    rows_known(first_row);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const uint32_t at = lds0 + (2 * kRegion + (32 * wave + 8 * j) * kD) * 2;
-      if (contig) {
-        const uint32_t row = kw + 8 * j;
-        stage_rows(at, stage_lane_off(lane, j & 1, ks) + row * (uint32_t)ks * 2u, k_rsrc);
-        stage_rows(at + kRegion * 2, stage_lane_off(lane, j & 1, vs) + row * (uint32_t)vs * 2u, v_rsrc);
-      } else {
-        stage_each(at, stage_address(k + h * kD, ks, rows, start, kw + 8 * j, nk, lane, j & 1));
-        stage_each(at + kRegion * 2, stage_address(v + h * kD, vs, rows, start, kw + 8 * j, nk, lane, j & 1));
-      }
+      const bool there = kw + 8 * j + (lane >> 3) < nk;
+      stage_each(at, stage_address(k + h * kD, ks, own_row[j], there, stage_piece(lane, j & 1) * 16));
+      stage_each(at + kRegion * 2, stage_address(v + h * kD, vs, own_row[j], there, stage_piece(lane, j & 1) * 16));
+    }
+  } else {
+    const u32x4 k_rsrc = stage_rsrc(k + row0 * ks + h * kD, ks, nk), v_rsrc = stage_rsrc(v + row0 * vs + h * kD, vs, nk);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t at = lds0 + (2 * kRegion + (32 * wave + 8 * j) * kD) * 2, row = kw + 8 * j;
+      stage_rows(at, stage_lane_off(lane, j & 1, ks) + row * (uint32_t)ks * 2u, k_rsrc);
+      stage_rows(at + kRegion * 2, stage_lane_off(lane, j & 1, vs) + row * (uint32_t)vs * 2u, v_rsrc);
     }
   }
   const u32x4 q_rsrc = stage_rsrc(q + row0 * qs + h * kD, qs, n), g_rsrc = stage_rsrc(dout + row0 * dos + h * kD, dos, n);
-  // the wave's first 8 rows of the tile to load next; its second 8 rows lie 32 behind them
+  // the wave's first 8 rows of the tile to load next; its second 8 rows lie 32 behind them (without descriptors: the lane's
+  // place among the row numbers, and inside a row)
   uint32_t q_off = stage_lane_off(lane, wave & 1, qs) + 8u * wave * (uint32_t)qs * 2u;
   uint32_t g_off = stage_lane_off(lane, wave & 1, dos) + 8u * wave * (uint32_t)dos * 2u;
-  // The j-th of the wave's four loads of tile t into `region`; the tiles are taken in order.
-  auto issue_row = [&](int t, int region, int j) {
-    const int i = j >> 1;
+  if (!contig) {
+    q_off = StageRows::lane_off(wave, lane);
+    g_off = stage_piece(lane, wave & 1) * 16;
+  }
+  constexpr int kRowLoads = 4;   // loads per wave and tile
+  auto place = [&](int region, int j) {   // of the j-th of them: Q and dO rows by turns
+    return lds0 + (uint32_t)(region * kRegion + ((j & 1) == 0 ? 0 : kTileS * kD) + 8 * (wave + 4 * (j >> 1)) * kD) * 2;
+  };
+  auto issue_row = [&](int region, int j) {   // with descriptors; the tiles are taken in order
     const bool is_q = (j & 1) == 0;
-    const uint32_t at = lds0 + (uint32_t)(region * kRegion + (is_q ? 0 : kTileS * kD) + 8 * (wave + 4 * i) * kD) * 2;
     uint32_t& off = is_q ? q_off : g_off;
-    const int64_t stride = is_q ? qs : dos;
-    if (contig) {
-      stage_rows(at, off, is_q ? q_rsrc : g_rsrc);
-      off += 64u * (uint32_t)stride;
-    } else {
-      stage_each(at, stage_address((is_q ? q : dout) + h * kD, stride, rows, start, t * kTileS + 8 * (wave + 4 * i), n,
-                                         lane, wave & 1));
+    stage_rows(place(region, j), off, is_q ? q_rsrc : g_rsrc);
+    off += 64u * (uint32_t)(is_q ? qs : dos);
+  };
+  auto issue_each = [&](int t, int region, const int* row) {   // without: tile t, whose rows are `row`
+#pragma unroll
+    for (int j = 0; j < kRowLoads; ++j) {
+      const bool is_q = (j & 1) == 0;
+      stage_each(place(region, j), stage_address((is_q ? q : dout) + h * kD, is_q ? qs : dos, row[j >> 1],
+                                                 t * kTileS + 8 * (wave + 4 * (j >> 1)) + (lane >> 3) < n, g_off));
     }
   };
-  constexpr int kRowLoads = 4;   // loads per wave and tile
-  auto issue_rows = [&](int t, int region) {
+  // Requests tile t, and before it (without descriptors) the row numbers of tile `ahead`.
+  auto issue_rows = [&](int t, int region, int ahead) {
+    if (contig) {
 #pragma unroll
-    for (int j = 0; j < kRowLoads; ++j) issue_row(t, region, j);
+      for (int j = 0; j < kRowLoads; ++j) issue_row(region, j);
+    } else {
+      const int row[2] = {where.get(t, 0, lane), where.get(t, 1, lane)};
+      if (ahead > 0) where.request(ahead, q_off);
+      issue_each(t, region, row);
+    }
   };
   // lse and Delta of a tile: the first wave brings one and the second the other (the other waves' loads, which keep the
   // number of loads the same, read nothing).
@@ -165,11 +192,18 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
     const int i = min(t * kTileS + lane, n - 1);
     return (wave == 0 ? lse : delta)[(int64_t)h * T + start + i];
   };
-  issue_rows(0, 0);
+  if (contig) {
+    issue_rows(0, 0, 0);
+  } else {
+    issue_each(0, 0, first_row);
+    where.request(2, q_off);
+    where.request(3, q_off);
+  }
   issue_raw(2, 2);
   issue_raw(3, 3);
   const float raw0 = first_raw(0), raw1 = first_raw(1);
-  issue_rows(1, 1);
+  if (contig) issue_rows(1, 1, 0);
+  else issue_each(1, 1, first_row + 2);
   store_tables(0, 0, raw0);
   store_tables(1, 1, raw1);
 
@@ -324,8 +358,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
   if (!wave_active) {   // (a loop of its own: inside the other one the accumulators would be copied in every step)
     for (int t = 0; t + 1 < ntiles; ++t) {
       staged_barrier<kRowLoads + 1>();
-      if (t == 0) issue_rows(2, 2);
-      issue_rows(t + 3, (t + 3) & (kRing - 1));
+      if (t == 0) issue_rows(2, 2, 0);
+      issue_rows(t + 3, (t + 3) & (kRing - 1), t + 4);
       issue_raw(t + 4, t & (kRing - 1));
       if (wave < 2) store_tables(t + 2, (t + 2) & (kRing - 1), sRaw[wave][(t + 2) & (kRing - 1)][lane]);
     }
@@ -344,18 +378,18 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(
   for (int t = 0; t + 1 < ntiles; ++t) {
     const int here = t & (kRing - 1), next = (t + 1) & (kRing - 1), after = (t + 2) & (kRing - 1), to = (t + 3) & (kRing - 1);
     staged_barrier<kRowLoads + 1>();
-    if (t == 0) issue_rows(2, 2);   // (the region of the K rows)
+    if (t == 0) issue_rows(2, 2, 0);   // (the region of the K rows)
     // Loads in one go block the waves for 300 to 500 cycles, so they are spread over the step's matrix instructions (not
     // the ones with an address per lane: there are no registers left for those).
-    if (!contig) issue_rows(t + 3, to);
+    if (!contig) issue_rows(t + 3, to, t + 4);
     const Places tr = places_tr(here * kRegionBytes), row = places_row(next * kRegionBytes);
     float raw = 0.f;
     auto first_half = [&](int j) {
-      if ((j == 0 || j == 2) && contig) issue_row(t + 3, to, j >> 1);
+      if ((j == 0 || j == 2) && contig) issue_row(to, j >> 1);
       if (j == 3) issue_raw(t + 4, here);
     };
     auto second_half = [&](int j) {
-      if ((j == 0 || j == 2) && contig) issue_row(t + 3, to, 2 + (j >> 1));
+      if ((j == 0 || j == 2) && contig) issue_row(to, 2 + (j >> 1));
       if (j == 1 && wave < 2) raw = sRaw[wave][after][lane];
       if (j == 3 && wave < 2) store_tables(t + 2, after, raw);
     };
@@ -419,6 +453,7 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
   const int32_t* rows = kMode == kRowsIdentity ? nullptr : token_rows;
   __shared__ __attribute__((aligned(1024))) uint16_t smem[3 * kRegion];   // regions of a K and a V tile each
   __shared__ __attribute__((aligned(16))) float sDelta[kTile];       // -Delta of this workgroup's queries
+  __shared__ __attribute__((aligned(16))) int32_t sRows[kMode == kRowsIdentity ? 4 : StageRows::kWords];
 
   int start, n, nk, qtile, h;   // nk <= n: the sequence's first nk tokens are its keys
   if (!plan_fetch(plan, plan_cap, &start, &n, &nk, &qtile, &h)) return;
@@ -443,45 +478,77 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
 
   // ---- loads: this wave's Q and dO rows, then its share of the K / V tiles
   const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t*)smem);
-  {
-    const u32x4 q_rsrc = stage_rsrc(q + row0 * qs + h * kD, qs, n), g_rsrc = stage_rsrc(dout + row0 * dos + h * kD, dos, n);
+  const StageRows where(rows, start, nk, sRows, wave);
+  int first_row[2], o_row[4];   // without descriptors: rows of the wave's share of the first tile, and of O
+  if (!contig) {
+    int own_row[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) own_row[j] = stage_row_of(rows, start, qw + 8 * j + (lane >> 3), n);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o_row[j] = stage_row_of(rows, start, q0 + 32 * j + st_row, n);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) first_row[j] = stage_row_of(rows, start, 8 * (wave + 4 * j) + (lane >> 3), nk);
+    rows_known(own_row);
+    rows_known(o_row);
+    rows_known(first_row);
+    where.request(1, StageRows::lane_off(wave, lane));
+    where.request(2, StageRows::lane_off(wave, lane));
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const uint32_t at = lds0 + (kRegion + (32 * wave + 8 * j) * kD) * 2;
-      if (contig) {
-        const uint32_t row = qw + 8 * j;
-        stage_rows(at, stage_lane_off(lane, j & 1, qs) + row * (uint32_t)qs * 2u, q_rsrc);
-        stage_rows(at + kRegion * 2, stage_lane_off(lane, j & 1, dos) + row * (uint32_t)dos * 2u, g_rsrc);
-      } else {
-        stage_each(at, stage_address(q + h * kD, qs, rows, start, qw + 8 * j, n, lane, j & 1));
-        stage_each(at + kRegion * 2, stage_address(dout + h * kD, dos, rows, start, qw + 8 * j, n, lane, j & 1));
-      }
+      const bool there = qw + 8 * j + (lane >> 3) < n;
+      stage_each(at, stage_address(q + h * kD, qs, own_row[j], there, stage_piece(lane, j & 1) * 16));
+      stage_each(at + kRegion * 2, stage_address(dout + h * kD, dos, own_row[j], there, stage_piece(lane, j & 1) * 16));
+    }
+  } else {
+    const u32x4 q_rsrc = stage_rsrc(q + row0 * qs + h * kD, qs, n), g_rsrc = stage_rsrc(dout + row0 * dos + h * kD, dos, n);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t at = lds0 + (kRegion + (32 * wave + 8 * j) * kD) * 2, row = qw + 8 * j;
+      stage_rows(at, stage_lane_off(lane, j & 1, qs) + row * (uint32_t)qs * 2u, q_rsrc);
+      stage_rows(at + kRegion * 2, stage_lane_off(lane, j & 1, dos) + row * (uint32_t)dos * 2u, g_rsrc);
     }
   }
   const u32x4 k_rsrc = stage_rsrc(k + row0 * ks + h * kD, ks, nk), v_rsrc = stage_rsrc(v + row0 * vs + h * kD, vs, nk);
-  // the wave's first 8 rows of the tile to load next; its second 8 rows lie 32 behind them
+  // the wave's first 8 rows of the tile to load next; its second 8 rows lie 32 behind them (without descriptors: the lane's
+  // place among the row numbers, and inside a row)
   uint32_t k_off = stage_lane_off(lane, wave & 1, ks) + 8u * wave * (uint32_t)ks * 2u;
   uint32_t v_off = stage_lane_off(lane, wave & 1, vs) + 8u * wave * (uint32_t)vs * 2u;
+  if (!contig) {
+    k_off = StageRows::lane_off(wave, lane);
+    v_off = stage_piece(lane, wave & 1) * 16;
+  }
   constexpr int kRowLoads = 4;   // loads per wave and tile
-  auto issue_row = [&](int t, int region, int j) {   // the j-th of them, of tile t; the tiles are taken in order
-    const int i = j >> 1;
+  auto place = [&](int region, int j) {   // of the j-th of them: K and V rows by turns
+    return lds0 + (uint32_t)(region * kRegion + ((j & 1) == 0 ? 0 : kTileS * kD) + 8 * (wave + 4 * (j >> 1)) * kD) * 2;
+  };
+  auto issue_row = [&](int region, int j) {   // with descriptors; the tiles are taken in order
     const bool is_k = (j & 1) == 0;
-    const uint32_t at = lds0 + (uint32_t)(region * kRegion + (is_k ? 0 : kTileS * kD) + 8 * (wave + 4 * i) * kD) * 2;
     uint32_t& off = is_k ? k_off : v_off;
-    const int64_t stride = is_k ? ks : vs;
-    if (contig) {
-      stage_rows(at, off, is_k ? k_rsrc : v_rsrc);
-      off += 64u * (uint32_t)stride;
-    } else {
-      stage_each(at, stage_address((is_k ? k : v) + h * kD, stride, rows, start, t * kTileS + 8 * (wave + 4 * i), nk, lane,
-                                   wave & 1));
+    stage_rows(place(region, j), off, is_k ? k_rsrc : v_rsrc);
+    off += 64u * (uint32_t)(is_k ? ks : vs);
+  };
+  auto issue_each = [&](int t, int region, const int* row) {   // without: tile t, whose rows are `row`
+#pragma unroll
+    for (int j = 0; j < kRowLoads; ++j) {
+      const bool is_k = (j & 1) == 0;
+      stage_each(place(region, j), stage_address((is_k ? k : v) + h * kD, is_k ? ks : vs, row[j >> 1],
+                                                 t * kTileS + 8 * (wave + 4 * (j >> 1)) + (lane >> 3) < nk, v_off));
     }
   };
+  // Requests tile t, and before it (without descriptors) the row numbers of the tile behind it.
   auto issue_tile = [&](int t, int region) {
+    if (contig) {
 #pragma unroll
-    for (int j = 0; j < kRowLoads; ++j) issue_row(t, region, j);
+      for (int j = 0; j < kRowLoads; ++j) issue_row(region, j);
+    } else {
+      const int row[2] = {where.get(t, 0, lane), where.get(t, 1, lane)};
+      if (t > 1) where.request(t + 1, k_off);   // (those of tiles 1 and 2 are here)
+      issue_each(t, region, row);
+    }
   };
-  issue_tile(0, 0);
+  if (contig) issue_tile(0, 0);
+  else issue_each(0, 0, first_row);
 
   // ---- places in a region (bytes): K and V rows, transposed patches of K
   const char* const lds = reinterpret_cast<const char*>(smem);
@@ -497,7 +564,7 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
     for (int it = 0; it < 4; ++it) {
       to[it] = u32x4{0u, 0u, 0u, 0u};
       const int i = q0 + 32 * it + st_row;
-      if (i < n) to[it] = *reinterpret_cast<const u32x4*>(o + tok_row(rows, start + i) * os + h * kD + st_col);
+      if (i < n) to[it] = *reinterpret_cast<const u32x4*>(o + (contig ? (int64_t)(row0 + i) : (int64_t)o_row[it]) * os + h * kD + st_col);
     }
     staged_barrier<0>();
 #pragma unroll
@@ -626,13 +693,13 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dq_kernel(
     for (int s = 0; s < 4; ++s) ta[s >> 1][s & 1] = tr_at[s >> 1][s & 1] + region * (kRegion * 2);
     const int rem = nk - j0;
     if (contig) {
-      issue_row(jt + 2, to, 0);
-      issue_row(jt + 2, to, 1);
+      issue_row(to, 0);
+      issue_row(to, 1);
     }
     kblock(ra, ta, j0, 0, rem);
     if (contig) {
-      issue_row(jt + 2, to, 2);
-      issue_row(jt + 2, to, 3);
+      issue_row(to, 2);
+      issue_row(to, 3);
     }
     kblock(ra, ta, j0, 1, rem);
     region = region == 2 ? 0 : region + 1;

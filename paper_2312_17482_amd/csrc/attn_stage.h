@@ -43,15 +43,56 @@ __device__ __forceinline__ void stage_words(uint32_t lds, uint32_t lane_off, u32
 __device__ __forceinline__ void stage_each(uint32_t lds, const void* lane_ptr) { load_to_lds_each(lds, lane_ptr); }
 
 // Rows that are not consecutive, or too far apart for a descriptor: every lane's own address (`head`: the head's columns in
-// buffer row 0).  Lanes whose row is at or beyond `count` read zeros here.
+// buffer row 0, `row`: the buffer row of the lane's token).  Lanes without a token read zeros here.
 static __device__ const uint32_t kZeroPiece[4] = {0u, 0u, 0u, 0u};
-__device__ __forceinline__ const void* stage_address(const uint16_t* head, int64_t stride, const int32_t* __restrict__ rows,
-                                                     int start, int first, int count, int lane, int odd) {
-  const int i = first + (lane >> 3);
+__device__ __forceinline__ const void* stage_address(const uint16_t* head, int64_t stride, int row, bool there, uint32_t piece_bytes) {
   const void* p = kZeroPiece;
-  if (i < count) p = head + tok_row(rows, start + i) * stride + stage_piece(lane, odd) * 8;
+  if (there) p = reinterpret_cast<const char*>(head + (int64_t)row * stride) + piece_bytes;
   return p;
 }
+// The buffer row of token i of a sequence that has `count` (past the end: of its last token).
+__device__ __forceinline__ int stage_row_of(const int32_t* __restrict__ rows, int start, int i, int count) {
+  const int t = start + min(i, count - 1);
+  return rows ? rows[t] : t;
+}
+
+// (waited for here: among the loads into LDS, of which the compiler knows nothing, it would wait for all of those as well)
+template <int kN>
+__device__ __forceinline__ void rows_known(int (&row)[kN]) {
+#pragma unroll
+  for (int j = 0; j < kN; ++j) asm volatile("" : "+v"(row[j]));
+}
+
+// Where token_rows says where the rows are, a wave brings the row numbers of its 16 rows of a tile (8 w .. + 7 and 32 behind
+// them) to LDS a step before it requests the rows.  A number that a lane waits for in a register is waited for behind
+// every tile requested before it, which puts each step's loads a memory round trip behind the last ones.  So and now, masks with
+// holes: 64 sequences of up to 512 tokens, 12 heads, forward 62 and 48 us, dQ + dK/dV 177 and 131; 16 of up to 1815, 16 heads, 150
+// and 116, 382 and 303.
+struct StageRows {
+  static constexpr int kWords = 2 * 4 * 64;   // LDS: two tiles, four waves
+  const int32_t* rows;   // the sequence's row numbers, nullptr: token t sits in row t
+  int start, count, wave;
+  int32_t* part;         // this wave's words
+  __device__ __forceinline__ StageRows(const int32_t* all, int start_, int count_, int32_t* words, int wave_)
+      : rows(all ? all + start_ : nullptr), start(start_), count(count_), wave(wave_), part(words + wave_ * 64) {}
+  // byte offset of the number that a lane brings of the first tile
+  static __device__ __forceinline__ uint32_t lane_off(int wave, int lane) {
+    return (uint32_t)(8 * wave + (lane & 7) + 4 * (lane & 8)) * 4u;
+  }
+  __device__ __forceinline__ void request(int t, uint32_t lane_off) const {   // of tile t (past the end: zeros)
+    if (!rows) return;
+    const uint64_t a = reinterpret_cast<uint64_t>(rows);
+    const u32x4 rsrc = {(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a),
+                        (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu),
+                        (uint32_t)__builtin_amdgcn_readfirstlane(count * 4), 0x00020000u};
+    const uint32_t lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) int32_t*)part);
+    stage_words(__builtin_amdgcn_readfirstlane(lds + (t & 1) * 1024), lane_off + (uint32_t)t * 256u, rsrc);
+  }
+  // the row of the lane's token in the wave's first (half 0) or second eight rows of tile t
+  __device__ __forceinline__ int get(int t, int half, int lane) const {
+    return rows ? part[(t & 1) * 256 + half * 8 + (lane >> 3)] : start + t * 64 + 8 * (wave + 4 * half) + (lane >> 3);
+  }
+};
 
 // Byte offsets of what a lane reads of a staged tile as matrix operands.  Rows (lds_read8): k-step s takes columns
 // 16 s + 8 g .. + 7 of row lane % 32, the next 32 rows lie 4096 bytes on.

@@ -9,7 +9,7 @@ import torch
 
 from oracle import mosaic_oracle as orc
 from paper_2312_17482_amd import build, workloads as wl
-from tests.helpers import err_stats, run_oracle, to_dev
+from tests.helpers import err_stats, replay_us, run_oracle, to_dev
 from tests.test_lds_load import assembly, too_early
 
 BF16_TOL = (2e-2, 1e-2)   # as for all bf16 parity tests
@@ -84,6 +84,33 @@ def test_tile_counts_and_row_modes(mode):
     for b, n in enumerate(lengths):
         if n:
             assert np.max(np.abs(got[:, start[b]:start[b] + n] - ref["lse"][b, :, :n])) <= 1e-3, n
+
+
+@pytest.mark.gpu
+def test_rows_with_holes_cost_little_more_than_consecutive_ones():
+    """64 sequences of up to 512 tokens out of a padded batch, the mask's holes in the middle of each or its padding behind it:
+    at most a quarter more, in either direction (1.09; 1.43 where a wave waited for row numbers among its loads of rows)."""
+    from paper_2312_17482_amd import binding as mb
+    B, L, H = 64, 512, 12
+    lengths = np.random.default_rng(3).integers(64, L - 1, size=B)
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lengths)]), dtype=torch.int32, device="cuda")
+    T = int(lengths.sum())
+    data = torch.randn((4, B * L, H, 64), device="cuda").bfloat16()
+    out, lse = torch.empty_like(data), torch.zeros((H, T), device="cuda")
+    slopes, plan = mb.mb_alibi_slopes(H).cuda(), mb.mb_attn_plan(cu, L, H)
+    workspace = torch.empty(mb.mb_alibi_attn_bwd_workspace_bytes(B, T, L, H, 64, mb.MB_BF16), dtype=torch.uint8, device="cuda")
+    times = []
+    for hole in (0, 1):
+        rows = torch.tensor(np.concatenate([b * L + np.arange(n) + hole * (np.arange(n) > n // 2) for b, n in enumerate(lengths)]),
+                            dtype=torch.int32, device="cuda")
+        opt = dict(token_rows=rows, T=T, plan=plan)
+        torch.cuda.synchronize()
+        times.append([replay_us(f) for f in (
+            lambda: mb.mb_alibi_attn_fwd(*data[:3], cu, L, slopes, 0.125, out=out[0], lse=lse, **opt),
+            lambda: mb.mb_alibi_attn_bwd(data[3], *data[:3], out[0], lse, cu, L, slopes, 0.125, dq=out[1], dk=out[2], dv=out[3],
+                                         workspace=workspace, **opt))])
+    print("consecutive %.1f %.1f us, with holes %.1f %.1f us" % tuple(times[0] + times[1]), flush=True)
+    assert all(b <= 1.25 * a for a, b in zip(*times))
 
 
 def test_no_load_of_the_attention_kernels_comes_too_early(tmp_path):
