@@ -172,3 +172,10 @@ def test_rows_at_the_edges_of_a_lanes_pieces(mb, T, W, bf16):
     for name, got, ref in (("dgamma", dgamma, dg_ref), ("dbeta", dbeta, db_ref)):
         _, rf = err_stats(got.double().cpu().numpy(), ref)
         assert rf <= (1e-4 if bf16 else 1e-5), "%s rel_fro=%.3e" % (name, rf)
+
+
+@pytest.mark.parametrize("W,bf16", [(1536, True), (1544, True), (768, False), (772, False)])
+@pytest.mark.parametrize("T", [1, 2051, 8200])
+def test_rows_on_both_sides_of_three_pieces(mb, T, W, bf16):
+    """192 pieces of 16 bytes, three per lane, and one piece more."""
+    test_rows_at_the_edges_of_a_lanes_pieces(mb, T, W, bf16)
