@@ -135,14 +135,14 @@ def packed_call(mb, q, k, v, do, cu, L, out, **opt):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("rows", [False, True])
-@pytest.mark.parametrize("L,lengths,stride", [(129, [129, 1, 128, 65], ((1 << 30) // 129 - 1) // 8 * 8), (128, [128, 1, 127, 33], (1 << 24) - 8)])
+@pytest.mark.parametrize("L,lengths,stride", [(129, [129, 1, 128, 65], ((1 << 30) // 129 - 1) // 8 * 8), (128, [128, 1, 127, 33], (1 << 24) - 8),
+                                              (129, [129, 1, 128, 65], ((1 << 30) // 129 // 8 + 1) * 8)])
 def test_rows_as_far_apart_as_32_bit_offsets_allow(L, lengths, stride, rows):
-    """The any-length kernels with a span just under 2^31 bytes (tiles requested past the end wrap round 2^32), the single-tile
-    forward with units between 2^31 and 2^32 bytes: the same bits as from dense rows."""
+    """The any-length kernels with a span just under 2^31 bytes (tiles requested past the end wrap round 2^32) and just over it (an
+    address per lane), the single-tile forward with units between 2^31 and 2^32 bytes: the same bits as from dense rows."""
     from paper_2312_17482_amd import binding as mb
     print("attention rows %d elements apart, L=%d rows=%s" % (stride, L, rows), flush=True)
     H, D, T = 2, 64, sum(lengths)
-    assert L <= 128 or L * stride * 2 < 1 << 31
     gen = torch.Generator(device="cuda").manual_seed(L)
     cu = torch.tensor(np.concatenate([[0], np.cumsum(lengths)]), dtype=torch.int32, device="cuda")
     data = torch.randn((4, T, H, D), generator=gen, device="cuda").bfloat16()
@@ -155,6 +155,33 @@ def test_rows_as_far_apart_as_32_bit_offsets_allow(L, lengths, stride, rows):
     for name, a, b in zip(("o", "dq", "dk", "dv", "lse"), got, dense):
         assert torch.equal(a, b), name
     assert torch.equal(far[:, :4], data.transpose(0, 1))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,lengths", [(600, LENGTHS), (128, [n for n in LENGTHS if n <= 128])])
+@pytest.mark.parametrize("keys", [None, 1, 64, 70])
+def test_listed_rows_with_a_key_limit_give_the_bits_of_packed_ones(L, lengths, keys):
+    """token_rows with holes and key_lens in one call: the rows of keys and of queries end at different places."""
+    from paper_2312_17482_amd import binding as mb
+    print("attention listed rows L=%d keys=%s" % (L, keys), flush=True)
+    H, T = 2, sum(lengths)
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lengths)]), dtype=torch.int32, device="cuda")
+    opt = {}
+    if keys:
+        opt["key_lens"] = torch.tensor([max(1, min(n, keys * max(n // 100, 1))) for n in lengths], dtype=torch.int32, device="cuda")
+    data = torch.randn((4, T, H, 64), generator=gen, device="cuda").bfloat16()
+    dense = packed_call(mb, *data, cu, L, torch.zeros_like(data), **opt)
+    rows = torch.arange(T, device="cuda") // 2 * 3 + torch.arange(T, device="cuda") % 2
+    spread = torch.full((8, 2 * T, H, 64), float("nan"), dtype=torch.bfloat16, device="cuda")   # what is not listed is NaN
+    spread[:4, rows] = data
+    spread[4:, rows] = 0.0
+    got = packed_call(mb, *spread[:4], cu, L, spread[4:], token_rows=rows.to(torch.int32), **opt)
+    for name, a, b in zip(("o", "dq", "dk", "dv"), got, dense):
+        assert torch.equal(a[rows], b), name
+    assert torch.equal(got[4], dense[4])
+    unlisted = torch.ones(2 * T, dtype=torch.bool, device="cuda").index_fill(0, rows, False)
+    assert torch.isnan(spread[:, unlisted]).all()
 
 
 @pytest.mark.gpu
