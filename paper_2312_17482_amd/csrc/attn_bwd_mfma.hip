@@ -54,7 +54,7 @@ constexpr int kRing = 4;                            // regions that the tiles of
 // kMode (both kernels; see kRowsIdentity .. in common.h): the rows of a sequence whose tokens sit in consecutive
 // rows of the activation buffers, spanning fewer than 2^31 bytes, are loaded through descriptors that start at its first row
 // and end at its last one: a lane's offset grows by a constant from tile to tile, and rows past the end arrive as zeros
-// without a compare.  Otherwise every lane forms its own address (row index looked up in token_rows when given).
+// without a compare.  Otherwise every lane forms its own address (row numbers out of token_rows, if given: StageRows).
 constexpr int kRsrcFlags = 0x00020000;   // raw buffer, 32-bit data format (gfx9 family)
 
 template <int kMode>
@@ -752,8 +752,7 @@ constexpr int kDsPitch = 136;   // LDS row pitch of dS in bf16 (272 B)
 // kMode (see kRowsIdentity .. in common.h): a unit whose tokens sit in consecutive buffer rows moves all its rows with
 // buffer instructions: one descriptor per tensor and unit that starts at the unit's first row and ends with its last
 // (built with scalar arithmetic) and one per-lane byte offset per tensor that is the same for every unit, to which
-// the step from one group of rows to the next is added (the whole offset must be the vector operand: the scalar
-// offset of a buffer instruction takes no part in its range check).  Rows past the unit's end then read as zeros and
+// the step from one group of rows to the next is added.  Rows past the unit's end then read as zeros and
 // are dropped on a store without a compare, and forming an address is one 32-bit add.  (With per-lane 64-bit
 // addresses every row access costs a 64-bit multiply, three quarter-rate vector instructions: a fifth of all vector
 // instructions of this kernel were address arithmetic.)

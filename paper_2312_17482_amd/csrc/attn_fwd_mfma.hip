@@ -27,7 +27,7 @@ constexpr int kVStride = 80;   // LDS row pitch of V in bf16 (160 B): 4-row tran
 
 // Any sequence length: tiles of 64 keys with a running (online) softmax.  The tiles go straight to LDS, two steps ahead,
 // through a ring of three regions (attn_stage.h): no registers and no vector instructions on the way, no bank conflicts,
-// one barrier per tile.  At most 168 registers and 48 KB of LDS, so that three workgroups share a compute unit.
+// one barrier per tile.  At most 168 registers and 50 KB of LDS, so that three workgroups share a compute unit.
 // Same arithmetic as the single-tile kernel below (bias in the accumulator's start value, scale folded into the exponent);
 // the running output is rescaled only when some query's maximum actually moved.
 // What bounds it at full length: the vector unit.  A tile costs a wave about 155 vector instructions of 4 cycles, 32
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(const int32_t* 
 // kMode (see kRowsIdentity .. in common.h): the rows of a sequence whose tokens sit in consecutive rows of the activation
 // buffers, spanning fewer than 2^31 bytes, are loaded through descriptors that start at its first row and end at its last
 // one: a lane's offset grows by a constant from tile to tile, and rows past the end arrive as zeros without a compare.
-// Otherwise every lane forms its own address (row index looked up in token_rows when given).
+// Otherwise every lane forms its own address (row numbers out of token_rows, if given: StageRows).
 template <int kMode>
 __global__ __launch_bounds__(256, 3) void attn_fwd_tiled_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, int64_t qs,

@@ -22,7 +22,9 @@ __device__ __forceinline__ uint32_t stage_lane_off(int lane, int odd, int64_t st
 }
 
 // One head of `count` consecutive rows (fewer than 2^31 bytes) as a descriptor: a lane's offset past the last row is out of
-// its range and deposits zeros.
+// its range and deposits zeros.  (From 129 rows on the last row of a tile that holds any stays below 2^32 bytes, so what has to
+// be zeros is.  In the tiles that are requested beyond it an offset may wrap round: those loads stay inside the descriptor and
+// nobody reads what they bring.)
 __device__ __forceinline__ u32x4 stage_rsrc_bytes(const void* base, uint32_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(base);
   u32x4 r;

@@ -108,13 +108,14 @@ constexpr int kGemmLds = kStages * (64 * kMB + 32 * kWN * kNB) * kBK + 2 * kWN *
 // from memory (two and three stages, 48 weights in turn; 64-token tiles: 8 steps 945 x 1536 8.5 and 7.3 us, 12 steps
 // 1500 x 768 11.4 and 8.9, 200 x 6144 15.5 and 12.0, 48 steps 4000 x 768 38 and 26, 4 steps 5.9 and 5.9; 128-token tiles: 12
 // steps 2500 x 2304 15.1 and 14.0, 945 x 6144 18.7 and 15.6, 16 steps 1500 x 3072 22.7 and 17.5).  Out of a warm L2 it makes
-// no difference up to 12 steps (6.74 and 6.80, 8.19 and 8.24, 8.25 and 8.32, 14.3 and 13.8, 14.0 and 13.9); with the third
-// stage's loads in front of the first products and behind the last ones it cost 0.3 us.
+// little difference up to 12 steps (6.74 and 6.80, 8.19 and 8.24, 8.25 and 8.32, 14.3 and 13.8, 14.0 and 13.9; a gated product
+// of 80 to 350 tokens 0.1 us more, 24505 x 192 with 8 steps 10.9 and 11.2); with the third stage's loads in front of the first
+// products and behind the last ones it cost 0.3 us.
 constexpr int kThirdStageFrom = 8;
 
 // One workgroup of 2 kWN waves (2 along the tokens by kWN along the weight rows) per compute unit walks the tiles
 // blockIdx.x, + gridDim.x, ...  A tile is 64 kMB tokens x 32 kWN kNB weight rows; a wave computes 32 kMB x 32 kNB of it.
-// Wide (4 x 2 blocks, two stages): 64 to 320 tokens x 256.  Narrow (2 x 1 blocks, eight stages): 64 x 64 for products of
+// Wide (4 x 2 blocks, two stages, for 64 and 128 tokens three from kThirdStageFrom steps on): 64 to 320 tokens x 256.  Narrow (2 x 1 blocks, eight stages): 64 x 64 for products of
 // few rows and columns, whose time is the latency of a step: a sixteenth of the bytes per step, seven steps in flight.
 // X rows are K elements long.  The weight is stored by output column, rows of K elements (kWT false), or the other way round,
 // K rows of ldw elements with the output columns along them (kWT: the weights of the forward, contracted over their other
